@@ -132,6 +132,19 @@ __device__ __forceinline__ void dot2_acc(double &s, double &c, double x, double 
     s = t;
     c += e + pe;
 }
+// The same in four operations, for sums that start at s = DOT_BIAS and products
+// smaller than s: then t - s, of t = s + x*y rounded once, is exact and x*y - (t - s)
+// is the whole rounding error.  The factors summed here are components of T_n(H~) xi
+// with |T_n| <= 1 and |xi_i| <= 1, so products stay near 1 and a thread's sum far
+// above -DOT_BIAS; the bias costs 2^-106 DOT_BIAS (1e-27) per product.  Larger
+// products (a scale that does not enclose the spectrum) are summed to FP64 accuracy.
+constexpr double DOT_BIAS = 98304.0;   // 1.5 * 2^16
+__device__ __forceinline__ void dot2_acc_biased(double &s, double &c, double x, double y)
+{
+    const double t = fma(x, y, s);
+    c += fma(x, y, s - t);
+    s = t;
+}
 __device__ __forceinline__ dd dd_div_d(dd x, double b)
 {
     double q1 = x.hi / b;
@@ -142,9 +155,34 @@ __device__ __forceinline__ dd dd_div_d(dd x, double b)
     return dd_fast_two_sum(q1, q2);
 }
 
-__device__ __forceinline__ double shfl_xor_d(double v, int mask)
+// ---------------------------------------------------------------------------
+// lane exchanges in the vector ALU (ds_bpermute shuffles take 24 cycles each)
+// ---------------------------------------------------------------------------
+// (x, y) -> ([x.low, y.low], [x.high, y.high]), low / high the lower and upper 32 lanes
+__device__ __forceinline__ void swap_halves(double &x, double &y)
 {
-    return __shfl_xor(v, mask, 64);
+    const uint64_t a = (uint64_t)__double_as_longlong(x), b = (uint64_t)__double_as_longlong(y);
+    const auto l = __builtin_amdgcn_permlane32_swap((uint32_t)a, (uint32_t)b, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap((uint32_t)(a >> 32), (uint32_t)(b >> 32), false, false);
+    x = __longlong_as_double((long long)(((uint64_t)h[0] << 32) | l[0]));
+    y = __longlong_as_double((long long)(((uint64_t)h[1] << 32) | l[1]));
+}
+// the same with the even and odd rows of 16 lanes
+__device__ __forceinline__ void swap_rows(double &x, double &y)
+{
+    const uint64_t a = (uint64_t)__double_as_longlong(x), b = (uint64_t)__double_as_longlong(y);
+    const auto l = __builtin_amdgcn_permlane16_swap((uint32_t)a, (uint32_t)b, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap((uint32_t)(a >> 32), (uint32_t)(b >> 32), false, false);
+    x = __longlong_as_double((long long)(((uint64_t)h[0] << 32) | l[0]));
+    y = __longlong_as_double((long long)(((uint64_t)h[1] << 32) | l[1]));
+}
+// the value N lanes up within the row of 16 (a rotation)
+template <int N> __device__ __forceinline__ double row_ror(double v)
+{
+    const uint64_t a = (uint64_t)__double_as_longlong(v);
+    const uint32_t l = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)a, 0x120 + N, 0xf, 0xf, false);
+    const uint32_t h = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(a >> 32), 0x120 + N, 0xf, 0xf, false);
+    return __longlong_as_double((long long)(((uint64_t)h << 32) | l));
 }
 
 }  // namespace kpm

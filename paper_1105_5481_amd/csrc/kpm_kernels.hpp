@@ -176,28 +176,34 @@ template <> struct Arith<float> {
     }
 };
 
-// Dot-product accumulators: (sum, error) pairs in FP64 for FP64 vectors; for
-// FP32 vectors the products are exact in FP64 and a plain FP64 sum suffices.
+// Dot-product accumulators: (sum, error) pairs in FP64 for FP64 vectors, started at
+// DOT_BIAS (four operations per product instead of ten); for FP32 vectors the
+// products are exact in FP64 and a plain FP64 sum suffices.  (x0 + x1, x2 + x3) are
+// the two sums.
 template <typename S> struct Dots;
 template <> struct Dots<double> {
-    double s0 = 0.0, c0 = 0.0, s1 = 0.0, c1 = 0.0;
+    double s0 = DOT_BIAS, c0 = 0.0, s1 = DOT_BIAS, c1 = 0.0;
     __device__ __forceinline__ void add(V16<double>::T o, V16<double>::T v)
     {
 #pragma unroll
         for (int l = 0; l < 2; ++l) {
-            dot2_acc(s0, c0, o[l], o[l]);
-            dot2_acc(s1, c1, o[l], v[l]);
+            dot2_acc_biased(s0, c0, o[l], o[l]);
+            dot2_acc_biased(s1, c1, o[l], v[l]);
         }
     }
     __device__ __forceinline__ void norm_only(V16<double>::T o)
     {
 #pragma unroll
-        for (int l = 0; l < 2; ++l) dot2_acc(s0, c0, o[l], o[l]);
+        for (int l = 0; l < 2; ++l) dot2_acc_biased(s0, c0, o[l], o[l]);
     }
+    __device__ __forceinline__ double x0() const { return s0 - DOT_BIAS; }
+    __device__ __forceinline__ double x1() const { return c0; }
+    __device__ __forceinline__ double x2() const { return s1 - DOT_BIAS; }
+    __device__ __forceinline__ double x3() const { return c1; }
     static constexpr bool DD = true;
 };
 template <> struct Dots<float> {
-    double s0 = 0.0, c0 = 0.0, s1 = 0.0, c1 = 0.0;
+    double s0 = 0.0, s1 = 0.0;
     __device__ __forceinline__ void add(V16<float>::T o, V16<float>::T v)
     {
 #pragma unroll
@@ -215,74 +221,114 @@ template <> struct Dots<float> {
             s0 = fma(a, a, s0);
         }
     }
+    __device__ __forceinline__ double x0() const { return s0; }
+    __device__ __forceinline__ double x1() const { return 0.0; }
+    __device__ __forceinline__ double x2() const { return s1; }
+    __device__ __forceinline__ double x3() const { return 0.0; }
     static constexpr bool DD = false;
 };
+// FP64 sums of any magnitude (vectors that are not near 1): ten operations per product.
+struct DotsWide {
+    double s0 = 0.0, c0 = 0.0, s1 = 0.0, c1 = 0.0;
+    __device__ __forceinline__ void add(V16<double>::T o, V16<double>::T v)
+    {
+#pragma unroll
+        for (int l = 0; l < 2; ++l) {
+            dot2_acc(s0, c0, o[l], o[l]);
+            dot2_acc(s1, c1, o[l], v[l]);
+        }
+    }
+    __device__ __forceinline__ void norm_only(V16<double>::T o)
+    {
+#pragma unroll
+        for (int l = 0; l < 2; ++l) dot2_acc(s0, c0, o[l], o[l]);
+    }
+    __device__ __forceinline__ double x0() const { return s0; }
+    __device__ __forceinline__ double x1() const { return c0; }
+    __device__ __forceinline__ double x2() const { return s1; }
+    __device__ __forceinline__ double x3() const { return c1; }
+    static constexpr bool DD = true;
+};
 
-// Sum (x0 + x1, x2 + x3) over the wavefront: every lane receives the sums,
-// as double-double pairs (x0, x1), (x2, x3) when DD, else in x0 and x2 with
-// x1 = x3 = 0.
+// Sums of x0 + x1 and x2 + x3 over the wavefront, in (a, b): the lower 32 lanes
+// receive the first, the upper 32 the second (as a double-double when DD, else in a
+// alone).  The first exchange gives each half of the wave one of the two sums, so a
+// reduction is six additions, and no exchange goes through the LDS: with ds_bpermute
+// shuffles of both sums it was twelve additions and 48 shuffles of 24 cycles, most of a
+// step of the single-workgroup solves.
 template <bool DD>
-__device__ __forceinline__ void wave_reduce(double &x0, double &x1, double &x2, double &x3)
+__device__ __forceinline__ void wave_reduce(double x0, double x1, double x2, double x3, double &a, double &b)
 {
     if (DD) {
-        dd a = dd_fast_two_sum(x0, x1), b = dd_fast_two_sum(x2, x3);
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            dd oa{shfl_xor_d(a.hi, off), shfl_xor_d(a.lo, off)};
-            dd ob{shfl_xor_d(b.hi, off), shfl_xor_d(b.lo, off)};
-            a = dd_add(a, oa);
-            b = dd_add(b, ob);
-        }
-        x0 = a.hi; x1 = a.lo; x2 = b.hi; x3 = b.lo;
+        dd p = dd_two_sum(x0, x1), q = dd_two_sum(x2, x3);
+        swap_halves(p.hi, q.hi);
+        swap_halves(p.lo, q.lo);
+        p = dd_add(p, q);
+        q = p;
+        swap_rows(p.hi, q.hi);
+        swap_rows(p.lo, q.lo);
+        p = dd_add(p, q);
+        p = dd_add(p, dd{row_ror<8>(p.hi), row_ror<8>(p.lo)});
+        p = dd_add(p, dd{row_ror<4>(p.hi), row_ror<4>(p.lo)});
+        p = dd_add(p, dd{row_ror<2>(p.hi), row_ror<2>(p.lo)});
+        p = dd_add(p, dd{row_ror<1>(p.hi), row_ror<1>(p.lo)});
+        a = p.hi;
+        b = p.lo;
     } else {
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            x0 += shfl_xor_d(x0, off);
-            x2 += shfl_xor_d(x2, off);
-        }
-        x1 = 0.0;
-        x3 = 0.0;
+        swap_halves(x0, x2);
+        a = x0 + x2;
+        b = a;
+        swap_rows(a, b);
+        a += b;
+        a += row_ror<8>(a);
+        a += row_ror<4>(a);
+        a += row_ror<2>(a);
+        a += row_ror<1>(a);
+        b = 0.0;
     }
 }
 
-// The wavefront's sums of (x0 + x1, x2 + x3); lane 0 stores the four doubles
-// (hi, lo, hi, lo) at dst.
+// The wavefront's sums of (x0 + x1, x2 + x3), stored as four doubles (hi, lo, hi, lo) at dst.
 template <bool DD>
 __device__ __forceinline__ void wave_reduce_store(double x0, double x1, double x2, double x3, double *dst)
 {
-    wave_reduce<DD>(x0, x1, x2, x3);
-    if ((threadIdx.x & 63) == 0) {
-        dst[0] = x0; dst[1] = x1; dst[2] = x2; dst[3] = x3;
+    double a, b;
+    wave_reduce<DD>(x0, x1, x2, x3, a, b);
+    const int lane = threadIdx.x & 63;
+    if ((lane & 31) == 0) {
+        dst[lane >> 4] = a;
+        dst[(lane >> 4) + 1] = b;
     }
 }
+template <typename A> __device__ __forceinline__ void wave_reduce_store(const A &d, double *dst)
+{
+    wave_reduce_store<A::DD>(d.x0(), d.x1(), d.x2(), d.x3(), dst);
+}
 
-// Sum (x0 + x1, x2 + x3) over the block in a fixed order; thread 0 stores
-// the four doubles (hi, lo, hi, lo) at dst.
+// Sum (x0 + x1, x2 + x3) over the block in a fixed order, stored as four doubles
+// (hi, lo, hi, lo) at dst; thread 0 adds the waves' first sums, thread 1 the second.
 template <bool DD, int NT = BLOCK>
 __device__ __forceinline__ void block_reduce_store(double x0, double x1, double x2, double x3, double *dst)
 {
     __shared__ double red[NT / 64][4];
-    wave_reduce<DD>(x0, x1, x2, x3);
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    if (lane == 0) {
-        red[w][0] = x0; red[w][1] = x1; red[w][2] = x2; red[w][3] = x3;
-    }
+    wave_reduce_store<DD>(x0, x1, x2, x3, red[threadIdx.x >> 6]);
     __syncthreads();
-    if (threadIdx.x == 0) {
-        dd a{red[0][0], red[0][1]}, b{red[0][2], red[0][3]};
+    if (threadIdx.x < 2) {
+        const int o = threadIdx.x * 2;
+        dd a{red[0][o], red[0][o + 1]};
 #pragma unroll
         for (int k = 1; k < NT / 64; ++k) {
-            if (DD) {
-                a = dd_add(a, dd{red[k][0], red[k][1]});
-                b = dd_add(b, dd{red[k][2], red[k][3]});
-            } else {
-                a.hi += red[k][0];
-                b.hi += red[k][2];
-            }
+            if (DD) a = dd_add(a, dd{red[k][o], red[k][o + 1]});
+            else a.hi += red[k][o];
         }
-        dst[0] = a.hi; dst[1] = a.lo; dst[2] = b.hi; dst[3] = b.lo;
+        dst[o] = a.hi;
+        dst[o + 1] = a.lo;
     }
     __syncthreads();
+}
+template <int NT = BLOCK, typename A> __device__ __forceinline__ void block_reduce_store(const A &d, double *dst)
+{
+    block_reduce_store<A::DD, NT>(d.x0(), d.x1(), d.x2(), d.x3(), dst);
 }
 
 // ---------------------------------------------------------------------------
@@ -468,7 +514,7 @@ __global__ __launch_bounds__(BLOCK) void k_init(const Inst *__restrict__ tab, co
                     acc.norm_only(v);
                 }
             }
-            block_reduce_store<Dots<S>::DD>(acc.s0, acc.c0, acc.s1, acc.c1, part + (size_t)(sg * I.nct + ct) * 4);
+            block_reduce_store(acc, part + (size_t)(sg * I.nct + ct) * 4);
         }
     } else {
         const ItemRange ir = item_range(I, I.tiles, 1);
@@ -484,7 +530,7 @@ __global__ __launch_bounds__(BLOCK) void k_init(const Inst *__restrict__ tab, co
                     acc.norm_only(v);
                 }
             }
-            block_reduce_store<Dots<S>::DD>(acc.s0, acc.c0, acc.s1, acc.c1, part + (size_t)t * 4);
+            block_reduce_store(acc, part + (size_t)t * 4);
         }
     }
 }
@@ -650,16 +696,16 @@ __global__ __launch_bounds__(BLOCK) void k_step_march(const Inst *__restrict__ t
                 v0 = va;
             }
         }
-        block_reduce_store<Dots<S>::DD>(acc.s0, acc.c0, acc.s1, acc.c1, part + (size_t)(sg * I.nct + ct) * 4);
+        block_reduce_store(acc, part + (size_t)(sg * I.nct + ct) * 4);
     }
 }
 
 // ---------------------------------------------------------------------------
 // the fused recursion step, flat form (CSR; lattices on request)
 // ---------------------------------------------------------------------------
-template <typename S, int OPK, bool WIDE>
+template <typename S, int OPK, bool WIDE, typename A_>
 __device__ __forceinline__ void flat_elem(const Inst &I, uint32_t e, const void *cur, void *nxt, bool first, S hop,
-                                          Dots<S> &acc)
+                                          A_ &acc)
 {
     typedef typename V16<S>::T T;
     typedef Mem<S, WIDE> G;
@@ -769,7 +815,7 @@ __global__ __launch_bounds__(BLOCK) void k_step_flat(const Inst *__restrict__ ta
             const uint32_t e = t * (uint32_t)(BLOCK * I.tpt) + (uint32_t)(u * BLOCK) + threadIdx.x;
             if (e < I.nel) flat_elem<S, OPK, WIDE>(I, e, cur, nxt, first, hop, acc);
         }
-        block_reduce_store<Dots<S>::DD>(acc.s0, acc.c0, acc.s1, acc.c1, part + (size_t)t * 4);
+        block_reduce_store(acc, part + (size_t)t * 4);
     }
 }
 
@@ -887,7 +933,7 @@ __global__ __launch_bounds__(SMALL_BLOCK) void k_solve_small(const Inst *__restr
             b0[e] = v;
             acc.norm_only(v);
         }
-        wave_reduce_store<Dots<S>::DD>(acc.s0, acc.c0, acc.s1, acc.c1, I.partial + (size_t)w * 4);
+        wave_reduce_store(acc, I.partial + (size_t)w * 4);
     }
     __syncthreads();   // r_0 complete
     for (int32_t n = 0; n < I.K; ++n) {
@@ -900,7 +946,7 @@ __global__ __launch_bounds__(SMALL_BLOCK) void k_solve_small(const Inst *__restr
             nxt[e] = out;
             acc.add(out, cur[e]);
         }
-        wave_reduce_store<Dots<S>::DD>(acc.s0, acc.c0, acc.s1, acc.c1,
+        wave_reduce_store(acc,
                                        I.partial + ((size_t)(n + 1) * SMALL_WAVES + w) * 4);
         // step n's LDS writes before step n + 1 reads them, and its reads before they are overwritten
         __syncthreads();

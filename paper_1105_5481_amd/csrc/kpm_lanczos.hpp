@@ -37,12 +37,12 @@ __global__ __launch_bounds__(BLOCK) void k_lz_matvec(const Inst *__restrict__ ta
     const ItemRange ir = item_range(I, I.tiles, 1);
     for (uint32_t it = ir.first; it < ir.count; it += ir.stride) {
         const uint32_t t = ir.ub + it;
-        Dots<double> acc;
+        DotsWide acc;
         for (int q = 0; q < I.tpt; ++q) {
             const uint32_t e = t * (uint32_t)(BLOCK * I.tpt) + (uint32_t)(q * BLOCK) + threadIdx.x;
             if (e < I.nel) flat_elem<double, OPK, WIDE>(I, e, v, u, true, hop, acc);
         }
-        block_reduce_store<true>(acc.s0, acc.c0, acc.s1, acc.c1, part + (size_t)t * 4);
+        block_reduce_store(acc, part + (size_t)t * 4);
     }
 }
 
@@ -61,7 +61,7 @@ __global__ __launch_bounds__(BLOCK) void k_lz_update(const Inst *__restrict__ ta
     const ItemRange ir = item_range(I, I.tiles, 1);
     for (uint32_t it = ir.first; it < ir.count; it += ir.stride) {
         const uint32_t t = ir.ub + it;
-        Dots<double> acc;
+        DotsWide acc;
         for (int q = 0; q < I.tpt; ++q) {
             const uint32_t e = t * (uint32_t)(BLOCK * I.tpt) + (uint32_t)(q * BLOCK) + threadIdx.x;
             if (e < I.nel) {
@@ -78,7 +78,7 @@ __global__ __launch_bounds__(BLOCK) void k_lz_update(const Inst *__restrict__ ta
                 acc.norm_only(w);
             }
         }
-        block_reduce_store<true>(acc.s0, acc.c0, 0.0, 0.0, part + (size_t)t * 4);
+        block_reduce_store(acc, part + (size_t)t * 4);
     }
 }
 

@@ -92,8 +92,7 @@ __global__ __launch_bounds__(TB_BLOCK) void k_init_tb(const Inst *__restrict__ t
                 G::st(cur, i * C + c, v);
                 a.norm_only(v);
             }
-        block_reduce_store<Dots<S>::DD, TB_BLOCK>(a.s0, a.c0, a.s1, a.c1,
-                                                  I.partial + (size_t)(sg * I.nct * Gs + unit) * 4);
+        block_reduce_store<TB_BLOCK>(a, I.partial + (size_t)(sg * I.nct * Gs + unit) * 4);
     }
 }
 
@@ -257,8 +256,7 @@ __global__ __launch_bounds__(TB_BLOCK) __attribute__((amdgpu_waves_per_eu(TB_WAV
         }
 #pragma unroll
         for (int k = 0; k < D; ++k)
-            block_reduce_store<Dots<S>::DD, TB_BLOCK>(acc[k].s0, acc[k].c0, acc[k].s1, acc[k].c1,
-                                                      I.partial + (size_t)((n + 1 + k) % I.pslots) * I.tiles * 4 +
+            block_reduce_store<TB_BLOCK>(acc[k], I.partial + (size_t)((n + 1 + k) % I.pslots) * I.tiles * 4 +
                                                           (size_t)t * 4);
     }
 }

@@ -119,7 +119,7 @@ __global__ __launch_bounds__(TB3_BLOCK) void k_init_tb3(const Inst *__restrict__
                 a.norm_only(v);
             }
         }
-        block_reduce_store<Dots<S>::DD, TB3_BLOCK>(a.s0, a.c0, a.s1, a.c1, I.partial + (size_t)(sg * I.nct * I.C + unit) * 4);
+        block_reduce_store<TB3_BLOCK>(a, I.partial + (size_t)(sg * I.nct * I.C + unit) * 4);
     }
 }
 
@@ -293,12 +293,10 @@ __global__ __launch_bounds__(TB3_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) 
             __syncthreads();
         }
         const uint32_t tslot = sg * I.nct * I.C + unit;
-        block_reduce_store<Dots<S>::DD, TB3_BLOCK>(acc1.s0, acc1.c0, acc1.s1, acc1.c1,
-                                                   I.partial + (size_t)((n + 1) % I.pslots) * I.tiles * 4 +
+        block_reduce_store<TB3_BLOCK>(acc1, I.partial + (size_t)((n + 1) % I.pslots) * I.tiles * 4 +
                                                        (size_t)tslot * 4);
         if constexpr (D == 2)
-            block_reduce_store<Dots<S>::DD, TB3_BLOCK>(acc2.s0, acc2.c0, acc2.s1, acc2.c1,
-                                                       I.partial + (size_t)((n + 2) % I.pslots) * I.tiles * 4 +
+            block_reduce_store<TB3_BLOCK>(acc2, I.partial + (size_t)((n + 2) % I.pslots) * I.tiles * 4 +
                                                            (size_t)tslot * 4);
     }
 }
