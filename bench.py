@@ -44,12 +44,13 @@ WORKLOAD_TEXT = {
 CONFIG3_KERNEL = "k_step_march<float, OP_SPIN3> (multi-instance)"
 TB_KERNEL = {d: "k_step_tbd<float, OP_REAL2, %d> (%d step%s per launch)" % (d, d, "s" if d > 1 else "")
              for d in range(1, 7)}
+CONFIG4_DEPTH = 6    # steps per pass the library takes on the 2048^2 FP32 lattice, R = 64
 TB3_KERNEL = "k_step_tb3<float, OP_SPIN3, 2> (2 steps per launch)"
 
 
 def tb_groups(C, Lx, group=8):
-    """Chunk groups of a 2D blocked solve (the library's rule for KPM_LAUNCH_TB_GROUP = group):
-    none when the whole site already gives a window of 32 sites or more, else the most groups that
+    """Chunk groups by which the library decides whether a 2D solve is blocked (its row must hold the
+    window they give; the tiles it then takes are chosen by estimated time): none when the whole site already gives a window of 32 sites or more, else the most groups that
     keep at least `group` chunks per group and a window of 512 / (C / G) sites within the row."""
     best = 1
     if group <= 0 or 512 // C >= 32:
@@ -64,8 +65,8 @@ def tb_groups(C, Lx, group=8):
 
 
 def tb_depth(tblock, prec, C=16, spin=False, Lx=1 << 30, group=8):
-    """Steps of the deepest pass of a temporally blocked solve for a KPM_LAUNCH_TBLOCK value (the
-    library's rule: -1 gives 4 for FP32 real hopping and for FP32 spin hopping in chunk groups, 3
+    """Halo by which the library decides whether a 2D solve is blocked (its columns must hold two) for
+    a KPM_LAUNCH_TBLOCK value (-1 gives 4 for FP32 real hopping and for FP32 spin hopping in chunk groups, 3
     otherwise; 1 pairs; at most a quarter of the window of 512 / Cg sites, Cg = 16-byte chunks per
     site in one chunk group)."""
     G = tb_groups(C, Lx, group)
@@ -74,11 +75,6 @@ def tb_depth(tblock, prec, C=16, spin=False, Lx=1 << 30, group=8):
     else:
         d = tblock if tblock >= 3 else 2
     return min(d, 512 // (C // G) // 4)
-
-
-def kpm_default_tblock():
-    """The library's default KPM_LAUNCH_TBLOCK."""
-    return kpm_default_launch("tblock")
 
 
 def kpm_default_launch(key):
@@ -574,7 +570,7 @@ def bench_lattice(args, workload, steps, warmup, fp64=True, cpu=True):
     L = kpm.lib()
     sp = ctypes.c_void_p(stream.cuda_stream)
     K = M // 2
-    solve_mode = {}
+    solve_mode, solve_depth = {}, {}
 
     def run_step(state, instance, ev=None):
         h, ws, nbytes, mu, om, rho = state
@@ -582,7 +578,7 @@ def bench_lattice(args, workload, steps, warmup, fp64=True, cpu=True):
         s = ctypes.c_void_p()
         kpm._check(L.kpm_solve_begin(h.handle, M, R, vec, seed, instance, ws.data_ptr(), nbytes, sp,
                                      ctypes.byref(s)), "kpm_solve_begin")                         # a1
-        solve_mode[h.prec] = L.kpm_solve_mode(s)
+        solve_mode[h.prec], solve_depth[h.prec] = L.kpm_solve_mode(s), L.kpm_solve_depth(s)
         if ev is not None:
             ev[0].record(stream)
         rem = ctypes.c_int32()
@@ -614,12 +610,7 @@ def bench_lattice(args, workload, steps, warmup, fp64=True, cpu=True):
     updates = float(N) * M * R
     value = updates / (dt32 / steps)
     tblocked = solve_mode.get(kpm.F32) in (3, 4)     # 2D blocked passes (3), 3D two-step passes (4)
-    chunks = -(-R * (2 if cplx else 1) // 4)  # 16-byte chunks per site (FP32)
-    if solve_mode.get(kpm.F32) == 4:
-        depth = 2
-    else:
-        lk = kpm.get_launch()
-        depth = tb_depth(lk["tblock"], kpm.F32, chunks, lat.hop == wl.HOP_SPIN, lat.L[0], lk["tb_group"]) if tblocked else 1
+    depth = solve_depth.get(kpm.F32, 1)
     nrec = K if tblocked else K - 1          # begin runs step 0 except with temporal blocking
     step_us = rec32 * 1e3 / nrec             # per recursion step
     launch_us = step_us * depth
@@ -716,7 +707,7 @@ def main():
     ap.add_argument("--streaming", type=int, default=-1)
     ap.add_argument("--wave-mib", type=int, default=-1, help="batched solves: MiB of state per wave, 0 = one wave")
     ap.add_argument("--tblock", type=int, default=-1, help="2D lattices: steps per pass, 1 two, 3..6, 0 one step")
-    ap.add_argument("--tb-group", type=int, default=-1, help="2D blocked solves: least chunks per chunk group (0: one group)")
+    ap.add_argument("--tb-group", type=int, default=-1, help="2D blocked solves: least chunks per chunk group (0: as few groups as possible)")
     ap.add_argument("--tb3", type=int, default=-2, help="3D two-step passes: 1 on, 0 off, -1 FP32 real hopping")
     ap.add_argument("--calib-copy", action="store_true",
                     help="first run a plain 1 GiB device copy three times (counter calibration under rocprofv3)")
@@ -742,7 +733,7 @@ def main():
         cfg = getattr(wl, args.workload)()
         kern = {"config2": TB3_KERNEL if kpm_default_launch("tb3") == 1 else "k_step_march<float, OP_SPIN3>",
                 "config3": CONFIG3_KERNEL,
-                "config4": TB_KERNEL[tb_depth(kpm_default_tblock(), 1)]}[args.workload]
+                "config4": TB_KERNEL[CONFIG4_DEPTH]}[args.workload]
         extra = {"config2": "--no-fp64 --no-cpu-baseline --no-serve ", "config4": "--no-fp64 --no-cpu-baseline --no-serve --no-secondary ",
                  "config3": ""}[args.workload]
         cmds = [f"rocprofv3 --pmc {c} --output-format csv -d <dir> -o p -- python3 bench.py --workload "

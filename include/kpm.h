@@ -251,6 +251,9 @@ void kpm_solve_free(kpm_solve *s);
  * begin), 3 temporal blocking (1 to 6 steps per launch, KPM_LAUNCH_TBLOCK);
  * -1 for NULL. */
 int32_t kpm_solve_mode(const kpm_solve *s);
+/* Recursion steps of the solve's deepest launch (mode 3 and the 3D blocked passes:
+ * up to 6; else 1); -1 for NULL. */
+int32_t kpm_solve_depth(const kpm_solve *s);
 
 /* Many independent solves in one set of launches: each instance computes the
  * moments of Eq. (munr) by the recursion of Eq. (rn) exactly as kpm_moments
@@ -378,20 +381,18 @@ kpm_status kpm_start_vectors(int32_t vec, int32_t complex_layout, uint64_t seed,
  *                                vectors and operators total at most this many MiB (default
  *                                224, so a wave stays in the Infinity Cache); a wave runs all
  *                                its recursion steps before the next starts.  0 = one wave
- *   KPM_LAUNCH_TBLOCK            solves on 2D lattices (real or spin hopping; windows of
- *                                floor(512/Cg) sites of Cg <= 64 chunks each (KPM_LAUNCH_TB_GROUP),
- *                                L_x >= 512/Cg) take
- *                                several recursion steps per pass over the vectors (temporal
- *                                blocking; 4 vector buffers instead of 2, bitwise the same
- *                                vectors; in a dynamic batch they share blocked launches):
+ *   KPM_LAUNCH_TBLOCK            solves on 2D lattices (real or spin hopping) whose row holds
+ *                                512 / Cg sites (Cg chunks per site, in groups of at least 8
+ *                                beyond 16) take several recursion steps per pass over the
+ *                                vectors (temporal blocking; 4 vector buffers instead of 2,
+ *                                bitwise the same vectors; in a dynamic batch they share
+ *                                blocked launches):
  *                                D = 3 .. 6: D steps per pass where at least D remain (only
  *                                r_{n+D-1} and r_{n+D} are written; x-tiles with D-site
  *                                halos, L_y >= 2D), shorter passes for the rest; -1
- *                                (default): D = 4 for FP32 real hopping and for FP32
- *                                spin hopping split into chunk groups, else 3; 1: two
- *                                steps per pass (L_y >= 4); 0: one step per pass.  D is
- *                                capped at 128/C (a quarter of the 512/C-site window);
- *                                below 2 the solve takes one step per pass.  Batched
+ *                                (default): the depth with the least estimated time per step;
+ *                                1: two steps per pass (L_y >= 4); 0: one step per pass.  D is
+ *                                capped at a quarter of the tile's window.  Batched
  *                                solves (kpm_moments_batched) always take one step per
  *                                pass
  *   KPM_LAUNCH_TB3               solves on 3D lattices (KPM_LAUNCH_TBLOCK not 0) take two
@@ -401,12 +402,12 @@ kpm_status kpm_start_vectors(int32_t vec, int32_t complex_layout, uint64_t seed,
  *                                lattice, -1 (default) for FP32 recursions with real
  *                                hopping only, 0 never.  Needs L_x L_y <= 1024 sites or
  *                                L_x <= 170
- *   KPM_LAUNCH_TB_GROUP          2D temporally blocked solves with more than 16 chunks per
- *                                site split its C chunks into groups of at least this many
- *                                chunks (default 8 = 128 bytes, 0 = one group), as many groups
- *                                as keep the window of floor(512 / chunks per group) sites
- *                                within L_x: a wider window recomputes and re-reads a smaller
- *                                halo share
+ *   KPM_LAUNCH_TB_GROUP          2D temporally blocked solves split a site's C chunks into groups
+ *                                of Cg and hold windows of 256 / Cg sites within L_x: a wider
+ *                                window recomputes and re-reads a smaller halo share.  -1
+ *                                (default): Cg with the least estimated time per step; g >= 1:
+ *                                at least g chunks (where the row allows); 0: as few groups
+ *                                as leave a window of 8 sites
  * The partial sums of the dot products are formed per work item, so the
  * moments do not depend on the grid (MAX_BLOCKS) nor on the batch an instance
  * runs in; the other keys change the work items and with them the order in

@@ -102,6 +102,7 @@ def lib():
         "kpm_green": (i32, [P, i32, i32, f64, i32, f64, f64, P, P, P, P]),
         "kpm_last_hip_error": (ctypes.c_char_p, []),
         "kpm_solve_mode": (i32, [P]),
+        "kpm_solve_depth": (i32, [P]),
         "kpm_dense_workspace_bytes": (sz, [i64, i32, i32]),
         "kpm_dense_moments": (i32, [P, i64, f64, f64, i32, i32, i32, u64, u64, P, sz, P, P]),
         "kpm_bounds_lanczos": (i32, [P, i32, u64, f64, f64, f64, P, sz, P, P]),

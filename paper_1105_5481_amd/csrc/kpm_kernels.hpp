@@ -51,7 +51,7 @@ struct Inst {
     int32_t opk;
     int32_t has_diag;
     int32_t mode;
-    int32_t xcd;       // items split per XCD (0 none, 1 by units, 2 by segments)
+    int32_t xcd;       // items split per XCD (0 none, 1 by units, 2 by segments, 3 evenly)
     int32_t alt;       // march: odd segments walk downwards
     int32_t nt;        // march: r_{n-1}/r_{n+1} accessed with non-temporal hints
     uint32_t Lx, Ly, Lz, N;
@@ -83,7 +83,7 @@ struct Inst {
     void *tb2, *tb3;   // temporal blocking: buffers 2 and 3 of four (buf0, buf1 are 0 and 1)
     int32_t tbp, tbc;  // ... and which of them hold r_{step0-1}, r_{step0} (batched passes)
     int32_t tbfull, tbrem;  // batched passes of this chunk: tbfull of depth tbh, then one of depth tbrem
-    uint32_t tbg;      // 2D temporal blocking: chunk groups per site (a work item covers C / tbg chunks)
+    uint32_t tbg, tbw; // 2D temporal blocking: chunk groups per site, chunks per group (the last may have fewer)
     double *partial;   // [pslots][tiles][4]
     double *dots;      // [K+1][4] = (nn.hi, nn.lo, nm.hi, nm.lo)
     double *mu;        // [M]
@@ -341,9 +341,18 @@ template <int NT = BLOCK, typename A> __device__ __forceinline__ void block_redu
 //   xcd == 2: XCD x owns segments [x*segs/8, (x+1)*segs/8) of every unit, so a
 //             whole plane stays in one L2;
 //   xcd == 1: XCD x owns units [x*units/8, (x+1)*units/8) of every segment;
+//   xcd == 3: XCD x owns the x-th eighth of all items in the order of seg, then unit
+//             (equal to one item, whatever the units and segments);
 //   xcd == 0: no split.
 struct ItemRange {
-    uint32_t first, stride, count, ub, nu, sb;
+    uint32_t first, stride, count, ub, nu, sb, base;
+    // unit and segment of local item `it`
+    __device__ __forceinline__ void at(uint32_t it, uint32_t &unit, uint32_t &sg) const
+    {
+        const uint32_t q = base + it, sl = q / nu;
+        sg = sb + sl;
+        unit = ub + (q - sl * nu);
+    }
 };
 __device__ __forceinline__ ItemRange item_range(const Inst &I, uint32_t units, uint32_t segs)
 {
@@ -352,9 +361,18 @@ __device__ __forceinline__ ItemRange item_range(const Inst &I, uint32_t units, u
     r.ub = 0;
     r.nu = units;
     r.sb = 0;
+    r.base = 0;
     uint32_t ns = segs;
     if (I.xcd) {
         const uint32_t x8 = bl & 7u;
+        r.first = bl >> 3;
+        r.stride = I.nb >> 3;
+        if (I.xcd == 3) {
+            const uint64_t all = (uint64_t)units * segs;
+            r.base = (uint32_t)((all * x8) >> 3);
+            r.count = (uint32_t)((all * (x8 + 1)) >> 3) - r.base;
+            return r;
+        }
         if (I.xcd == 2) {
             r.sb = (uint32_t)(((uint64_t)segs * x8) >> 3);
             ns = (uint32_t)(((uint64_t)segs * (x8 + 1)) >> 3) - r.sb;
@@ -362,8 +380,6 @@ __device__ __forceinline__ ItemRange item_range(const Inst &I, uint32_t units, u
             r.ub = (uint32_t)(((uint64_t)units * x8) >> 3);
             r.nu = (uint32_t)(((uint64_t)units * (x8 + 1)) >> 3) - r.ub;
         }
-        r.first = bl >> 3;
-        r.stride = I.nb >> 3;
     } else {
         r.first = bl;
         r.stride = I.nb;
@@ -499,9 +515,8 @@ __global__ __launch_bounds__(BLOCK) void k_init(const Inst *__restrict__ tab, co
         const ItemRange ir = item_range(I, I.nct, I.nseg);
         const uint32_t PC = I.P * I.C;
         for (uint32_t it = ir.first; it < ir.count; it += ir.stride) {
-            const uint32_t sl = it / ir.nu;
-            const uint32_t sg = ir.sb + sl;
-            const uint32_t ct = ir.ub + (it - sl * ir.nu);
+            uint32_t ct, sg;
+            ir.at(it, ct, sg);
             const uint32_t e = ct * BLOCK + threadIdx.x;
             Dots<S> acc;
             if (e < PC) {
@@ -613,9 +628,8 @@ __global__ __launch_bounds__(BLOCK) void k_step_march(const Inst *__restrict__ t
     const uint32_t PC = P * C;
     const ItemRange ir = item_range(I, I.nct, I.nseg);
     for (uint32_t it = ir.first; it < ir.count; it += ir.stride) {
-        const uint32_t sl = it / ir.nu;
-        const uint32_t sg = ir.sb + sl;
-        const uint32_t ct = ir.ub + (it - sl * ir.nu);
+        uint32_t ct, sg;
+        ir.at(it, ct, sg);
         const uint32_t e = ct * BLOCK + threadIdx.x;
         Dots<S> acc;
         if (e < PC) {

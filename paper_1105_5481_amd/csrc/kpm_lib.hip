@@ -506,19 +506,17 @@ struct Plan {
     size_t esz;
     size_t part_bytes, dots_bytes, buf_bytes;
     uint32_t nbuf;    // vector buffers (2, or 4 with temporal blocking)
-    uint32_t tbg;     // 2D temporal blocking: chunk groups per site
+    uint32_t tbg, tbw;   // 2D temporal blocking: chunk groups per site, chunks per group
     int32_t tbh;      // temporal blocking: x-tile halo = steps of the deepest pass (1 .. 6)
     uint64_t state;   // bytes the recursion touches per step (vectors + operator)
     uint32_t grid_cap;   // most blocks per launch (0: KPM_LAUNCH_MAX_BLOCKS)
 };
 
-// Halo (= steps of the deepest pass, 2 for pairs) of a temporally blocked solve.
-// Default (-1), measured on 2048^2 lattices: FP32 real hopping four steps (R = 64: 2.5x
-// one step per pass); FP32 spin hopping three (R = 16 / 32: 1.53x / 1.68x, 1-10% faster
-// than four) unless its sites are split into chunk groups (grouped), where four are
-// 2.4-5.6% faster (us per step, three -> four: 2048^2 R = 64 684.1 -> 653.9, 1024^2
-// R = 48 163.4 -> 159.1, R = 64 195.7 -> 191.0, 512^2 R = 64 71.0 -> 67.0); FP64 three
-// (four need over 150 VGPRs and run slower; spin R = 8: 1.27x).
+// Which 2D solves are temporally blocked: those whose row holds a window of
+// TB_WINDOW / (chunks per group) sites and whose columns hold two halos, with the
+// depth and groups below (narrower lattices run one step per launch).  The tiles
+// themselves are chosen by tb_plan.
+constexpr uint32_t TB_WINDOW = 512;
 int tb_depth(int prec, int opk, bool grouped = false)
 {
     if (g_tblock < 0) return (prec == KPM_F64 || (opk == OP_SPIN2 && !grouped)) ? 3 : 4;
@@ -528,25 +526,21 @@ int tb_depth(int prec, int opk, bool grouped = false)
 // of the window of TB_BLOCK / C sites, so that at least half of it is owned.
 int tb_halo(int prec, int opk, uint32_t C, bool grouped = false)
 {
-    return std::min<int>(tb_depth(prec, opk, grouped), (int)(TB_BLOCK / C / 4));
+    return std::min<int>(tb_depth(prec, opk, grouped), (int)(TB_WINDOW / C / 4));
 }
 
-// Chunk groups of a 2D blocked solve whose window would be narrower than 32
-// sites (more than 16 chunks per site): the most groups (the widest window, so
-// the smallest halo share) that keep at least g_tb_group chunks (128 bytes at
-// 8) per site in a group and a window no wider than the row.  0 turns grouping
-// off.  Measured on the 2048^2 lattice, R = 64: FP64 (32 chunks, window 16 ->
-// 64 sites) 1443 -> 1306 ms per solve; FP32 (16 chunks, window 32 -> 64) 478 ->
-// 506 ms, hence no grouping from 32-site windows up.
-int g_tb_group = 8;
+// Chunk groups taken for that: sites of more than 16 chunks are split into as many
+// groups (of at least g_tb_group chunks, 8 by default) as keep the window within the row.
+int g_tb_group = -1;
 uint32_t tb_groups(uint32_t C, uint32_t Lx)
 {
     uint32_t best = 1;
-    if (g_tb_group <= 0 || TB_BLOCK / C >= 32) return best;
+    const uint32_t least = g_tb_group < 0 ? 8 : (uint32_t)g_tb_group;
+    if (least == 0 || TB_WINDOW / C >= 32) return best;
     for (uint32_t G = 2; G <= C; ++G) {
         if (C % G) continue;
         const uint32_t Cg = C / G;
-        if (Cg < (uint32_t)g_tb_group || Lx < TB_BLOCK / Cg) break;
+        if (Cg < least || Lx < TB_WINDOW / Cg) break;
         best = G;
     }
     return best;
@@ -591,6 +585,73 @@ bool tb3_plan(const kpm_ham *h, Plan &p)
     return true;
 }
 
+// Tiles of a 2D blocked solve: steps per pass D (KPM_LAUNCH_TBLOCK, else 3 .. 6),
+// chunks per group Cg (a narrower group widens the window of TB_BLOCK / Cg sites and
+// so cuts the share of its 2 D halo sites) and segments of rows, the combination with
+// the least estimated time per step.  A launch runs in rounds of `slots` resident
+// blocks, so the segments are chosen to fill whole rounds; each block then takes
+// S + 2 D iterations (rows and the fill of the pipeline) of
+//   max(lat + b w D, b 0.75 us if the vectors stream from HBM),
+// b blocks per CU at once.  lat and w (us) fit measured passes of ten lattices
+// (144^2 .. 2048^2, R = 2 .. 64, both precisions and hoppings; 700 tilings) within 5-20%,
+// and the tiling picked is within 8% of the best one measured (FP64 spin: 13%).
+// Per step against 512-thread blocks with whole sites or groups of >= 8 chunks, XCDs
+// split by tiles and 3 or 4 steps per pass: 2048^2 R = 64 FP32 235 -> 166 us, FP64
+// 636 -> 405; 1024^2 spin R = 32 FP32 112 -> 79; 339^2 spin R = 34 18.1 -> 11.5;
+// 1001 x 750 R = 21 FP64 65 -> 30; 512^2 R = 16 7.6 -> 5.4.
+void tb_plan(const kpm_ham *h, Plan &p)
+{
+    const uint32_t Lx = (uint32_t)h->L[0], Ly = (uint32_t)h->L[1], C = p.C;
+    const bool f64 = h->prec == KPM_F64, spin = h->opk == OP_SPIN2;
+    const double lat = spin ? (f64 ? 0.9 : 1.2) : 0.8;
+    const double w = spin ? (f64 ? 0.11 : 0.08) : (f64 ? 0.06 : 0.045);
+    const double mem = 2.0 * (double)h->N * C * 16.0 > (double)CACHE_RESIDENT_BYTES ? 0.75 : 0.0;
+    const int dlo = g_tblock < 0 ? 3 : (g_tblock >= 3 ? g_tblock : 2), dhi = g_tblock < 0 ? TB_DMAX : dlo;
+    // groups of at least this many chunks (0: as few groups as leave a window of 8 sites)
+    const uint32_t gmin = g_tb_group < 0 ? 1 : (g_tb_group == 0 ? TB_BLOCK / 8 : (uint32_t)g_tb_group);
+    double best = 1e300;
+    for (uint32_t Cg = std::min(C, TB_BLOCK / 8); Cg >= 1; --Cg) {
+        if (TB_BLOCK / Cg > Lx) break;                                      // the window must fit the row
+        if (Cg < std::min({gmin, C, TB_BLOCK / 8}) && best < 1e300) break;
+        if (Cg > 8 && C > 8 && g_tb_group < 0 && TB_BLOCK / (Cg - 1) <= Lx) continue;   // far too narrow
+        const uint32_t G = (C + Cg - 1) / Cg, Wn = TB_BLOCK / Cg;
+        for (int D = dlo; D <= dhi || D == dlo; ++D) {
+            const int d = std::max(2, std::min({D, (int)(Wn / 4), (int)(Ly / 2)}));
+            if (d != D && best < 1e300) break;
+            const uint32_t Tn = Wn - 2 * (uint32_t)d, nct = (Lx + Tn - 1) / Tn;
+            const uint64_t units = (uint64_t)nct * G;
+            const uint32_t bpc = (uint32_t)TB_WAVES_PER_EU(f64, spin, d);
+            const uint64_t slots = std::max<uint64_t>(1, 256ull * bpc * (uint64_t)g_march_items / 512);
+            uint32_t seen = 0;
+            for (uint64_t r = 1; r <= 8; ++r) {
+                uint32_t nseg = (uint32_t)std::max<uint64_t>(1, r * slots / units);
+                nseg = std::min<uint32_t>(nseg, std::max<uint32_t>(1, Ly / 4));
+                const uint32_t S = (Ly + nseg - 1) / nseg;
+                nseg = (Ly + S - 1) / S;
+                if (nseg == seen) continue;
+                seen = nseg;
+                const uint64_t items = units * nseg, full = items / slots, rest = items % slots;
+                auto iter = [&](double b) { return std::max(lat + b * w * d, b * mem); };
+                const double t = full * iter((double)bpc) + (rest ? iter(std::ceil((double)rest / 256.0)) : 0.0);
+                const double cost = (2.0 + d + (S + 2 * d) * t) / d;
+                if (cost < 0.999 * best) {
+                    best = cost;
+                    p.tbh = d;
+                    p.tbw = Cg;
+                    p.tbg = G;
+                    p.nct = nct;
+                    p.S = S;
+                    p.nseg = nseg;
+                    p.tiles = (uint32_t)items;
+                }
+            }
+        }
+    }
+    p.P = Lx;
+    p.Lm = Ly;
+    p.xcd = p.tiles >= XCD_MIN_ITEMS ? 3 : 0;
+}
+
 bool make_plan(const kpm_ham *h, int32_t M, int32_t R, int32_t vec, Plan &p, bool allow_tb = true)
 {
     if (!h || M < 1 || R < 1 || vec < 0 || vec > 2) return false;
@@ -619,7 +680,7 @@ bool make_plan(const kpm_ham *h, int32_t M, int32_t R, int32_t vec, Plan &p, boo
     } else if (allow_tb && g_tblock && g_march && (h->opk == OP_REAL2 || h->opk == OP_SPIN2) &&
                tb_halo(h->prec, h->opk, p.C / tb_groups(p.C, (uint32_t)h->L[0]),
                        tb_groups(p.C, (uint32_t)h->L[0]) > 1) >= 2 &&
-               h->L[0] >= TB_BLOCK / (p.C / tb_groups(p.C, (uint32_t)h->L[0])) &&
+               h->L[0] >= TB_WINDOW / (p.C / tb_groups(p.C, (uint32_t)h->L[0])) &&
                h->L[1] >= 2 * tb_halo(h->prec, h->opk, p.C / tb_groups(p.C, (uint32_t)h->L[0]),
                                       tb_groups(p.C, (uint32_t)h->L[0]) > 1)) {
         // several steps per pass: the site's chunks in tbg groups, windows of
@@ -627,27 +688,7 @@ bool make_plan(const kpm_ham *h, int32_t M, int32_t R, int32_t vec, Plan &p, boo
         // idle), x-tiles of the window less 2 tbh halo sites, segments of rows
         p.mode = MODE_TB;
         p.nbuf = 4;
-        p.tbg = tb_groups(p.C, (uint32_t)h->L[0]);
-        const uint32_t Cg = p.C / p.tbg;
-        p.tbh = tb_halo(h->prec, h->opk, Cg, p.tbg > 1);
-        const uint32_t Tn = TB_BLOCK / Cg - 2 * (uint32_t)p.tbh;
-        p.P = (uint32_t)h->L[0];
-        p.Lm = (uint32_t)h->L[1];
-        p.nct = (p.P + Tn - 1) / Tn;
-        // more and shorter segments than the one-step kernels (6x the item target;
-        // measured on the 2048^2 lattice with two-step passes: 4096 items 455 us per
-        // step, 512 items 554 us; with four-step passes (R = 64) 1024 / 1536 / 2048 /
-        // 2560 / 3072 / 4096 items: 524.7 / 491.9 / 471.5 / 469.5 / 466.8 / 476.4 ms
-        // per solve, FP64 three-step passes 1428.7 / 1349.4 / 1303.5 / 1277.6 / 1281.7
-        // / 1302.4 ms)
-        const uint64_t units = (uint64_t)p.nct * p.tbg;
-        const uint64_t target = 6ull * (uint64_t)g_march_items;
-        uint32_t nseg = (uint32_t)((target + units - 1) / units);
-        nseg = std::max<uint32_t>(1, std::min<uint32_t>(nseg, std::max<uint32_t>(1, p.Lm / 8)));
-        p.S = (p.Lm + nseg - 1) / nseg;
-        p.nseg = (p.Lm + p.S - 1) / p.S;
-        p.tiles = (uint32_t)(units * p.nseg);
-        p.xcd = units >= 8 ? 1 : 0;
+        tb_plan(h, p);
     } else if (allow_tb && g_tblock && g_march &&
                (g_tb3 > 0 ? (h->opk == OP_REAL3 || h->opk == OP_SPIN3)
                           : (g_tb3 < 0 && h->opk == OP_REAL3 && h->prec == KPM_F32)) &&
@@ -747,6 +788,7 @@ void fill_inst(const kpm_ham *h, const Plan &p, int32_t M, int32_t R, int32_t ve
     I.pslots = p.P_slots;
     I.tbh = p.tbh;
     I.tbg = p.tbg ? p.tbg : 1;
+    I.tbw = p.tbw ? p.tbw : p.C;
     I.seed = seed;
     I.instance = instance;
     I.norm = (vec == KPM_VEC_UNIT) ? (double)R : (double)h->N * (double)R;
@@ -1330,6 +1372,11 @@ kpm_status kpm_solve_finish(kpm_solve *s, double *mu_dev, void *stream)
 void kpm_solve_free(kpm_solve *s) { delete s; }
 
 int32_t kpm_solve_mode(const kpm_solve *s) { return s ? s->inst.mode : -1; }
+int32_t kpm_solve_depth(const kpm_solve *s)
+{
+    if (!s) return -1;
+    return s->inst.mode == MODE_TB || s->inst.mode == MODE_TB3 ? s->inst.tbh : 1;
+}
 
 kpm_status kpm_moments(kpm_ham *h, int32_t M, int32_t R, int32_t vec, uint64_t seed, uint64_t instance, void *ws,
                        size_t ws_bytes, double *mu_dev, void *stream)
@@ -1450,7 +1497,7 @@ uint32_t place_blocks(std::vector<Inst> &ins, std::vector<uint32_t> &map, bool w
         for (int y = 1; y < 8; ++y)
             if (load[y] < load[x]) x = y;
         if ((double)(load[x] + cost(r)) > share && units(r) >= SPLIT_MIN_UNITS && ins[r].nb >= 8) {
-            ins[r].xcd = 1;   // split over all XCDs by units
+            ins[r].xcd = ins[r].mode == MODE_TB ? 3 : 1;   // split over all XCDs (blocked passes evenly, else by units)
             big.push_back(r);
             for (int y = 0; y < 8; ++y) load[y] += cost(r) / 8;
             continue;
@@ -2249,7 +2296,7 @@ kpm_status kpm_set_launch(int32_t key, int32_t value)
         g_tb3 = value;
         return KPM_OK;
     case KPM_LAUNCH_TB_GROUP:
-        if (value < 0 || value > 512) return KPM_ERR_INVALID_ARG;
+        if (value < -1 || value > 512) return KPM_ERR_INVALID_ARG;
         g_tb_group = value;
         return KPM_OK;
     }

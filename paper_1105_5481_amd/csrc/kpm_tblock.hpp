@@ -2,9 +2,9 @@
 // several steps per pass over the vectors.
 //
 // A work item is an x-tile of T sites times a segment of rows (the march axis
-// y) times one group of the site's chunks (C / G of its C 16-byte chunks, G
-// groups; smaller groups widen the window and so cut the halo's share).  Its
-// block holds a window of W = TB_BLOCK / (C / G) sites (T = W - 2h owned plus
+// y) times one group of the site's chunks (Cg of its C 16-byte chunks; narrower
+// groups widen the window and so cut the halo's share).  Its block holds a
+// window of W = TB_BLOCK / Cg sites (T = W - 2h owned plus
 // h halo sites on each side, h = the depth of the solve's deepest passes), one
 // thread per 16-byte chunk of the group.  A pass of D <= h steps reads r_{n-1} and r_n
 // and writes r_{n+D-1} and r_{n+D} (for D = 1 only r_{n+1}); the halo
@@ -12,15 +12,26 @@
 // pass runs, so the outputs go to the two free buffers of four.  r_{n-1} (read
 // once) and the outputs (written once) use non-temporal accesses when the
 // instance streams.
+//
+// What bounds a pass: at 2048^2 sites, R = 64, FP32, six steps in 995 us move 4.5
+// vector streams (4.8 TB/s, a plain copy reaches 5.0) and issue 55 vector
+// instructions per chunk and step (70% of the vector ALU's rate).
 #pragma once
 
 namespace kpm {
 
-constexpr int TB_BLOCK = 512;
+constexpr uint32_t TB_BLOCK = 256;
+constexpr int TB_DMAX = 6;   // deepest pass
 constexpr int MODE_TB = 3;   // plan mode of solves run by these kernels
-// Passes shallow enough for two blocks per CU in LDS (D <= 4: 16 KiB per level)
-// are held to 128 VGPRs (4 waves per SIMD), so that the second block fits.
-#define TB_WAVES_PER_EU(S, D) ((sizeof(S) == 4 ? (D) <= 4 : (D) <= 3) ? 4 : 1)
+// Blocks per CU (= waves per SIMD) a pass is held to: the VGPR budget is 512 over this
+// (FP32 four steps 118 of 128, six 152 of 168; FP64 five 165 real, 176 spin, six 194),
+// and its D levels of 8 KiB LDS fit as often.  Blocks of 256 threads: of 512, two per
+// CU, with the same tiles measured 1.2-1.5x slower (235 -> 166 us per step on the 2048^2
+// lattice at R = 64), their barriers tie twice the waves together.
+constexpr int TB_WAVES_PER_EU(bool f64, bool spin, int D)
+{
+    return f64 ? (D <= 2 || (D == 3 && !spin) ? 4 : (D <= 4 || (D == 5 && !spin) ? 3 : 2)) : (D <= 4 ? 4 : 3);
+}
 
 // Batched passes: the pass a launch with argument `arg` runs for instance I
 // (arg >= 0: full-depth pass arg of the chunk, D = tbh; arg < 0: the remainder
@@ -62,6 +73,23 @@ __device__ __forceinline__ bool tb_pass_roles(const Inst &I, int32_t arg, int D,
     return true;
 }
 
+// Group gi of a site's C chunks: chunks gi Cg .. (fewer in the last group if Cg
+// does not divide C).  Vectors are stored group-major, a group's chunks of all
+// sites together: chunk c of site i is at 16-byte index base + i n.  Threads
+// beyond the last group's chunks follow its last chunk and own nothing.
+struct TbGroup {
+    uint32_t n, c, base;
+    bool valid;
+    __device__ __forceinline__ TbGroup(uint32_t C, uint32_t Cg, uint32_t gi, uint32_t ct, uint32_t N)
+    {
+        n = min(Cg, C - gi * Cg);
+        valid = ct < n;
+        const uint32_t cl = min(ct, n - 1);
+        c = gi * Cg + cl;
+        base = gi * Cg * N + cl;
+    }
+};
+
 // r_0 (and the partials of <r_0|r_0>, slot 0) into `cur` over the solve's work
 // items (the owned sites of each tile and segment).
 template <typename S, bool WIDE>
@@ -70,33 +98,32 @@ __global__ __launch_bounds__(TB_BLOCK) void k_init_tb(const Inst *__restrict__ t
     typedef typename V16<S>::T T;
     typedef Mem<S, WIDE> G;
     const Inst I = tab[0];
-    const uint32_t C = I.C, Gs = I.tbg, Cg = C / Gs, Lx = I.P, Ly = I.Lm;
+    const uint32_t C = I.C, Gs = I.tbg, Cg = I.tbw, Lx = I.P, Ly = I.Lm;
     const uint32_t h = (uint32_t)I.tbh, Wn = TB_BLOCK / Cg, Tn = Wn - 2 * h;
-    const uint32_t tid = threadIdx.x, s = tid / Cg, cl = tid - s * Cg;
+    const uint32_t tid = threadIdx.x, s = tid / Cg, ct = tid - s * Cg;
     const ItemRange ir = item_range(I, I.nct * Gs, I.nseg);
     for (uint32_t it = ir.first; it < ir.count; it += ir.stride) {
-        const uint32_t sl = it / ir.nu;
-        const uint32_t sg = ir.sb + sl;
-        const uint32_t unit = ir.ub + (it - sl * ir.nu);
-        const uint32_t tx = unit / Gs, c = (unit - tx * Gs) * Cg + cl;
-        const uint32_t x0 = tx * Tn;
+        uint32_t unit, sg;
+        ir.at(it, unit, sg);
+        const TbGroup g(C, Cg, unit % Gs, ct, I.N);
+        const uint32_t x0 = (unit / Gs) * Tn;
         const uint32_t xend = min(x0 + Tn, Lx);
         const uint32_t x = (x0 + Lx - h + s) % Lx;
-        const bool own = s >= h && s < Wn - h && x0 + s - h < xend;
+        const bool own = g.valid && s >= h && s < Wn - h && x0 + s - h < xend;
         const uint32_t y0 = sg * I.S, y1 = min(y0 + I.S, Ly);
         Dots<S> a;
         if (own)
             for (uint32_t y = y0; y < y1; ++y) {
                 const uint32_t i = x + Lx * y;
-                const T v = start_chunk<S>(I, i, c);
-                G::st(cur, i * C + c, v);
+                const T v = start_chunk<S>(I, i, g.c);
+                G::st(cur, g.base + i * g.n, v);
                 a.norm_only(v);
             }
         block_reduce_store<TB_BLOCK>(a, I.partial + (size_t)(sg * I.nct * Gs + unit) * 4);
     }
 }
 
-// Depth-D passes (D = 1 .. 6, D <= the tiles' halo h): one launch advances D
+// Depth-D passes (D = 1 .. TB_DMAX, D <= the tiles' halo h): one launch advances D
 // steps.  It reads r_{n-1} and r_n and writes only r_{n+D-1} and r_{n+D}, all
 // the next pass needs; r_{n+1} .. r_{n+D-2} exist only on chip, where their
 // dots are formed: 4 vector transfers for D steps (a single step writes r_{n+1}
@@ -114,7 +141,7 @@ __global__ __launch_bounds__(TB_BLOCK) void k_init_tb(const Inst *__restrict__ t
 // the four buffer roles from the arguments.  Batched launches take the instance
 // from the block map and run one pass of its current chunk (tb_pass_roles).
 template <typename S, int OPK, bool WIDE, bool NT, int D>
-__global__ __launch_bounds__(TB_BLOCK) __attribute__((amdgpu_waves_per_eu(TB_WAVES_PER_EU(S, D)))) void k_step_tbd(
+__global__ __launch_bounds__(TB_BLOCK) __attribute__((amdgpu_waves_per_eu(TB_WAVES_PER_EU(sizeof(S) == 8, OPK == OP_SPIN2, D)))) void k_step_tbd(
     const Inst *__restrict__ tab, const uint32_t *__restrict__ bmap, int32_t arg, const void *prev, const void *cur,
     void *outa, void *outb)
 {
@@ -128,9 +155,9 @@ __global__ __launch_bounds__(TB_BLOCK) __attribute__((amdgpu_waves_per_eu(TB_WAV
     const Inst I = tab[hb];
     int32_t n = arg;
     if (bmap && !tb_pass_roles(I, arg, D, n, prev, cur, outa, outb)) return;
-    const uint32_t C = I.C, Gs = I.tbg, Cg = C / Gs, Lx = I.P, Ly = I.Lm;
+    const uint32_t C = I.C, Gs = I.tbg, Cg = I.tbw, Lx = I.P, Ly = I.Lm;
     const uint32_t h = (uint32_t)I.tbh, Wn = TB_BLOCK / Cg, Tn = Wn - 2 * h;   // h >= D
-    const uint32_t tid = threadIdx.x, s = tid / Cg, cl = tid - s * Cg;
+    const uint32_t tid = threadIdx.x, s = tid / Cg, ct = tid - s * Cg;
     const bool hd = I.has_diag;
     const S hop = SPIN ? (S)0 : G::lds(I.hop, 0);
     const bool first = (n == 0);
@@ -138,23 +165,23 @@ __global__ __launch_bounds__(TB_BLOCK) __attribute__((amdgpu_waves_per_eu(TB_WAV
     const T two = (T)(S)2;
     const ItemRange ir = item_range(I, I.nct * Gs, I.nseg);
     for (uint32_t it = ir.first; it < ir.count; it += ir.stride) {
-        const uint32_t sl = it / ir.nu;
-        const uint32_t sg = ir.sb + sl;
-        const uint32_t unit = ir.ub + (it - sl * ir.nu);
-        const uint32_t tx = unit / Gs, c = (unit - tx * Gs) * Cg + cl;
-        const uint32_t x0 = tx * Tn;
+        uint32_t unit, sg;
+        ir.at(it, unit, sg);
+        const TbGroup g(C, Cg, unit % Gs, ct, I.N);
+        const uint32_t gb = g.base, gn = g.n;
+        const uint32_t x0 = (unit / Gs) * Tn;
         const uint32_t xend = min(x0 + Tn, Lx);
         const uint32_t x = (x0 + Lx - h + s) % Lx;
         const uint32_t xm = (x == 0) ? Lx - 1 : x - 1;   // -x neighbour (its forward x-bond)
-        const bool own = s >= h && s < Wn - h && x0 + s - h < xend;
+        const bool own = g.valid && s >= h && s < Wn - h && x0 + s - h < xend;
         const uint32_t y0 = sg * I.S, y1 = min(y0 + I.S, Ly), ns = y1 - y0;
         const uint32_t t = sg * I.nct * Gs + unit;
         const uint32_t tl = (s >= 1) ? tid - Cg : tid, tr = (s + 1 < Wn) ? tid + Cg : tid;   // in-row neighbours
         Dots<S> acc[D];
         auto row = [&](int32_t off) { return (y0 + Ly + (uint32_t)off) % Ly; };   // y0 + off, periodic
         // level 0 (r_n): rows y-1, y, y+1 of the current iteration; diagonal d[q] of row y + 1 - q
-        T rnm = G::ld(cur, (x + Lx * row(-D)) * C + c);
-        T rn0 = G::ld(cur, (x + Lx * row(1 - D)) * C + c);
+        T rnm = G::ld(cur, gb + (x + Lx * row(-D)) * gn);
+        T rn0 = G::ld(cur, gb + (x + Lx * row(1 - D)) * gn);
         S d[D + 2];
 #pragma unroll
         for (int q = 0; q < D + 2; ++q) d[q] = (S)0;
@@ -162,31 +189,38 @@ __global__ __launch_bounds__(TB_BLOCK) __attribute__((amdgpu_waves_per_eu(TB_WAV
             d[2] = G::lds(I.diag, x + Lx * row(-D));
             d[1] = G::lds(I.diag, x + Lx * row(1 - D));
         }
-        // rows advance by one per iteration, tracked without divisions: yc = y0 + j + 2 - D (periodic)
+        // rows advance by one per iteration, tracked without divisions: yc = y0 + j + 2 - D (periodic).
+        // Iterations run in pairs, each with load registers of its own (q = 0, 1), refilled two
+        // iterations ahead: one row ahead left each iteration waiting for most of a load's latency.
         uint32_t yc = row(2 - D);
-        T rnp_n = G::ld(cur, (x + Lx * yc) * C + c);
-        S dp_n = hd ? G::lds(I.diag, x + Lx * yc) : (S)0;
-        T pv_n = (!first && s >= 1 && s + 1 < Wn) ? G::template ld_s<NT>(prev, (x + Lx * row(1 - D)) * C + c) : zero;
+        const bool ldp = !first && s >= 1 && s + 1 < Wn;
+        T rnp_q[2], pv_q[2] = {zero, zero};
+        S dp_q[2] = {(S)0, (S)0};
+        const uint32_t iters = ns + 2 * (D - 1);
+        auto next_row = [&](uint32_t r) { return (r + 1 == Ly) ? 0u : r + 1; };
+        auto load_rows = [&](T &rn, T &pv, S &dp, uint32_t yn, uint32_t yp) {   // r_n and diagonal at yn, r_{n-1} at yp
+            rn = G::ld(cur, gb + (x + Lx * yn) * gn);
+            if (hd) dp = G::lds(I.diag, x + Lx * yn);
+            if (ldp) pv = G::template ld_s<NT>(prev, gb + (x + Lx * yp) * gn);
+        };
+        load_rows(rnp_q[0], pv_q[0], dp_q[0], yc, row(1 - D));
+        load_rows(rnp_q[1], pv_q[1], dp_q[1], next_row(yc), yc);   // iters >= 2 or unused
         T m2[D], m1[D];   // level k at rows (its current row) - 2 and - 1, k = 1 .. D-1
 #pragma unroll
         for (int k = 0; k < D; ++k) {
             m2[k] = zero;
             m1[k] = zero;
         }
-        const uint32_t iters = ns + 2 * (D - 1);
-        for (uint32_t j = 0; j < iters; ++j) {
+        auto iteration = [&](uint32_t j, const uint32_t b, T &rnp_n, T &pv_n, S &dp_n) {
+            const uint32_t bp = b ^ 1u;
             const T rnp = rnp_n;
             const T pv = pv_n;
             d[0] = dp_n;
-            if (j + 1 < iters) {   // rows the next iteration needs
-                const uint32_t yn = (yc + 1 == Ly) ? 0 : yc + 1;
-                rnp_n = G::ld(cur, (x + Lx * yn) * C + c);
-                dp_n = hd ? G::lds(I.diag, x + Lx * yn) : (S)0;
-                if (!first && s >= 1 && s + 1 < Wn)
-                    pv_n = G::template ld_s<NT>(prev, (x + Lx * yc) * C + c);
-            }
-            const uint32_t b = j & 1u, bp = b ^ 1u;
             lv_s[0][b][tid] = rn0;
+            if (j + 2 < iters) {   // rows of the iteration after the next
+                const uint32_t yp = next_row(yc);
+                load_rows(rnp_n, pv_n, dp_n, next_row(yp), yp);
+            }
             __syncthreads();
             T cur_k[D + 1];
             cur_k[0] = rnp;
@@ -237,8 +271,8 @@ __global__ __launch_bounds__(TB_BLOCK) __attribute__((amdgpu_waves_per_eu(TB_WAV
                 // stores and dots on the owned rows [y0, y1): level k is at row offset j - D - k + 2
                 const int32_t ro = (int32_t)j - D - k + 2;
                 if (own && ro >= 0 && ro < (int32_t)ns) {
-                    if (k == D - 1) G::template st_s<NT>(outa, (x + Lx * (y0 + ro)) * C + c, v);
-                    if (k == D) G::template st_s<NT>(outb, (x + Lx * (y0 + ro)) * C + c, v);
+                    if (k == D - 1) G::template st_s<NT>(outa, gb + (x + Lx * (y0 + ro)) * gn, v);
+                    if (k == D) G::template st_s<NT>(outb, gb + (x + Lx * (y0 + ro)) * gn, v);
                     acc[k - 1].add(v, k == 1 ? rn0 : m1[k - 1]);
                 }
                 if (k < D) lv_s[k][b][tid] = v;
@@ -253,11 +287,15 @@ __global__ __launch_bounds__(TB_BLOCK) __attribute__((amdgpu_waves_per_eu(TB_WAV
 #pragma unroll
             for (int q = D + 1; q > 0; --q) d[q] = d[q - 1];
             yc = (yc + 1 == Ly) ? 0 : yc + 1;
+        };
+        for (uint32_t j = 0; j < iters; j += 2) {
+            iteration(j, 0u, rnp_q[0], pv_q[0], dp_q[0]);
+            if (j + 1 < iters) iteration(j + 1, 1u, rnp_q[1], pv_q[1], dp_q[1]);
         }
 #pragma unroll
         for (int k = 0; k < D; ++k)
             block_reduce_store<TB_BLOCK>(acc[k], I.partial + (size_t)((n + 1 + k) % I.pslots) * I.tiles * 4 +
-                                                          (size_t)t * 4);
+                                                     (size_t)t * 4);
     }
 }
 

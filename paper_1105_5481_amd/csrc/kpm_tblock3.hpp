@@ -103,9 +103,8 @@ __global__ __launch_bounds__(TB3_BLOCK) void k_init_tb3(const Inst *__restrict__
     const uint32_t N = I.N, P = I.Lx * I.Ly;
     const ItemRange ir = item_range(I, I.C * I.nct, I.nseg);
     for (uint32_t it = ir.first; it < ir.count; it += ir.stride) {
-        const uint32_t sl = it / ir.nu;
-        const uint32_t sg = ir.sb + sl;
-        const uint32_t unit = ir.ub + (it - sl * ir.nu);
+        uint32_t unit, sg;
+        ir.at(it, unit, sg);
         const Tb3Item t = tb3_item(I, unit, sg);
         Dots<S> a;
 #pragma unroll
@@ -151,9 +150,8 @@ __global__ __launch_bounds__(TB3_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) 
     const T zero = (T)(S)0;
     const ItemRange ir = item_range(I, I.C * I.nct, I.nseg);
     for (uint32_t it = ir.first; it < ir.count; it += ir.stride) {
-        const uint32_t sl = it / ir.nu;
-        const uint32_t sg = ir.sb + sl;
-        const uint32_t unit = ir.ub + (it - sl * ir.nu);
+        uint32_t unit, sg;
+        ir.at(it, unit, sg);
         const Tb3Item t = tb3_item(I, unit, sg);
         const uint32_t cb = t.c * N;   // this chunk's plane of the vectors
         Tb3Elem e[TB3_EPT];

@@ -39,8 +39,8 @@ CANDIDATES: Dict[str, List[int]] = {
     "max_blocks": [512, 1024, 2048, 4096, 8192],
     "elems_per_thread": [1, 2, 4],
     "wave_mib": [0, 128, 192, 224, 256],
-    "tblock": [-1, 0, 1, 3, 4, 5],
-    "tb_group": [0, 4, 8, 16],
+    "tblock": [-1, 0, 1, 3, 4, 5, 6],
+    "tb_group": [-1, 2, 4, 8],
     "tb3": [-1, 0, 1],
 }
 LATTICE_KEYS = ["march_items", "xcd_split", "alternate", "streaming", "max_blocks", "tblock", "tb_group", "tb3"]
