@@ -367,8 +367,8 @@ kpm_status kpm_start_vectors(int32_t vec, int32_t complex_layout, uint64_t seed,
  *                                (KPM_LAUNCH_STREAMING) take 4x this target on a quarter of
  *                                KPM_LAUNCH_MAX_BLOCKS blocks
  *   KPM_LAUNCH_XCD_SPLIT         how an instance's work items are split over the 8 XCDs:
- *                                0 automatic, 1 by column tiles, 2 by march segments, 3 none
- *   KPM_LAUNCH_ALTERNATE         1: odd march segments walk downwards
+ *                                0 automatic (march: evenly, in plane order), 1 by column tiles, 2 by march segments, 3 none
+ *   KPM_LAUNCH_ALTERNATE         1: odd march segments of 4 planes or more walk downwards
  *   KPM_LAUNCH_SMALL             1: a solve whose two vector blocks fit in the LDS of one
  *                                compute unit runs entirely in one workgroup (one launch)
  *   KPM_LAUNCH_STREAMING         march kernels: 1 = r_{n-1} read / r_{n+1} written with

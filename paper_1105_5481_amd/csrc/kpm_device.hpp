@@ -121,6 +121,14 @@ __device__ __forceinline__ dd dd_add(dd x, dd y)
     s.lo += t.lo;
     return dd_fast_two_sum(s.hi, s.lo);
 }
+// x + y for sums of many terms: the rounded sum and, unnormalised, all errors so far
+// (summed in FP64, so the result is off by 2^-106 of the largest term).  8 operations;
+// dd_add takes 20.
+__device__ __forceinline__ dd dd_sum(dd x, dd y)
+{
+    const dd s = dd_two_sum(x.hi, y.hi);
+    return dd{s.hi, s.lo + (x.lo + y.lo)};
+}
 // (s, c) += x*y exactly up to the error term c, which is summed in FP64.
 __device__ __forceinline__ void dot2_acc(double &s, double &c, double x, double y)
 {

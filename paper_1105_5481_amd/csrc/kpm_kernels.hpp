@@ -24,6 +24,11 @@
 // Flat kernels (CSR, and lattices on request).  Work is cut into tiles of
 // 256*TPT consecutive chunks; every neighbour is loaded through the caches.
 //
+// A solve alone cuts the march axis into as many segments as keep the chip busy, down
+// to one plane each; where a launch has blocks enough, a block walks a run of
+// consecutive segments, which reads the two halo planes once per run.  The segments,
+// and with them the partial sums, are the same either way.
+//
 // Reductions.  Each work item (march: column tile x segment; flat: tile) of a
 // step leaves one partial (FP64 sums of its dot products) in a ring of
 // per-step slots; a separate kernel sums the partials of a step over the items
@@ -51,7 +56,7 @@ struct Inst {
     int32_t opk;
     int32_t has_diag;
     int32_t mode;
-    int32_t xcd;       // items split per XCD (0 none, 1 by units, 2 by segments, 3 evenly)
+    int32_t xcd;       // items split per XCD (0 none, 1 by units, 2 by segments, 3 evenly, 4 explicit)
     int32_t alt;       // march: odd segments walk downwards
     int32_t nt;        // march: r_{n-1}/r_{n+1} accessed with non-temporal hints
     uint32_t Lx, Ly, Lz, N;
@@ -63,8 +68,10 @@ struct Inst {
     uint32_t nb;       // blocks given to this instance (multiple of 8)
     uint32_t block0;   // first block of this instance in the grid
     uint32_t bstride;  // its blocks are block0, block0 + bstride, ... (1, or 8 to keep them on one XCD)
+    uint32_t q0, q1;   // xcd == 4: its items
     int32_t tpt;       // flat: chunks per thread per tile
     uint32_t P, Lm, S, nct, nseg;  // march: plane size, march extent, segment, column tiles, segments
+    uint32_t run;      // march: consecutive segments a block walks without reloading its window
     int32_t cplx;      // data stored as interleaved complex
     int32_t M, K, R, vec;
     int32_t step0;     // recursion step n = step0 + (launch offset k)
@@ -183,6 +190,17 @@ template <> struct Arith<float> {
 template <typename S> struct Dots;
 template <> struct Dots<double> {
     double s0 = DOT_BIAS, c0 = 0.0, s1 = DOT_BIAS, c1 = 0.0;
+    static constexpr int NV = 4;   // values save() keeps
+    __device__ __forceinline__ Dots() {}
+    __device__ __forceinline__ explicit Dots(const double (&h)[NV][BLOCK])
+        : s0(h[0][threadIdx.x]), c0(h[1][threadIdx.x]), s1(h[2][threadIdx.x]), c1(h[3][threadIdx.x]) {}
+    __device__ __forceinline__ void save(double (&h)[NV][BLOCK]) const
+    {
+        h[0][threadIdx.x] = s0;
+        h[1][threadIdx.x] = c0;
+        h[2][threadIdx.x] = s1;
+        h[3][threadIdx.x] = c1;
+    }
     __device__ __forceinline__ void add(V16<double>::T o, V16<double>::T v)
     {
 #pragma unroll
@@ -204,6 +222,14 @@ template <> struct Dots<double> {
 };
 template <> struct Dots<float> {
     double s0 = 0.0, s1 = 0.0;
+    static constexpr int NV = 2;
+    __device__ __forceinline__ Dots() {}
+    __device__ __forceinline__ explicit Dots(const double (&h)[NV][BLOCK]) : s0(h[0][threadIdx.x]), s1(h[1][threadIdx.x]) {}
+    __device__ __forceinline__ void save(double (&h)[NV][BLOCK]) const
+    {
+        h[0][threadIdx.x] = s0;
+        h[1][threadIdx.x] = s1;
+    }
     __device__ __forceinline__ void add(V16<float>::T o, V16<float>::T v)
     {
 #pragma unroll
@@ -253,25 +279,25 @@ struct DotsWide {
 // Sums of x0 + x1 and x2 + x3 over the wavefront, in (a, b): the lower 32 lanes
 // receive the first, the upper 32 the second (as a double-double when DD, else in a
 // alone).  The first exchange gives each half of the wave one of the two sums, so a
-// reduction is six additions, and no exchange goes through the LDS: with ds_bpermute
-// shuffles of both sums it was twelve additions and 48 shuffles of 24 cycles, most of a
-// step of the single-workgroup solves.
+// reduction is six additions of 8 operations, and no exchange goes through the LDS: with
+// ds_bpermute shuffles of both sums it was twelve of 20 and 48 shuffles of 24 cycles, most
+// of a step of the single-workgroup solves.
 template <bool DD>
 __device__ __forceinline__ void wave_reduce(double x0, double x1, double x2, double x3, double &a, double &b)
 {
     if (DD) {
-        dd p = dd_two_sum(x0, x1), q = dd_two_sum(x2, x3);
+        dd p{x0, x1}, q{x2, x3};
         swap_halves(p.hi, q.hi);
         swap_halves(p.lo, q.lo);
-        p = dd_add(p, q);
+        p = dd_sum(p, q);
         q = p;
         swap_rows(p.hi, q.hi);
         swap_rows(p.lo, q.lo);
-        p = dd_add(p, q);
-        p = dd_add(p, dd{row_ror<8>(p.hi), row_ror<8>(p.lo)});
-        p = dd_add(p, dd{row_ror<4>(p.hi), row_ror<4>(p.lo)});
-        p = dd_add(p, dd{row_ror<2>(p.hi), row_ror<2>(p.lo)});
-        p = dd_add(p, dd{row_ror<1>(p.hi), row_ror<1>(p.lo)});
+        p = dd_sum(p, q);
+        p = dd_sum(p, dd{row_ror<8>(p.hi), row_ror<8>(p.lo)});
+        p = dd_sum(p, dd{row_ror<4>(p.hi), row_ror<4>(p.lo)});
+        p = dd_sum(p, dd{row_ror<2>(p.hi), row_ror<2>(p.lo)});
+        p = dd_sum(p, dd{row_ror<1>(p.hi), row_ror<1>(p.lo)});
         a = p.hi;
         b = p.lo;
     } else {
@@ -305,6 +331,50 @@ template <typename A> __device__ __forceinline__ void wave_reduce_store(const A 
     wave_reduce_store<A::DD>(d.x0(), d.x1(), d.x2(), d.x3(), dst);
 }
 
+// The wavefront's sums of two accumulators at once, each in the order of
+// wave_reduce_store: after the first exchange the even rows of 16 lanes go on with the
+// first, the odd rows with the second (7 additions instead of 12).
+template <typename A> __device__ __forceinline__ void wave_reduce_store(const A &d, const A &f, double *dst, double *fdst)
+{
+    double a = d.x0(), b = d.x2(), u = f.x0(), v = f.x2();
+    if (A::DD) {
+        dd p{a, d.x1()}, q{b, d.x3()}, r{u, f.x1()}, s{v, f.x3()};
+        swap_halves(p.hi, q.hi);
+        swap_halves(p.lo, q.lo);
+        swap_halves(r.hi, s.hi);
+        swap_halves(r.lo, s.lo);
+        p = dd_sum(p, q);
+        r = dd_sum(r, s);
+        swap_rows(p.hi, r.hi);
+        swap_rows(p.lo, r.lo);
+        p = dd_sum(p, r);
+        p = dd_sum(p, dd{row_ror<8>(p.hi), row_ror<8>(p.lo)});
+        p = dd_sum(p, dd{row_ror<4>(p.hi), row_ror<4>(p.lo)});
+        p = dd_sum(p, dd{row_ror<2>(p.hi), row_ror<2>(p.lo)});
+        p = dd_sum(p, dd{row_ror<1>(p.hi), row_ror<1>(p.lo)});
+        a = p.hi;
+        b = p.lo;
+    } else {
+        swap_halves(a, b);
+        swap_halves(u, v);
+        a += b;
+        u += v;
+        swap_rows(a, u);
+        a += u;
+        a += row_ror<8>(a);
+        a += row_ror<4>(a);
+        a += row_ror<2>(a);
+        a += row_ror<1>(a);
+        b = 0.0;
+    }
+    const int lane = threadIdx.x & 63;
+    if ((lane & 15) == 0) {
+        double *o = (lane & 16) ? fdst : dst;
+        o[(lane & 32) >> 4] = a;
+        o[((lane & 32) >> 4) + 1] = b;
+    }
+}
+
 // Sum (x0 + x1, x2 + x3) over the block in a fixed order, stored as four doubles
 // (hi, lo, hi, lo) at dst; thread 0 adds the waves' first sums, thread 1 the second.
 template <bool DD, int NT = BLOCK>
@@ -318,7 +388,7 @@ __device__ __forceinline__ void block_reduce_store(double x0, double x1, double 
         dd a{red[0][o], red[0][o + 1]};
 #pragma unroll
         for (int k = 1; k < NT / 64; ++k) {
-            if (DD) a = dd_add(a, dd{red[k][o], red[k][o + 1]});
+            if (DD) a = dd_sum(a, dd{red[k][o], red[k][o + 1]});
             else a.hi += red[k][o];
         }
         dst[o] = a.hi;
@@ -329,6 +399,25 @@ __device__ __forceinline__ void block_reduce_store(double x0, double x1, double 
 template <int NT = BLOCK, typename A> __device__ __forceinline__ void block_reduce_store(const A &d, double *dst)
 {
     block_reduce_store<A::DD, NT>(d.x0(), d.x1(), d.x2(), d.x3(), dst);
+}
+
+// The block's sums of `n` segments from their waves' (red[k][wave]), added in the order of
+// block_reduce_store: segment k's four doubles go to dst + k * pitch.
+constexpr int RUN_MAX = 4;   // segments per run
+template <bool DD>
+__device__ __forceinline__ void reduce_run(const double (&red)[RUN_MAX][BLOCK / 64][4], uint32_t n, double *dst,
+                                           size_t pitch)
+{
+    if (threadIdx.x >= 2 * n) return;
+    const uint32_t k = threadIdx.x >> 1, o = (threadIdx.x & 1u) * 2;
+    dd a{red[k][0][o], red[k][0][o + 1]};
+#pragma unroll
+    for (int w = 1; w < BLOCK / 64; ++w) {
+        if (DD) a = dd_sum(a, dd{red[k][w][o], red[k][w][o + 1]});
+        else a.hi += red[k][w][o];
+    }
+    dst[k * pitch + o] = a.hi;
+    dst[k * pitch + o + 1] = a.lo;
 }
 
 // ---------------------------------------------------------------------------
@@ -343,6 +432,7 @@ template <int NT = BLOCK, typename A> __device__ __forceinline__ void block_redu
 //   xcd == 1: XCD x owns units [x*units/8, (x+1)*units/8) of every segment;
 //   xcd == 3: XCD x owns the x-th eighth of all items in the order of seg, then unit
 //             (equal to one item, whatever the units and segments);
+//   xcd == 4: this table entry covers items [q0, q1) of its instance, in that order;
 //   xcd == 0: no split.
 struct ItemRange {
     uint32_t first, stride, count, ub, nu, sb, base;
@@ -363,6 +453,13 @@ __device__ __forceinline__ ItemRange item_range(const Inst &I, uint32_t units, u
     r.sb = 0;
     r.base = 0;
     uint32_t ns = segs;
+    if (I.xcd == 4) {
+        r.first = bl;
+        r.stride = I.nb;
+        r.base = I.q0;
+        r.count = I.q1 - I.q0;
+        return r;
+    }
     if (I.xcd) {
         const uint32_t x8 = bl & 7u;
         r.first = bl >> 3;
@@ -512,24 +609,26 @@ __global__ __launch_bounds__(BLOCK) void k_init(const Inst *__restrict__ tab, co
     if (I.step0 != 0) return;
     double *part = I.partial;   // slot 0
     if (I.mode == MODE_MARCH) {
-        const ItemRange ir = item_range(I, I.nct, I.nseg);
+        const ItemRange ir = item_range(I, I.nct, (I.nseg + I.run - 1) / I.run);
         const uint32_t PC = I.P * I.C;
         for (uint32_t it = ir.first; it < ir.count; it += ir.stride) {
-            uint32_t ct, sg;
-            ir.at(it, ct, sg);
+            uint32_t ct, rn;
+            ir.at(it, ct, rn);
             const uint32_t e = ct * BLOCK + threadIdx.x;
-            Dots<S> acc;
-            if (e < PC) {
-                const uint32_t p = fdiv(e, I.fC), c = e - p * I.C;
-                const uint32_t m0 = sg * I.S, m1 = min(m0 + I.S, I.Lm);
-                for (uint32_t m = m0; m < m1; ++m) {
-                    const uint32_t i = p + I.P * m;
-                    const auto v = start_chunk<S>(I, i, c);
-                    G::st(I.buf0, i * I.C + c, v);
-                    acc.norm_only(v);
+            for (uint32_t sg = rn * I.run; sg < min((rn + 1) * I.run, I.nseg); ++sg) {
+                Dots<S> acc;
+                if (e < PC) {
+                    const uint32_t p = fdiv(e, I.fC), c = e - p * I.C;
+                    const uint32_t m0 = sg * I.S, m1 = min(m0 + I.S, I.Lm);
+                    for (uint32_t m = m0; m < m1; ++m) {
+                        const uint32_t i = p + I.P * m;
+                        const auto v = start_chunk<S>(I, i, c);
+                        G::st(I.buf0, i * I.C + c, v);
+                        acc.norm_only(v);
+                    }
                 }
+                block_reduce_store(acc, part + (size_t)(sg * I.nct + ct) * 4);
             }
-            block_reduce_store(acc, part + (size_t)(sg * I.nct + ct) * 4);
         }
     } else {
         const ItemRange ir = item_range(I, I.tiles, 1);
@@ -626,91 +725,105 @@ __global__ __launch_bounds__(BLOCK) void k_step_march(const Inst *__restrict__ t
     double *part = I.partial + (size_t)((n + 1) % I.pslots) * I.tiles * 4;
     const uint32_t C = I.C, P = I.P, Lx = I.Lx, Ly = I.Ly, Lm = I.Lm;
     const uint32_t PC = P * C;
-    const ItemRange ir = item_range(I, I.nct, I.nseg);
+    __shared__ double red[RUN_MAX][BLOCK / 64][4];   // wave sums of the run's segments
+    // a thread's sums of the even segment of a pair, reduced with the odd one's (in the LDS:
+    // four more VGPRs would cost the FP32 3D spin kernel one of its 7 waves per SIMD)
+    __shared__ double held[Dots<S>::NV][BLOCK];
+    const ItemRange ir = item_range(I, I.nct, (I.nseg + I.run - 1) / I.run);
     for (uint32_t it = ir.first; it < ir.count; it += ir.stride) {
-        uint32_t ct, sg;
-        ir.at(it, ct, sg);
+        uint32_t ct, rn;
+        ir.at(it, ct, rn);
         const uint32_t e = ct * BLOCK + threadIdx.x;
-        Dots<S> acc;
-        if (e < PC) {
-            const uint32_t p = fdiv(e, I.fC), c = e - p * C;
-            uint32_t x = p, y = 0;
-            if constexpr (D3) {
-                y = fdiv(p, I.fLx);
-                x = p - y * Lx;
-            }
-            const uint32_t pxm = (x == 0) ? p + (Lx - 1) : p - 1;
-            const uint32_t pxp = (x == Lx - 1) ? p - (Lx - 1) : p + 1;
-            uint32_t pym = 0, pyp = 0;
-            if constexpr (D3) {
-                pym = (y == 0) ? p + (Ly - 1) * Lx : p - Lx;
-                pyp = (y == Ly - 1) ? p - (Ly - 1) * Lx : p + Lx;
-            }
-            const uint32_t m0 = sg * I.S, m1 = min(m0 + I.S, Lm);
-            // Odd segments march downwards, so that two adjacent segments reach
-            // their common boundary planes at about the same time and the second
-            // read of a halo plane hits in L2.
-            const bool down = I.alt && (sg & 1u) != 0;
-            const uint32_t mfirst = down ? m1 - 1 : m0;
-            const uint32_t mbefore = down ? ((m1 == Lm) ? 0 : m1) : ((m0 == 0) ? Lm - 1 : m0 - 1);
-            // window: vb = plane behind (in march order), v0 = current plane
-            T vb = G::ld(cur, (p + P * mbefore) * C + c);
-            T v0 = G::ld(cur, (p + P * mfirst) * C + c);
-            // march-axis bond linking plane mbefore and mfirst (H~_{(m-1), m} stored at plane m-1)
-            S2 bb = {0, 0};
-            if (SPIN) bb = G::ldc(I.bond, (p + P * (down ? mfirst : mbefore)) * DIM + (DIM - 1));
-            for (uint32_t s_ = 0; s_ < m1 - m0; ++s_) {
-                const uint32_t m = down ? mfirst - s_ : mfirst + s_;
-                const uint32_t ma = down ? ((m == 0) ? Lm - 1 : m - 1) : ((m + 1 == Lm) ? 0 : m + 1);  // plane ahead
-                const uint32_t i = p + P * m;
-                const uint32_t ch = i * C + c;
-                const T va = G::ld(cur, (p + P * ma) * C + c);
-                T nb[NS];
-                nb[0] = G::ld(cur, (pxm + P * m) * C + c);
-                nb[1] = G::ld(cur, (pxp + P * m) * C + c);
-                if constexpr (D3) {
-                    nb[2] = G::ld(cur, (pym + P * m) * C + c);
-                    nb[3] = G::ld(cur, (pyp + P * m) * C + c);
-                }
-                // slots -march, +march in the fixed order
-                nb[NS - 2] = down ? va : vb;
-                nb[NS - 1] = down ? vb : va;
-                T prev;
-                if (!first) prev = G::template ld_s<NT>(nxt, ch);
-                const S d = hd ? G::lds(I.diag, i) : (S)0;
-                T out;
-                if (!SPIN) {
-                    out = apply_real<S, NS>(hd, d, hop, v0, nb);
-                } else {
-                    S hr[NS], hi[NS];
-                    const S2 bxm = G::ldc(I.bond, (pxm + P * m) * DIM + 0);
-                    const S2 bxp = G::ldc(I.bond, i * DIM + 0);
-                    hr[0] = bxm[0]; hi[0] = -bxm[1];
-                    hr[1] = bxp[0]; hi[1] = bxp[1];
-                    if constexpr (D3) {
-                        const S2 bym = G::ldc(I.bond, (pym + P * m) * DIM + 1);
-                        const S2 byp = G::ldc(I.bond, i * DIM + 1);
-                        hr[2] = bym[0]; hi[2] = -bym[1];
-                        hr[3] = byp[0]; hi[3] = byp[1];
-                    }
-                    // the other march-axis bond: H~_{m, m+1} (up) lives at plane m,
-                    // H~_{m-1, m} (down) at plane m-1 = the plane ahead
-                    const S2 ba = G::ldc(I.bond, (p + P * (down ? ma : m)) * DIM + (DIM - 1));
-                    const S2 bminus = down ? ba : bb;   // H~_{m-1,m}: conjugated for slot -march
-                    const S2 bplus = down ? bb : ba;    // H~_{m,m+1}
-                    hr[NS - 2] = bminus[0]; hi[NS - 2] = -bminus[1];
-                    hr[NS - 1] = bplus[0]; hi[NS - 1] = bplus[1];
-                    out = apply_cplx<S, NS>(hd, d, v0, nb, hr, hi);
-                    bb = ba;
-                }
-                if (!first) out = (S)2 * out - prev;
-                G::template st_s<NT>(nxt, ch, out);
-                acc.add(out, v0);
-                vb = v0;
-                v0 = va;
-            }
+        const bool active = e < PC;
+        const uint32_t p = active ? fdiv(e, I.fC) : 0u, c = active ? e - p * C : 0u;
+        uint32_t x = p, y = 0;
+        if constexpr (D3) {
+            y = fdiv(p, I.fLx);
+            x = p - y * Lx;
         }
-        block_reduce_store(acc, part + (size_t)(sg * I.nct + ct) * 4);
+        const uint32_t pxm = (x == 0) ? p + (Lx - 1) : p - 1;
+        const uint32_t pxp = (x == Lx - 1) ? p - (Lx - 1) : p + 1;
+        uint32_t pym = 0, pyp = 0;
+        if constexpr (D3) {
+            pym = (y == 0) ? p + (Ly - 1) * Lx : p - Lx;
+            pyp = (y == Ly - 1) ? p - (Ly - 1) * Lx : p + Lx;
+        }
+        const uint32_t s0 = rn * I.run, s1 = min(s0 + I.run, I.nseg);
+        const uint32_t r0 = s0 * I.S, r1 = min(s1 * I.S, Lm);   // planes of the run
+        // Odd segments march downwards, so that two adjacent segments reach
+        // their common boundary planes at about the same time and the second
+        // read of a halo plane hits in L2.  (Runs of several segments march upwards.)
+        const bool down = I.alt && (s0 & 1u) != 0;
+        const uint32_t mfirst = down ? r1 - 1 : r0;
+        const uint32_t mbefore = down ? ((r1 == Lm) ? 0 : r1) : ((r0 == 0) ? Lm - 1 : r0 - 1);
+        // window: vb = plane behind (in march order), v0 = current plane
+        T vb = G::ld(cur, (p + P * mbefore) * C + c);
+        T v0 = G::ld(cur, (p + P * mfirst) * C + c);
+        // march-axis bond linking plane mbefore and mfirst (H~_{(m-1), m} stored at plane m-1)
+        S2 bb = {0, 0};
+        if (SPIN) bb = G::ldc(I.bond, (p + P * (down ? mfirst : mbefore)) * DIM + (DIM - 1));
+        for (uint32_t sg = s0; sg < s1; ++sg) {
+            Dots<S> acc;
+            const uint32_t m0 = sg * I.S, m1 = min(m0 + I.S, Lm);
+            if (active)
+                for (uint32_t s_ = 0; s_ < m1 - m0; ++s_) {
+                    const uint32_t m = down ? m1 - 1 - s_ : m0 + s_;
+                    const uint32_t ma = down ? ((m == 0) ? Lm - 1 : m - 1) : ((m + 1 == Lm) ? 0 : m + 1);  // plane ahead
+                    const uint32_t i = p + P * m;
+                    const uint32_t ch = i * C + c;
+                    const T va = G::ld(cur, (p + P * ma) * C + c);
+                    T nb[NS];
+                    nb[0] = G::ld(cur, (pxm + P * m) * C + c);
+                    nb[1] = G::ld(cur, (pxp + P * m) * C + c);
+                    if constexpr (D3) {
+                        nb[2] = G::ld(cur, (pym + P * m) * C + c);
+                        nb[3] = G::ld(cur, (pyp + P * m) * C + c);
+                    }
+                    // slots -march, +march in the fixed order
+                    nb[NS - 2] = down ? va : vb;
+                    nb[NS - 1] = down ? vb : va;
+                    T prev;
+                    if (!first) prev = G::template ld_s<NT>(nxt, ch);
+                    const S d = hd ? G::lds(I.diag, i) : (S)0;
+                    T out;
+                    if (!SPIN) {
+                        out = apply_real<S, NS>(hd, d, hop, v0, nb);
+                    } else {
+                        S hr[NS], hi[NS];
+                        const S2 bxm = G::ldc(I.bond, (pxm + P * m) * DIM + 0);
+                        const S2 bxp = G::ldc(I.bond, i * DIM + 0);
+                        hr[0] = bxm[0]; hi[0] = -bxm[1];
+                        hr[1] = bxp[0]; hi[1] = bxp[1];
+                        if constexpr (D3) {
+                            const S2 bym = G::ldc(I.bond, (pym + P * m) * DIM + 1);
+                            const S2 byp = G::ldc(I.bond, i * DIM + 1);
+                            hr[2] = bym[0]; hi[2] = -bym[1];
+                            hr[3] = byp[0]; hi[3] = byp[1];
+                        }
+                        // the other march-axis bond: H~_{m, m+1} (up) lives at plane m,
+                        // H~_{m-1, m} (down) at plane m-1 = the plane ahead
+                        const S2 ba = G::ldc(I.bond, (p + P * (down ? ma : m)) * DIM + (DIM - 1));
+                        const S2 bminus = down ? ba : bb;   // H~_{m-1,m}: conjugated for slot -march
+                        const S2 bplus = down ? bb : ba;    // H~_{m,m+1}
+                        hr[NS - 2] = bminus[0]; hi[NS - 2] = -bminus[1];
+                        hr[NS - 1] = bplus[0]; hi[NS - 1] = bplus[1];
+                        out = apply_cplx<S, NS>(hd, d, v0, nb, hr, hi);
+                        bb = ba;
+                    }
+                    if (!first) out = (S)2 * out - prev;
+                    G::template st_s<NT>(nxt, ch, out);
+                    acc.add(out, v0);
+                    vb = v0;
+                    v0 = va;
+                }
+            const uint32_t k = sg - s0, w = threadIdx.x >> 6;
+            if (k & 1u) wave_reduce_store(Dots<S>(held), acc, red[k - 1][w], red[k][w]);
+            else if (sg + 1 < s1) acc.save(held);
+            else wave_reduce_store(acc, red[k][w]);
+        }
+        __syncthreads();
+        reduce_run<Dots<S>::DD>(red, s1 - s0, part + (size_t)(s0 * I.nct + ct) * 4, (size_t)I.nct * 4);
+        __syncthreads();
     }
 }
 
@@ -980,8 +1093,8 @@ __global__ __launch_bounds__(BLOCK) void k_reduce(const Inst *__restrict__ tab, 
     const double *p = I->partial + (size_t)(idx % I->pslots) * I->tiles * 4;
     dd a{0.0, 0.0}, b{0.0, 0.0};
     for (uint32_t t = threadIdx.x; t < I->tiles; t += BLOCK) {
-        a = dd_add(a, dd{p[(size_t)t * 4 + 0], p[(size_t)t * 4 + 1]});
-        b = dd_add(b, dd{p[(size_t)t * 4 + 2], p[(size_t)t * 4 + 3]});
+        a = dd_sum(a, dd{p[(size_t)t * 4 + 0], p[(size_t)t * 4 + 1]});
+        b = dd_sum(b, dd{p[(size_t)t * 4 + 2], p[(size_t)t * 4 + 3]});
     }
     block_reduce_store<true>(a.hi, a.lo, b.hi, b.lo, I->dots + (size_t)idx * 4);
 }
@@ -996,8 +1109,8 @@ __global__ __launch_bounds__(BLOCK) void k_reduce_ranges(const Inst *__restrict_
     const double *p = I->partial + (size_t)(idx % I->pslots) * I->tiles * 4;
     dd a{0.0, 0.0}, b{0.0, 0.0};
     for (uint32_t t = threadIdx.x; t < I->tiles; t += BLOCK) {
-        a = dd_add(a, dd{p[(size_t)t * 4 + 0], p[(size_t)t * 4 + 1]});
-        b = dd_add(b, dd{p[(size_t)t * 4 + 2], p[(size_t)t * 4 + 3]});
+        a = dd_sum(a, dd{p[(size_t)t * 4 + 0], p[(size_t)t * 4 + 1]});
+        b = dd_sum(b, dd{p[(size_t)t * 4 + 2], p[(size_t)t * 4 + 3]});
     }
     block_reduce_store<true>(a.hi, a.lo, b.hi, b.lo, I->dots + (size_t)idx * 4);
 }

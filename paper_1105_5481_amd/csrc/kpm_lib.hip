@@ -652,6 +652,8 @@ void tb_plan(const kpm_ham *h, Plan &p)
     p.xcd = p.tiles >= XCD_MIN_ITEMS ? 3 : 0;
 }
 
+constexpr uint32_t RUN_PLANES = 4;   // planes a run of short segments covers
+
 bool make_plan(const kpm_ham *h, int32_t M, int32_t R, int32_t vec, Plan &p, bool allow_tb = true)
 {
     if (!h || M < 1 || R < 1 || vec < 0 || vec > 2) return false;
@@ -707,19 +709,32 @@ bool make_plan(const kpm_ham *h, int32_t M, int32_t R, int32_t vec, Plan &p, boo
         const bool spin_stream = h->opk == OP_SPIN3 && h->prec == KPM_F32 &&
                                  stream_choice(2ull * h->N * p.Rs * p.esz + (uint64_t)h->N * 7 * p.esz) == 1;
         p.grid_cap = spin_stream ? std::max<uint32_t>(8, (uint32_t)g_max_blocks / 32 * 8) : (uint32_t)g_max_blocks;
-        const uint64_t items = spin_stream ? 4ull * (uint64_t)g_march_items : (uint64_t)g_march_items;
-        uint32_t nseg = (uint32_t)((items + p.nct - 1) / p.nct);
-        nseg = std::max<uint32_t>(1, std::min<uint32_t>(nseg, std::max<uint32_t>(1, p.Lm / 8)));
+        // Segments: as many as give the target work items (two blocks per CU), down to one
+        // plane each.  A launch of a small lattice lasts as long as one block's planes, each
+        // a load's latency; held to 8 planes or more, 16^3 to 48^3 lattices filled a fraction
+        // of the chip.  us per step, 8 planes -> now (R): spin FP32 16^3 (8) 8.8 -> 3.6, 32^3
+        // (16) 11.7 -> 5.6, 40^3 (16) 11.1 -> 7.8, 70 x 50 x 33 (9) 15.4 -> 9; FP64 32^3 (16)
+        // 11.6 -> 9.0, real FP64 16^3 (8) 9.3 -> 4.0.  From 48^3 (R = 16) up both rules agree.
+        uint32_t nseg;
+        if (spin_stream) {
+            nseg = (uint32_t)((4ull * (uint64_t)g_march_items + p.nct - 1) / p.nct);
+            nseg = std::max<uint32_t>(1, std::min<uint32_t>(nseg, std::max<uint32_t>(1, p.Lm / 8)));
+        } else {
+            nseg = (uint32_t)(((uint64_t)g_march_items + p.nct / 2) / p.nct);
+            nseg = std::max<uint32_t>(1, std::min<uint32_t>(nseg, p.Lm));
+        }
         p.S = (p.Lm + nseg - 1) / nseg;
         p.nseg = (p.Lm + p.S - 1) / p.S;
         p.tiles = p.nct * p.nseg;
-        // split per XCD along the column tiles (measured best on the 64^3 and
-        // 2048^2 lattices), else along the march segments
-        p.xcd = p.nct >= XCD_MIN_ITEMS ? 1 : ((p.nseg >= 8 && p.tiles >= XCD_MIN_ITEMS) ? 2 : 0);
+        // each XCD an eighth of the items, in plane order.  Split by column tiles instead, the
+        // XCDs differ by up to a tile's whole column: 100^3 lattices 43.8 -> 28.4 us per step
+        // (spin FP32, R = 5), 53.4 -> 36.3 (real FP64, R = 8).  The streamed FP32 spin solves,
+        // a quarter of the blocks, keep the tiles together (even shares 3-6% slower)
+        p.xcd = spin_stream ? (p.nct >= XCD_MIN_ITEMS ? 1 : 0) : (p.tiles >= XCD_MIN_ITEMS ? 3 : 0);
         if (g_xcd_split == 1) p.xcd = p.nct >= XCD_MIN_ITEMS ? 1 : 0;
         if (g_xcd_split == 2) p.xcd = p.nseg >= 8 ? 2 : 0;
         if (g_xcd_split == 3) p.xcd = 0;
-        p.alt = g_alternate;
+        p.alt = p.S >= RUN_PLANES ? g_alternate : 0;   // shorter segments may be walked in runs
     } else {
         p.mode = MODE_FLAT;
         const uint64_t per_tile = (uint64_t)BLOCK * p.tpt;
@@ -779,6 +794,7 @@ void fill_inst(const kpm_ham *h, const Plan &p, int32_t M, int32_t R, int32_t ve
     I.S = p.S;
     I.nct = p.nct;
     I.nseg = p.nseg;
+    I.run = 1;
     I.cplx = p.cplx;
     I.M = M;
     I.K = p.K;
@@ -1467,6 +1483,26 @@ namespace {
 // 183.7 ms per batched solve (only the instances without a split of their own,
 // 10% slack: 192.3 ms).  Dynamic batches, whose few members differ widely in
 // size, measured 1-2% slower under that rule and keep the one above.
+// Runs of the march instances of one launch: short segments (fewer than RUN_PLANES
+// planes) are walked in runs of about that many planes once the launch has more than
+// RUN_BLOCKS blocks without them (4 per CU); below that the blocks are what is missing.
+// us per step of all waves of 256 cubes (L = 16 .. 48, R = 16, FP32) / 128 cubes (16 .. 24)
+// with runs of 1, 4, 6, 8, 12, 16 planes: 711 / 713 / 729 / 740 / 797 / 818 and 93.2 / 90.1 /
+// 93.9 / 93.6 / 98.5 / 103 (segments of 8 planes and whole instances per XCD: 752, 88).
+constexpr uint64_t RUN_BLOCKS = 1024;
+void set_runs(std::vector<Inst> &ins)
+{
+    uint64_t blocks = 0;
+    for (const Inst &I : ins) blocks += I.nb;
+    for (Inst &I : ins) {
+        I.run = 1;
+        if (I.mode != MODE_MARCH || I.S >= RUN_PLANES || blocks <= RUN_BLOCKS) continue;
+        I.run = (uint32_t)std::min<uint64_t>({RUN_PLANES / I.S, RUN_MAX, (blocks + RUN_BLOCKS - 1) / RUN_BLOCKS});
+        const uint32_t items = I.nct * ((I.nseg + I.run - 1) / I.run);
+        I.nb = std::min<uint32_t>(I.nb, (items + 7) / 8 * 8);
+    }
+}
+
 constexpr uint32_t SPLIT_MIN_UNITS = 48;   // below this a split leaves too few units per XCD (halo re-fetch)
 uint32_t place_blocks(std::vector<Inst> &ins, std::vector<uint32_t> &map, bool wave = false)
 {
@@ -1497,7 +1533,7 @@ uint32_t place_blocks(std::vector<Inst> &ins, std::vector<uint32_t> &map, bool w
         for (int y = 1; y < 8; ++y)
             if (load[y] < load[x]) x = y;
         if ((double)(load[x] + cost(r)) > share && units(r) >= SPLIT_MIN_UNITS && ins[r].nb >= 8) {
-            ins[r].xcd = ins[r].mode == MODE_TB ? 3 : 1;   // split over all XCDs (blocked passes evenly, else by units)
+            ins[r].xcd = 3;   // split over all XCDs
             big.push_back(r);
             for (int y = 0; y < 8; ++y) load[y] += cost(r) / 8;
             continue;
@@ -1530,6 +1566,63 @@ uint32_t place_blocks(std::vector<Inst> &ins, std::vector<uint32_t> &map, bool w
     }
     return blocks + 8 * span;
 }
+
+// Even placement of the march instances of one wave of a static batch: the items of
+// all instances, in table order, are cut into eight shares of equal work, one per XCD
+// (the cost of an item is its instance's chunks over its items).  An instance lies
+// whole on one XCD or in consecutive ranges on two neighbouring ones (more if it is
+// larger than a share), so its halo planes still meet in few L2s, and no XCD waits:
+// whole instances balanced by size left the slowest XCD of a wave of the 256-cube
+// batch (L = 16 .. 48) 9% above the mean.  Each range is a table entry of its own
+// (xcd = 4) in `pieces`, on blocks x, x + 8, ... of its XCD x; returns the grid size.
+struct EvenMap {
+    uint32_t used[8], span;   // blocks used on each XCD, and the most
+};
+uint32_t place_even(const std::vector<Inst> &ins, std::vector<Inst> &pieces, EvenMap &em)
+{
+    std::memset(&em, 0, sizeof(em));
+    double total = 0.0, done = 0.0;
+    for (const Inst &I : ins) total += (double)I.nel;
+    uint32_t x = 0;
+    for (const Inst &I : ins) {
+        const uint32_t n = I.nct * ((I.nseg + I.run - 1) / I.run);
+        const double cost = (double)I.nel / n;
+        for (uint32_t q = 0; q < n;) {
+            const double room = (total * (x + 1) / 8.0 - done) / cost;
+            if (x < 7 && room < 0.5) {
+                ++x;
+                continue;
+            }
+            const uint32_t take = x == 7 ? n - q : std::min<uint32_t>(n - q, (uint32_t)(room + 0.5));
+            Inst P = I;
+            P.xcd = 4;
+            P.q0 = q;
+            P.q1 = q + take;
+            P.nb = std::min<uint32_t>(take, (uint32_t)g_max_blocks);
+            P.block0 = x + 8 * em.used[x];
+            P.bstride = 8;
+            em.used[x] += P.nb;
+            pieces.push_back(P);
+            q += take;
+            done += take * cost;
+        }
+    }
+    for (uint32_t y = 0; y < 8; ++y) em.span = std::max(em.span, em.used[y]);
+    return 8 * em.span;
+}
+// The block map of place_even's pieces, written on the device: block p < count fills
+// entry p's blocks, the last one marks the idle blocks.
+__global__ __launch_bounds__(256) void k_fill_map(const Inst *__restrict__ pieces, uint32_t count, EvenMap em,
+                                                  uint32_t *__restrict__ map)
+{
+    if (blockIdx.x < count) {
+        const uint32_t nb = pieces[blockIdx.x].nb, b0 = pieces[blockIdx.x].block0;
+        for (uint32_t j = threadIdx.x; j < nb; j += 256) map[b0 + 8 * j] = blockIdx.x;
+    } else {
+        for (uint32_t y = 0; y < 8; ++y)
+            for (uint32_t j = em.used[y] + threadIdx.x; j < em.span; j += 256) map[y + 8 * j] = NO_INSTANCE;
+    }
+}
 }  // namespace
 namespace {
 // One multi-instance launch: the instances of one kernel class, contiguous in
@@ -1540,6 +1633,7 @@ struct BatchGroup {
     uint32_t blocks;         // grid size
     size_t map_off;          // offset into the block map (words)
     size_t lds;              // single-workgroup solves: dynamic LDS bytes
+    uint32_t pfirst, pcount; // march groups: range of the table of pieces (place_even)
 };
 // Instances whose recursions run together, step by step, before the next wave
 // starts.  A wave's vectors and operators are sized to stay in the Infinity
@@ -1554,7 +1648,8 @@ struct BatchLayout {
     std::vector<int> order;           // table index -> instance
     std::vector<BatchGroup> small;    // single-workgroup solves, one launch per kernel class
     std::vector<BatchWave> waves;
-    size_t tab_off, map_off, inst_off, total, map_words;
+    size_t tab_off, piece_off, map_off, inst_off, total, map_words;
+    uint32_t pieces;                  // table entries of the march groups
     std::vector<size_t> region_off;   // per instance
     int prec;
 };
@@ -1570,7 +1665,7 @@ void add_groups(kpm_ham *const *h, const std::vector<int> &ids, BatchLayout &L, 
         if (std::find(keys.begin(), keys.end(), key) == keys.end()) keys.push_back(key);
     }
     for (int key : keys) {
-        BatchGroup g{0, 0, 0, 0, (uint32_t)L.order.size(), 0, 0, L.map_words, 0};
+        BatchGroup g{0, 0, 0, 0, (uint32_t)L.order.size(), 0, 0, L.map_words, 0, L.pieces, 0};
         std::vector<Inst> ins;
         for (int i : ids) {
             const Plan &p = L.plans[i];
@@ -1587,15 +1682,27 @@ void add_groups(kpm_ham *const *h, const std::vector<int> &ids, BatchLayout &L, 
             I.nel = p.nel;
             I.mode = p.mode;
             I.nct = p.nct;
+            I.nseg = p.nseg;
+            I.S = p.S;
             I.tiles = p.tiles;
             ins.push_back(I);
             L.order.push_back(i);
         }
         g.count = (uint32_t)ins.size();
         if (g.mode != MODE_SMALL) {
-            std::vector<uint32_t> m;
-            g.blocks = place_blocks(ins, m, true);
-            L.map_words += m.size();
+            set_runs(ins);
+            if (g.mode == MODE_MARCH) {
+                std::vector<Inst> pieces;
+                EvenMap em;
+                g.blocks = place_even(ins, pieces, em);
+                g.pcount = (uint32_t)pieces.size();
+                L.pieces += g.pcount;
+                L.map_words += g.blocks;
+            } else {
+                std::vector<uint32_t> m;
+                g.blocks = place_blocks(ins, m, true);
+                L.map_words += m.size();
+            }
         }
         groups.push_back(g);
     }
@@ -1607,6 +1714,7 @@ bool batch_layout(kpm_ham *const *h, int32_t count, const int32_t *M, const int3
     L.plans.resize(count);
     L.prec = h[0] ? h[0]->prec : -1;
     L.map_words = 0;
+    L.pieces = 0;
     std::vector<int> small, rest;
     for (int i = 0; i < count; ++i) {
         if (!h[i] || h[i]->prec != L.prec) return false;
@@ -1648,7 +1756,8 @@ bool batch_layout(kpm_ham *const *h, int32_t count, const int32_t *M, const int3
         L.waves.push_back(std::move(bw));
     }
     L.tab_off = 0;
-    L.map_off = align256((size_t)count * sizeof(Inst));
+    L.piece_off = align256((size_t)count * sizeof(Inst));
+    L.map_off = L.piece_off + align256((size_t)L.pieces * sizeof(Inst));
     L.inst_off = L.map_off + align256(L.map_words * 4 + 4);
     L.region_off.resize(count);
     size_t off = L.inst_off;
@@ -1688,20 +1797,39 @@ kpm_status kpm_moments_batched(kpm_ham *const *h, int32_t count, const int32_t *
         tab[t].mu = mu_dev[i];
         Mmax = std::max(Mmax, M[i]);
     }
-    // block maps, with the placement batch_layout sized them for
-    std::vector<uint32_t> map;
+    // block maps, with the placement batch_layout sized them for: march groups through
+    // their pieces, the others from the host
+    std::vector<Inst> pieces;
     std::vector<const BatchGroup *> all;
     for (const BatchWave &w : L.waves)
         for (const BatchGroup &g : w.groups) all.push_back(&g);
-    for (const BatchGroup *g : all) {
-        std::vector<Inst> ins(tab.begin() + g->first, tab.begin() + g->first + g->count);
-        if (map.size() != g->map_off || place_blocks(ins, map, true) != g->blocks) return KPM_ERR_INVALID_ARG;
-        std::copy(ins.begin(), ins.end(), tab.begin() + g->first);
-    }
-    Inst *tab_dev = (Inst *)(base + L.tab_off);
+    Inst *tab_dev = (Inst *)(base + L.tab_off), *piece_dev = (Inst *)(base + L.piece_off);
     uint32_t *map_dev = (uint32_t *)(base + L.map_off);
-    kpm_status e = upload(tab_dev, tab.data(), tab.size() * sizeof(Inst), st);
-    if (e == KPM_OK && !map.empty()) e = upload(map_dev, map.data(), map.size() * 4, st);
+    std::vector<EvenMap> maps(all.size());
+    kpm_status e = KPM_OK;
+    for (size_t q = 0; q < all.size() && e == KPM_OK; ++q) {
+        const BatchGroup *g = all[q];
+        std::vector<Inst> ins(tab.begin() + g->first, tab.begin() + g->first + g->count);
+        set_runs(ins);
+        if (g->mode == MODE_MARCH) {
+            if (pieces.size() != g->pfirst || place_even(ins, pieces, maps[q]) != g->blocks) return KPM_ERR_INVALID_ARG;
+        } else {
+            std::vector<uint32_t> map;
+            if (place_blocks(ins, map, true) != g->blocks) return KPM_ERR_INVALID_ARG;
+            std::copy(ins.begin(), ins.end(), tab.begin() + g->first);
+            e = upload(map_dev + g->map_off, map.data(), map.size() * 4, st);
+        }
+    }
+    if (e == KPM_OK) e = upload(tab_dev, tab.data(), tab.size() * sizeof(Inst), st);
+    if (e == KPM_OK && !pieces.empty()) e = upload(piece_dev, pieces.data(), pieces.size() * sizeof(Inst), st);
+    for (size_t q = 0; q < all.size() && e == KPM_OK; ++q) {
+        const BatchGroup *g = all[q];
+        if (g->mode != MODE_MARCH) continue;
+        hipLaunchKernelGGL(k_fill_map, dim3(g->pcount + 1), dim3(256), 0, st, piece_dev + g->pfirst, g->pcount, maps[q],
+                           map_dev + g->map_off);
+        e = check_launch();
+    }
+    auto table = [&](const BatchGroup &g) { return g.mode == MODE_MARCH ? piece_dev + g.pfirst : tab_dev + g.first; };
     for (const BatchGroup &g : L.small) {
         int32_t kmax = 0;
         for (uint32_t t = g.first; t < g.first + g.count; ++t) kmax = std::max(kmax, L.plans[L.order[t]].K);
@@ -1710,7 +1838,7 @@ kpm_status kpm_moments_batched(kpm_ham *const *h, int32_t count, const int32_t *
     }
     for (const BatchWave &w : L.waves) {
         for (const BatchGroup &g : w.groups)
-            if (e == KPM_OK) e = launch_init(L.prec, g.wide, tab_dev + g.first, map_dev + g.map_off, g.blocks, st);
+            if (e == KPM_OK) e = launch_init(L.prec, g.wide, table(g), map_dev + g.map_off, g.blocks, st);
         Inst *wt = tab_dev + w.first;
         int32_t written = 1, reduced = 0;  // dots indices, in lockstep for every instance of the wave
         for (int32_t k = 0; k < w.Kmax && e == KPM_OK; ++k) {
@@ -1720,8 +1848,7 @@ kpm_status kpm_moments_batched(kpm_ham *const *h, int32_t count, const int32_t *
             }
             for (const BatchGroup &g : w.groups)
                 if (e == KPM_OK)
-                    e = launch_step(L.prec, g.opk, g.mode, g.wide, g.nt, tab_dev + g.first, map_dev + g.map_off,
-                                    g.blocks, k, st);
+                    e = launch_step(L.prec, g.opk, g.mode, g.wide, g.nt, table(g), map_dev + g.map_off, g.blocks, k, st);
             written += 1;
         }
         if (e == KPM_OK) e = launch_reduce(wt, (int32_t)w.count, reduced - 1, written - reduced, st);
@@ -1878,6 +2005,7 @@ kpm_status kpm_batch_advance(kpm_batch *b, int32_t steps, void *stream)
             ins.push_back(I);
         }
         g.count = (uint32_t)ins.size();
+        set_runs(ins);
         g.blocks = place_blocks(ins, map);
         tab.insert(tab.end(), ins.begin(), ins.end());
         groups.push_back(g);
