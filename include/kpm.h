@@ -247,8 +247,9 @@ kpm_status kpm_solve_advance(kpm_solve *s, int32_t max_steps, void *stream, int3
 kpm_status kpm_solve_finish(kpm_solve *s, double *mu_dev, void *stream);
 void kpm_solve_free(kpm_solve *s);
 /* How the solve's recursion runs: 0 flat kernels (one step per launch), 1 march
- * kernels (one step per launch), 2 whole recursion in one workgroup (done at
- * begin), 3 temporal blocking (1 to 6 steps per launch, KPM_LAUNCH_TBLOCK);
+ * kernels (one step per launch), 2 few sites: a workgroup's LDS per chunk group
+ * (the whole recursion at begin where all vectors fit one LDS, else many steps
+ * per launch), 3 temporal blocking (1 to 6 steps per launch, KPM_LAUNCH_TBLOCK);
  * -1 for NULL. */
 int32_t kpm_solve_mode(const kpm_solve *s);
 /* Recursion steps of the solve's deepest launch (mode 3 and the 3D blocked passes:
@@ -369,8 +370,9 @@ kpm_status kpm_start_vectors(int32_t vec, int32_t complex_layout, uint64_t seed,
  *   KPM_LAUNCH_XCD_SPLIT         how an instance's work items are split over the 8 XCDs:
  *                                0 automatic (march: evenly, in plane order), 1 by column tiles, 2 by march segments, 3 none
  *   KPM_LAUNCH_ALTERNATE         1: odd march segments of 4 planes or more walk downwards
- *   KPM_LAUNCH_SMALL             1: a solve whose two vector blocks fit in the LDS of one
- *                                compute unit runs entirely in one workgroup (one launch)
+ *   KPM_LAUNCH_SMALL             1: a solve of few sites (its two vector blocks fit in the LDS of
+ *                                one compute unit, or it has at most 2048 sites) keeps its
+ *                                vectors in the LDS, one workgroup per group of chunks
  *   KPM_LAUNCH_STREAMING         march kernels: 1 = r_{n-1} read / r_{n+1} written with
  *                                non-temporal hints, 0 = cached, 2 (default) = cached when
  *                                vectors and operator take at most 256 MiB (they then

@@ -216,7 +216,7 @@ __global__ __launch_bounds__(64 * NW) void k_dense_resident(const double *__rest
         dot2_acc_biased(s0, e0, re, re);
     }
     const size_t wslot = (size_t)blockIdx.x * NW + w;   // this wave's partial within a slot
-    wave_reduce_store<true>(s0 - DOT_BIAS, e0, 0.0, 0.0, part + wslot * 4);
+    wave_reduce_store<true, true>(s0 - DOT_BIAS, e0, 0.0, 0.0, part + wslot * 4);
     __syncthreads();
     for (int32_t n = 0; n < K; ++n) {
         dn_d4 acc[4];
@@ -242,7 +242,7 @@ __global__ __launch_bounds__(64 * NW) void k_dense_resident(const double *__rest
             cur[v] = out;
             Vs[(16 * w + 4 * v + lk) * 16 + lr] = out;
         }
-        wave_reduce_store<true>(x0 - DOT_BIAS, y0, x1 - DOT_BIAS, y1, part + ((size_t)(n + 1) * nblk * NW + wslot) * 4);
+        wave_reduce_store<true, true>(x0 - DOT_BIAS, y0, x1 - DOT_BIAS, y1, part + ((size_t)(n + 1) * nblk * NW + wslot) * 4);
         __syncthreads();   // the slab of r_{n+1} is complete
     }
 }

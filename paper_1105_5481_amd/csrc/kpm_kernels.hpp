@@ -90,7 +90,8 @@ struct Inst {
     void *tb2, *tb3;   // temporal blocking: buffers 2 and 3 of four (buf0, buf1 are 0 and 1)
     int32_t tbp, tbc;  // ... and which of them hold r_{step0-1}, r_{step0} (batched passes)
     int32_t tbfull, tbrem;  // batched passes of this chunk: tbfull of depth tbh, then one of depth tbrem
-    uint32_t tbg, tbw; // 2D temporal blocking: chunk groups per site, chunks per group (the last may have fewer)
+    uint32_t tbg, tbw; // 2D temporal blocking, few sites: chunk groups per site, chunks per group (the last may have fewer)
+    uint32_t tpb;      // few sites: threads per group
     double *partial;   // [pslots][tiles][4]
     double *dots;      // [K+1][4] = (nn.hi, nn.lo, nm.hi, nm.lo)
     double *mu;        // [M]
@@ -182,6 +183,12 @@ template <> struct Arith<float> {
         ai = fmaf(hr, vi, fmaf(hi, vr, ai));
     }
 };
+
+// 2 v - w in one rounding (2 v is exact, so this is the value of the two operations)
+template <typename T> __device__ __forceinline__ T two_minus(T v, T w)
+{
+    return __builtin_elementwise_fma((T)(2), v, -w);
+}
 
 // Dot-product accumulators: (sum, error) pairs in FP64 for FP64 vectors, started at
 // DOT_BIAS (four operations per product instead of ten); for FP32 vectors the
@@ -276,28 +283,37 @@ struct DotsWide {
     static constexpr bool DD = true;
 };
 
+// Sum of two double-doubles inside a reduction.  FEW: both high parts are multiples of
+// 2^-36 (the last bit of DOT_BIAS) below 2^17, as sums of up to some ten thousand biased
+// products are, so their plain sum is exact.
+template <bool FEW> __device__ __forceinline__ dd dd_part(dd x, dd y)
+{
+    if (FEW) return dd{x.hi + y.hi, x.lo + y.lo};
+    return dd_sum(x, y);
+}
+
 // Sums of x0 + x1 and x2 + x3 over the wavefront, in (a, b): the lower 32 lanes
 // receive the first, the upper 32 the second (as a double-double when DD, else in a
 // alone).  The first exchange gives each half of the wave one of the two sums, so a
 // reduction is six additions of 8 operations, and no exchange goes through the LDS: with
 // ds_bpermute shuffles of both sums it was twelve of 20 and 48 shuffles of 24 cycles, most
 // of a step of the single-workgroup solves.
-template <bool DD>
+template <bool DD, bool FEW = false>
 __device__ __forceinline__ void wave_reduce(double x0, double x1, double x2, double x3, double &a, double &b)
 {
     if (DD) {
         dd p{x0, x1}, q{x2, x3};
         swap_halves(p.hi, q.hi);
         swap_halves(p.lo, q.lo);
-        p = dd_sum(p, q);
+        p = dd_part<FEW>(p, q);
         q = p;
         swap_rows(p.hi, q.hi);
         swap_rows(p.lo, q.lo);
-        p = dd_sum(p, q);
-        p = dd_sum(p, dd{row_ror<8>(p.hi), row_ror<8>(p.lo)});
-        p = dd_sum(p, dd{row_ror<4>(p.hi), row_ror<4>(p.lo)});
-        p = dd_sum(p, dd{row_ror<2>(p.hi), row_ror<2>(p.lo)});
-        p = dd_sum(p, dd{row_ror<1>(p.hi), row_ror<1>(p.lo)});
+        p = dd_part<FEW>(p, q);
+        p = dd_part<FEW>(p, dd{row_ror<8>(p.hi), row_ror<8>(p.lo)});
+        p = dd_part<FEW>(p, dd{row_ror<4>(p.hi), row_ror<4>(p.lo)});
+        p = dd_part<FEW>(p, dd{row_ror<2>(p.hi), row_ror<2>(p.lo)});
+        p = dd_part<FEW>(p, dd{row_ror<1>(p.hi), row_ror<1>(p.lo)});
         a = p.hi;
         b = p.lo;
     } else {
@@ -315,26 +331,27 @@ __device__ __forceinline__ void wave_reduce(double x0, double x1, double x2, dou
 }
 
 // The wavefront's sums of (x0 + x1, x2 + x3), stored as four doubles (hi, lo, hi, lo) at dst.
-template <bool DD>
+template <bool DD, bool FEW = false>
 __device__ __forceinline__ void wave_reduce_store(double x0, double x1, double x2, double x3, double *dst)
 {
     double a, b;
-    wave_reduce<DD>(x0, x1, x2, x3, a, b);
+    wave_reduce<DD, FEW>(x0, x1, x2, x3, a, b);
     const int lane = threadIdx.x & 63;
     if ((lane & 31) == 0) {
         dst[lane >> 4] = a;
         dst[(lane >> 4) + 1] = b;
     }
 }
-template <typename A> __device__ __forceinline__ void wave_reduce_store(const A &d, double *dst)
+template <bool FEW = false, typename A> __device__ __forceinline__ void wave_reduce_store(const A &d, double *dst)
 {
-    wave_reduce_store<A::DD>(d.x0(), d.x1(), d.x2(), d.x3(), dst);
+    wave_reduce_store<A::DD, FEW>(d.x0(), d.x1(), d.x2(), d.x3(), dst);
 }
 
 // The wavefront's sums of two accumulators at once, each in the order of
 // wave_reduce_store: after the first exchange the even rows of 16 lanes go on with the
 // first, the odd rows with the second (7 additions instead of 12).
-template <typename A> __device__ __forceinline__ void wave_reduce_store(const A &d, const A &f, double *dst, double *fdst)
+template <bool FEW = false, typename A>
+__device__ __forceinline__ void wave_reduce_store(const A &d, const A &f, double *dst, double *fdst)
 {
     double a = d.x0(), b = d.x2(), u = f.x0(), v = f.x2();
     if (A::DD) {
@@ -343,15 +360,15 @@ template <typename A> __device__ __forceinline__ void wave_reduce_store(const A 
         swap_halves(p.lo, q.lo);
         swap_halves(r.hi, s.hi);
         swap_halves(r.lo, s.lo);
-        p = dd_sum(p, q);
-        r = dd_sum(r, s);
+        p = dd_part<FEW>(p, q);
+        r = dd_part<FEW>(r, s);
         swap_rows(p.hi, r.hi);
         swap_rows(p.lo, r.lo);
-        p = dd_sum(p, r);
-        p = dd_sum(p, dd{row_ror<8>(p.hi), row_ror<8>(p.lo)});
-        p = dd_sum(p, dd{row_ror<4>(p.hi), row_ror<4>(p.lo)});
-        p = dd_sum(p, dd{row_ror<2>(p.hi), row_ror<2>(p.lo)});
-        p = dd_sum(p, dd{row_ror<1>(p.hi), row_ror<1>(p.lo)});
+        p = dd_part<FEW>(p, r);
+        p = dd_part<FEW>(p, dd{row_ror<8>(p.hi), row_ror<8>(p.lo)});
+        p = dd_part<FEW>(p, dd{row_ror<4>(p.hi), row_ror<4>(p.lo)});
+        p = dd_part<FEW>(p, dd{row_ror<2>(p.hi), row_ror<2>(p.lo)});
+        p = dd_part<FEW>(p, dd{row_ror<1>(p.hi), row_ror<1>(p.lo)});
         a = p.hi;
         b = p.lo;
     } else {
@@ -810,7 +827,7 @@ __global__ __launch_bounds__(BLOCK) void k_step_march(const Inst *__restrict__ t
                         out = apply_cplx<S, NS>(hd, d, v0, nb, hr, hi);
                         bb = ba;
                     }
-                    if (!first) out = (S)2 * out - prev;
+                    if (!first) out = two_minus(out, prev);
                     G::template st_s<NT>(nxt, ch, out);
                     acc.add(out, v0);
                     vb = v0;
@@ -913,7 +930,7 @@ __device__ __forceinline__ void flat_elem(const Inst &I, uint32_t e, const void 
     }
     if (!first) {
         const T p = G::ld_nt(nxt, e);
-        out = (S)2 * out - p;
+        out = two_minus(out, p);
     }
     G::st_nt(nxt, e, out);
     acc.add(out, v);
@@ -947,137 +964,267 @@ __global__ __launch_bounds__(BLOCK) void k_step_flat(const Inst *__restrict__ ta
 }
 
 // ---------------------------------------------------------------------------
-// the whole solve of a small instance inside one workgroup
+// solves of few sites: a site's vectors in the LDS of one workgroup
 // ---------------------------------------------------------------------------
-// Both vector blocks live in LDS (2 * N * C * 16 bytes <= the LDS of one CU),
-// so the recursion never touches HBM; one block per instance, all steps in one
-// launch, one block barrier between steps.  The per-step dots are summed per
-// wave only: partial slot n + 1 holds SMALL_WAVES entries (a block-wide sum
-// each step, whose last part one thread does alone, took about two thirds of
-// the solve), reduced by k_reduce after the launch.
-constexpr int SMALL_BLOCK = 1024;
-constexpr int SMALL_WAVES = SMALL_BLOCK / 64;
+// The vectors of a solve are independent, so a solve of few sites runs as one
+// workgroup per group of tbw of its C chunks, each with r_{n-1}, r_n of all N sites in
+// the LDS (2 * N * tbw * 16 bytes), many steps per launch and one block barrier per
+// step.  A thread owns EPT = 1 or 2 chunks for the whole launch: their r_n and r_{n-1},
+// diagonal, neighbour indices (16 bits each) and bonds stay in registers, so a step
+// reads the neighbours from the LDS and writes one chunk.  (EPT = 0: more chunks per
+// thread, taken from the LDS and placed anew each step.)
+// Dots are summed per wave for two steps at once and over the waves every fourth step,
+// by waves 0 and 1 while the others go on; each step leaves one partial per group.
+//
+// What bounds it: the chain of one step (LDS reads, the stencil, the sums, the barrier).
+// us per step of whole solves of 128 steps, launches included; before: one 1024-thread
+// workgroup for all chunks and a whole wave sum per wave and step where they fitted, else a
+// launch per step: 32 x 32 sites FP64 R = 8 5.65 -> 1.13, R = 32 7.9 -> 1.16; 10^3 spin FP32
+// R = 16 10.5 -> 1.2; 12^3 spin FP64 R = 16 13.7 -> 2.9; 64 x 64 FP32 R = 4 3.5 -> 2.9.
+constexpr uint32_t SMALL_BLOCK = 1024;
+constexpr uint32_t SMALL_WAVES = SMALL_BLOCK / 64;
+constexpr uint32_t SMALL_EPT = 2;     // most chunks per thread kept in registers
 
-template <typename S, int OPK>
-__device__ __forceinline__ typename V16<S>::T small_elem(const Inst &I, uint32_t e, const typename V16<S>::T *cur,
-                                                         S hop)
+// Steps step0 + n0 .. step0 + n1 - 1 (at most to K) of each instance of the table; n0 < 0 draws
+// r_0 first and starts at step 0.  A solve that does not end with the launch leaves r_{n-1},
+// r_n in buf0 / buf1 (r_m in buffer m & 1) and takes them from there in the next.
+template <typename S, int OPK, int EPT>
+__global__ __launch_bounds__(SMALL_BLOCK) void k_solve_small(const Inst *__restrict__ tab, int32_t n0, int32_t n1)
 {
     typedef typename V16<S>::T T;
     typedef Mem<S, false> G;
     typedef typename Mem<S, false>::S2 S2;
     typedef Arith<S> A;
     constexpr int W = V16<S>::W;
-    const uint32_t C = I.C;
-    const uint32_t i = fdiv(e, I.fC);
-    const uint32_t c = e - i * C;
-    const T v = cur[e];
-    T out;
-    if constexpr (OPK <= OP_SPIN3) {
-        constexpr bool D3 = (OPK == OP_REAL3 || OPK == OP_SPIN3);
-        constexpr bool SPIN = (OPK == OP_SPIN2 || OPK == OP_SPIN3);
-        constexpr int DIM = D3 ? 3 : 2;
-        constexpr int NS = 2 * DIM;
-        const uint32_t Lx = I.Lx, Ly = I.Ly;
-        const uint32_t yq = fdiv(i, I.fLx);
-        const uint32_t x = i - yq * Lx;
-        uint32_t y = yq, z = 0;
-        if constexpr (D3) {
-            z = fdiv(yq, I.fLy);
-            y = yq - z * Ly;
-        }
-        uint32_t nbi[NS];
-        nbi[0] = (x == 0) ? i + (Lx - 1) : i - 1;
-        nbi[1] = (x == Lx - 1) ? i - (Lx - 1) : i + 1;
-        nbi[2] = (y == 0) ? i + (Ly - 1) * Lx : i - Lx;
-        nbi[3] = (y == Ly - 1) ? i - (Ly - 1) * Lx : i + Lx;
-        if constexpr (D3) {
-            const uint32_t Pz = Lx * Ly, Lz = I.Lz;
-            nbi[4] = (z == 0) ? i + (Lz - 1) * Pz : i - Pz;
-            nbi[5] = (z == Lz - 1) ? i - (Lz - 1) * Pz : i + Pz;
-        }
-        T nb[NS];
-#pragma unroll
-        for (int s = 0; s < NS; ++s) nb[s] = cur[nbi[s] * C + c];
-        const bool hd = I.has_diag;
-        const S d = hd ? G::lds(I.diag, i) : (S)0;
-        if (!SPIN) {
-            out = apply_real<S, NS>(hd, d, hop, v, nb);
-        } else {
-            S hr[NS], hi[NS];
-#pragma unroll
-            for (int ax = 0; ax < DIM; ++ax) {
-                const S2 bm = G::ldc(I.bond, nbi[2 * ax] * DIM + ax);
-                const S2 bp = G::ldc(I.bond, i * DIM + ax);
-                hr[2 * ax] = bm[0]; hi[2 * ax] = -bm[1];
-                hr[2 * ax + 1] = bp[0]; hi[2 * ax + 1] = bp[1];
+    constexpr bool CSR = OPK >= OP_CSR_R;
+    constexpr bool D3 = (OPK == OP_REAL3 || OPK == OP_SPIN3);
+    constexpr bool SPIN = (OPK == OP_SPIN2 || OPK == OP_SPIN3);
+    constexpr int DIM = D3 ? 3 : 2;
+    constexpr int NS = 2 * DIM;
+    constexpr int NE = EPT ? EPT : 1;   // EPT = 0: any number of chunks, their values in the LDS alone
+    extern __shared__ __align__(16) char kpm_lds[];
+    __shared__ double red[2][4][SMALL_WAVES][4];
+    const Inst I = tab[blockIdx.x];
+    const uint32_t g = blockIdx.y;
+    if (g >= I.tbg) return;
+    const int32_t na = I.step0 + max(n0, 0), nz = min(I.step0 + n1, I.K);
+    if (n0 >= 0 && na >= nz) return;
+    const uint32_t C = I.C, cg0 = g * I.tbw, ng = min(I.tbw, C - cg0), ne = I.N * ng, tpb = I.tpb;
+    const uint32_t tid = threadIdx.x, w = tid >> 6, nw = tpb >> 6;
+    const bool alive = tid < tpb;   // the other waves only keep the barriers
+    auto lb = [&](int32_t m) { return reinterpret_cast<T *>(kpm_lds) + ((m & 1) ? ne : 0u); };   // where r_m is
+    S hop = 0;
+    if (OPK == OP_REAL2 || OPK == OP_REAL3) hop = G::lds(I.hop, 0);
+    const bool hd = CSR || I.has_diag;
+    auto div_ng = [&](uint32_t e) { return ng == 1 ? e : e / ng; };
+    T v[NE], pv[NE];
+    S d[NE];
+    uint32_t site[NE];
+    uint32_t nbx[NE][EPT ? DIM : NS];   // neighbours' LDS elements, two per word where they are kept
+    // bonds in registers, but for two FP64 chunks per thread (96 VGPRs of bonds alone in 3D)
+    constexpr bool KEEP = SPIN && !(EPT == 2 && sizeof(S) == 8);
+    S2 bnd[NE][KEEP ? NS : 1];
+    uint32_t sbm[NE][SPIN && !KEEP ? DIM : 1];   // else the sites of the backward ones
+    // diagonal, neighbours and bonds of chunk e into the registers of slot u
+    auto place = [&](int u, uint32_t e) {
+        const uint32_t i = div_ng(e), cl = e - i * ng;
+        site[u] = i;
+        d[u] = hd ? G::lds(I.diag, i) : (S)0;
+        if constexpr (!CSR) {
+            const uint32_t Lx = I.Lx, Ly = I.Ly;
+            const uint32_t yq = fdiv(i, I.fLx), x = i - yq * Lx;
+            uint32_t y = yq, z = 0;
+            if constexpr (D3) {
+                z = fdiv(yq, I.fLy);
+                y = yq - z * Ly;
             }
-            out = apply_cplx<S, NS>(hd, d, v, nb, hr, hi);
-        }
-    } else {
-        const int64_t kb = I.row_ptr[i], ke = I.row_ptr[i + 1];
-        const S d = G::lds(I.diag, i);
-        T a;
+            uint32_t nb[6];
+            nb[0] = (x == 0) ? i + (Lx - 1) : i - 1;
+            nb[1] = (x == Lx - 1) ? i - (Lx - 1) : i + 1;
+            nb[2] = (y == 0) ? i + (Ly - 1) * Lx : i - Lx;
+            nb[3] = (y == Ly - 1) ? i - (Ly - 1) * Lx : i + Lx;
+            nb[4] = nb[5] = i;
+            if constexpr (D3) {
+                const uint32_t P = Lx * Ly, Lz = I.Lz;
+                nb[4] = (z == 0) ? i + (Lz - 1) * P : i - P;
+                nb[5] = (z == Lz - 1) ? i - (Lz - 1) * P : i + P;
+            }
 #pragma unroll
-        for (int l = 0; l < W; ++l) a[l] = d * v[l];
-        for (int64_t kk = kb; kk < ke; ++kk) {
-            const uint32_t jj = (uint32_t)I.col[kk];
-            if (jj == i) continue;
-            const T vj = cur[jj * C + c];
-            if constexpr (OPK == OP_CSR_R) {
-                a = A::mac(a, ((const S *)I.val)[kk], vj);
-            } else {
-                const S hr = ((const S *)I.val)[2 * kk], hi = ((const S *)I.val)[2 * kk + 1];
+            for (int k = 0; k < DIM; ++k) {
+                const uint32_t m = nb[2 * k] * ng + cl, q = nb[2 * k + 1] * ng + cl;   // below 2^16
+                if constexpr (EPT) {
+                    nbx[u][k] = m | (q << 16);
+                } else {
+                    nbx[u][2 * k] = m;
+                    nbx[u][2 * k + 1] = q;
+                }
+            }
+            if constexpr (SPIN) {
 #pragma unroll
-                for (int l = 0; l < W / 2; ++l) {
-                    S ar = a[2 * l], ai = a[2 * l + 1];
-                    A::cmac(ar, ai, hr, hi, vj[2 * l], vj[2 * l + 1]);
-                    a[2 * l] = ar;
-                    a[2 * l + 1] = ai;
+                for (int ax = 0; ax < DIM; ++ax) {
+                    if constexpr (KEEP) {
+                        const S2 m = G::ldc(I.bond, nb[2 * ax] * DIM + ax);
+                        bnd[u][2 * ax] = S2{m[0], -m[1]};
+                        bnd[u][2 * ax + 1] = G::ldc(I.bond, i * DIM + ax);
+                    } else {
+                        sbm[u][ax] = nb[2 * ax];
+                    }
                 }
             }
         }
-        out = a;
-    }
-    return out;
-}
-
-template <typename S, int OPK>
-__global__ __launch_bounds__(SMALL_BLOCK) void k_solve_small(const Inst *__restrict__ tab)
-{
-    typedef typename V16<S>::T T;
-    extern __shared__ __align__(16) char kpm_lds[];
-    const Inst I = tab[blockIdx.x];
-    T *b0 = reinterpret_cast<T *>(kpm_lds);
-    T *b1 = b0 + I.nel;
-    S hop = 0;
-    if (OPK == OP_REAL2 || OPK == OP_REAL3) hop = Mem<S, false>::lds(I.hop, 0);
-    const uint32_t w = threadIdx.x >> 6;
-    {
-        Dots<S> acc;
-        for (uint32_t e = threadIdx.x; e < I.nel; e += SMALL_BLOCK) {
-            const uint32_t i = fdiv(e, I.fC), c = e - i * I.C;
-            const T v = start_chunk<S>(I, i, c);
-            b0[e] = v;
-            acc.norm_only(v);
+    };
+    // r_n of chunk e: drawn, or left by the last launch (with r_{n-1} in buffer na & 1 ^ 1)
+    Dots<S> acc;
+    auto first_value = [&](uint32_t e) {
+        const uint32_t i = div_ng(e), c = cg0 + e - i * ng;
+        if (n0 >= 0) return G::ld((na & 1) ? I.buf1 : I.buf0, i * C + c);
+        const T x = start_chunk<S>(I, i, c);
+        acc.norm_only(x);
+        return x;
+    };
+    auto before = [&](uint32_t e) {
+        const uint32_t i = div_ng(e);
+        return (n0 >= 0 && na > 0) ? G::ld((na & 1) ? I.buf0 : I.buf1, i * C + cg0 + e - i * ng) : (T)(S)0;
+    };
+    if constexpr (EPT == 0) {
+        if (alive)
+            for (uint32_t e = tid; e < ne; e += tpb) {
+                lb(na)[e] = first_value(e);
+                lb(na + 1)[e] = before(e);
+            }
+    } else {
+#pragma unroll
+        for (int u = 0; u < EPT; ++u) {
+            const uint32_t e = tid + (uint32_t)u * tpb;
+            if (!alive || e >= ne) continue;
+            place(u, e);
+            v[u] = first_value(e);
+            pv[u] = before(e);
+            lb(na)[e] = v[u];
         }
-        wave_reduce_store(acc, I.partial + (size_t)w * 4);
     }
-    __syncthreads();   // r_0 complete
-    for (int32_t n = 0; n < I.K; ++n) {
-        const T *cur = (n & 1) ? b1 : b0;
-        T *nxt = (n & 1) ? b0 : b1;
-        Dots<S> acc;
-        for (uint32_t e = threadIdx.x; e < I.nel; e += SMALL_BLOCK) {
-            T out = small_elem<S, OPK>(I, e, cur, hop);
-            if (n > 0) out = (S)2 * out - nxt[e];
+    const size_t pitch = (size_t)I.tiles * 4;
+    double *const part = I.partial + (size_t)g * 4;
+    if (n0 < 0) {   // <r_0|r_0>
+        if (alive) wave_reduce_store<true>(acc, red[0][0][w]);
+        __syncthreads();
+        if (tid < 2) {
+            dd a{0.0, 0.0};
+            for (uint32_t k = 0; k < nw; ++k) a = dd_part<true>(a, dd{red[0][0][k][2 * tid], red[0][0][k][2 * tid + 1]});
+            part[2 * tid] = a.hi;
+            part[2 * tid + 1] = a.lo;
+        }
+    }
+    __syncthreads();   // r_n complete
+    // the sums over the waves of steps nq .. (at most four, `m` of them), from red[half]: rows of
+    // 16 lanes of waves 0 and 1, one row per step and sum
+    auto flush = [&](int32_t nq, int32_t m, int half) {
+        for (uint32_t h = w; h < 2; h += nw) {
+            const uint32_t lane = tid & 63, q = 2 * h + (lane >> 5), o = ((lane >> 4) & 1u) * 2, k = lane & 15;
+            dd a{0.0, 0.0};
+            if ((int32_t)q < m && k < nw) a = dd{red[half][q][k][o], red[half][q][k][o + 1]};
+            a = dd_part<true>(a, dd{row_ror<8>(a.hi), row_ror<8>(a.lo)});
+            a = dd_part<true>(a, dd{row_ror<4>(a.hi), row_ror<4>(a.lo)});
+            a = dd_part<true>(a, dd{row_ror<2>(a.hi), row_ror<2>(a.lo)});
+            a = dd_part<true>(a, dd{row_ror<1>(a.hi), row_ror<1>(a.lo)});
+            if ((int32_t)q < m && k == 0) {
+                double *dst = part + (size_t)((nq + (int32_t)q + 1) % I.pslots) * pitch;
+                dst[o] = a.hi;
+                dst[o + 1] = a.lo;
+            }
+        }
+    };
+    Dots<S> held;
+    for (int32_t n = na; n < nz; ++n) {
+        const int32_t j = n - na;          // steps of this launch so far
+        const int q = j & 3, half = (j >> 2) & 1;
+        const T *cur = lb(n);
+        T *nxt = lb(n + 1);
+        Dots<S> a2;
+        // r_{n+1} of chunk e, whose place is in slot u, from r_n = x and r_{n-1} = y
+        auto next = [&](int u, uint32_t e, T x, T y) {
+            T out;
+            if constexpr (!CSR) {
+                T nb[NS];
+#pragma unroll
+                for (int k = 0; k < DIM; ++k) {
+                    nb[2 * k] = cur[EPT ? nbx[u][k] & 0xffffu : nbx[u][EPT ? k : 2 * k]];
+                    nb[2 * k + 1] = cur[EPT ? nbx[u][k] >> 16 : nbx[u][EPT ? k : 2 * k + 1]];
+                }
+                if constexpr (!SPIN) {
+                    out = apply_real<S, NS>(hd, d[u], hop, x, nb);
+                } else {
+                    S hr[NS], hi[NS];
+#pragma unroll
+                    for (int k = 0; k < NS; ++k) {
+                        if constexpr (KEEP) {
+                            hr[k] = bnd[u][k][0];
+                            hi[k] = bnd[u][k][1];
+                        } else {
+                            const S2 b = G::ldc(I.bond, ((k & 1) ? site[u] : sbm[u][k / 2]) * DIM + k / 2);
+                            hr[k] = b[0];
+                            hi[k] = (k & 1) ? b[1] : -b[1];
+                        }
+                    }
+                    out = apply_cplx<S, NS>(hd, d[u], x, nb, hr, hi);
+                }
+            } else {
+                const uint32_t i = site[u], cl = e - i * ng;
+#pragma unroll
+                for (int l = 0; l < W; ++l) out[l] = d[u] * x[l];
+                for (int64_t kk = I.row_ptr[i]; kk < I.row_ptr[i + 1]; ++kk) {
+                    const uint32_t jj = (uint32_t)I.col[kk];
+                    if (jj == i) continue;
+                    const T vj = cur[jj * ng + cl];
+                    if constexpr (OPK == OP_CSR_R) {
+                        out = A::mac(out, ((const S *)I.val)[kk], vj);
+                    } else {
+                        const S hr = ((const S *)I.val)[2 * kk], hi = ((const S *)I.val)[2 * kk + 1];
+#pragma unroll
+                        for (int l = 0; l < W / 2; ++l) {
+                            S ar = out[2 * l], ai = out[2 * l + 1];
+                            A::cmac(ar, ai, hr, hi, vj[2 * l], vj[2 * l + 1]);
+                            out[2 * l] = ar;
+                            out[2 * l + 1] = ai;
+                        }
+                    }
+                }
+            }
+            if (n > 0) out = two_minus(out, y);
             nxt[e] = out;
-            acc.add(out, cur[e]);
+            a2.add(out, x);
+            return out;
+        };
+        if (alive) {
+            if constexpr (EPT == 0) {
+                for (uint32_t e = tid; e < ne; e += tpb) {
+                    place(0, e);
+                    next(0, e, cur[e], nxt[e]);
+                }
+            } else {
+#pragma unroll
+                for (int u = 0; u < EPT; ++u) {
+                    const uint32_t e = tid + (uint32_t)u * tpb;
+                    if (e >= ne) continue;
+                    const T out = next(u, e, v[u], pv[u]);
+                    pv[u] = v[u];
+                    v[u] = out;
+                }
+            }
+            if (q & 1) wave_reduce_store<true>(held, a2, red[half][q - 1][w], red[half][q][w]);
+            else if (n + 1 < nz) held = a2;
+            else wave_reduce_store<true>(a2, red[half][q][w]);
         }
-        wave_reduce_store(acc,
-                                       I.partial + ((size_t)(n + 1) * SMALL_WAVES + w) * 4);
         // step n's LDS writes before step n + 1 reads them, and its reads before they are overwritten
         __syncthreads();
+        if (alive && (q == 3 || n + 1 == nz)) flush(n - q, q + 1, half);
     }
+    if (nz < I.K && alive)
+        for (uint32_t e = tid; e < ne; e += tpb) {
+            const uint32_t i = div_ng(e), at = i * C + cg0 + e - i * ng;
+            G::st((nz & 1) ? I.buf1 : I.buf0, at, lb(nz)[e]);
+            if (nz > 0) G::st((nz & 1) ? I.buf0 : I.buf1, at, lb(nz + 1)[e]);
+        }
 }
 
 // ---------------------------------------------------------------------------

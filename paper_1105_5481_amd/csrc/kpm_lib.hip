@@ -506,7 +506,9 @@ struct Plan {
     size_t esz;
     size_t part_bytes, dots_bytes, buf_bytes;
     uint32_t nbuf;    // vector buffers (2, or 4 with temporal blocking)
-    uint32_t tbg, tbw;   // 2D temporal blocking: chunk groups per site, chunks per group
+    uint32_t tbg, tbw;   // 2D temporal blocking, few sites: chunk groups per site, chunks per group
+    uint32_t tpb, ept;   // few sites: threads per group, chunks per thread
+    int whole;           // few sites: all steps in one launch, no vector buffers
     int32_t tbh;      // temporal blocking: x-tile halo = steps of the deepest pass (1 .. 6)
     uint64_t state;   // bytes the recursion touches per step (vectors + operator)
     uint32_t grid_cap;   // most blocks per launch (0: KPM_LAUNCH_MAX_BLOCKS)
@@ -652,6 +654,41 @@ void tb_plan(const kpm_ham *h, Plan &p)
     p.xcd = p.tiles >= XCD_MIN_ITEMS ? 3 : 0;
 }
 
+// Solves of few sites (k_solve_small): those whose whole vector blocks fit the LDS of one CU
+// run all their steps in one launch (`whole`; at most 16 groups, whose partials of every step
+// are kept), and beyond them those of at most SMALL_SITES sites, in launches of up to P_slots
+// steps with the state in the workspace between.  At 2048 sites a step takes about 1 us
+// against 3.5 to 5 us of a launch per step; with more sites per workgroup the launches
+// win (16^3 spin FP32 3.6 us per step).
+constexpr int64_t SMALL_SITES = 2048;
+constexpr size_t SMALL_WS = 16u << 20;   // most workspace of the second kind
+int32_t small_slots(const Plan &p)
+{
+    if (p.whole) return p.K + 1;
+    const int64_t fit = (4ll << 20) / ((int64_t)p.tiles * 32);
+    return (int32_t)std::min<int64_t>(p.K + 1, std::max<int64_t>(PSLOTS_MAX, std::min<int64_t>(fit, 512)));
+}
+bool small_plan(const kpm_ham *h, Plan &p, int32_t M)
+{
+    const size_t lim = small_lds_limit();
+    if (lim == 0) return false;
+    const uint64_t N = (uint64_t)h->N;
+    p.whole = 2ull * p.nel * 16 <= lim;
+    if (!p.whole && h->N > SMALL_SITES) return false;
+    uint32_t w = p.whole ? (p.C + 15) / 16 : 1;                          // chunks per group
+    w = std::min<uint32_t>(p.C, std::max<uint32_t>(w, (uint32_t)((64 + N - 1) / N)));   // a wave's worth at least
+    if (2ull * N * w * 16 > lim) return false;
+    p.tbw = w;
+    p.tbg = (p.C + w - 1) / w;
+    p.tiles = p.tbg;
+    p.tpb = (uint32_t)std::min<uint64_t>(SMALL_BLOCK, (N * w + 63) / 64 * 64);
+    p.ept = (uint32_t)((N * w + p.tpb - 1) / p.tpb);
+    p.K = M / 2;
+    if (p.tbg > 65535) return false;
+    if (!p.whole && 2 * (size_t)p.nel * 16 + (size_t)small_slots(p) * p.tiles * 32 > SMALL_WS) return false;
+    return true;
+}
+
 constexpr uint32_t RUN_PLANES = 4;   // planes a run of short segments covers
 
 bool make_plan(const kpm_ham *h, int32_t M, int32_t R, int32_t vec, Plan &p, bool allow_tb = true)
@@ -673,12 +710,9 @@ bool make_plan(const kpm_ham *h, int32_t M, int32_t R, int32_t vec, Plan &p, boo
     // byte offsets beyond 32 bits need the 64-bit addressing variant
     const uint64_t bond_bytes = (uint64_t)h->N * (h->dim ? h->dim : 1) * 2 * p.esz;
     p.wide = (nel * 16 >= (1ull << 32) || bond_bytes >= (1ull << 32)) ? 1 : 0;
-    const uint64_t small_bytes = 2ull * nel * 16;
     p.nbuf = 2;
-    if (g_small && small_bytes <= small_lds_limit()) {
+    if (g_small && small_plan(h, p, M)) {
         p.mode = MODE_SMALL;
-        p.tiles = SMALL_WAVES;   // per-wave dot partials
-        p.xcd = 0;
     } else if (allow_tb && g_tblock && g_march && (h->opk == OP_REAL2 || h->opk == OP_SPIN2) &&
                tb_halo(h->prec, h->opk, p.C / tb_groups(p.C, (uint32_t)h->L[0]),
                        tb_groups(p.C, (uint32_t)h->L[0]) > 1) >= 2 &&
@@ -749,10 +783,9 @@ bool make_plan(const kpm_ham *h, int32_t M, int32_t R, int32_t vec, Plan &p, boo
     p.dots_bytes = align256((size_t)(p.K + 1) * 4 * sizeof(double));
     p.buf_bytes = align256((size_t)h->N * p.Rs * p.esz);
     if (p.mode == MODE_SMALL) {
-        // one launch runs every step: a partial slot per step, reduced afterwards
-        p.P_slots = p.K + 1;
+        p.P_slots = small_slots(p);
         p.part_bytes = align256((size_t)p.P_slots * p.tiles * 4 * sizeof(double));
-        p.buf_bytes = 0;
+        if (p.whole) p.buf_bytes = 0;   // one launch runs every step
         p.nb = 1;
     }
     // r_{n+1} is read again as r_n by the next step: keep it cached when the
@@ -805,6 +838,7 @@ void fill_inst(const kpm_ham *h, const Plan &p, int32_t M, int32_t R, int32_t ve
     I.tbh = p.tbh;
     I.tbg = p.tbg ? p.tbg : 1;
     I.tbw = p.tbw ? p.tbw : p.C;
+    I.tpb = p.tpb;
     I.seed = seed;
     I.instance = instance;
     I.norm = (vec == KPM_VEC_UNIT) ? (double)R : (double)h->N * (double)R;
@@ -925,31 +959,65 @@ kpm_status launch_step(int prec, int opk, int mode, int wide, int nt, const Inst
     hipLaunchKernelGGL(get_step(prec, opk, mode, wide, nt), dim3(blocks), dim3(BLOCK), 0, st, tab, bmap, k);
     return check_launch();
 }
-typedef void (*small_fn)(const Inst *);
-template <typename S>
-small_fn small_for(int opk)
+typedef void (*small_fn)(const Inst *, int32_t, int32_t);
+template <typename S, int EPT>
+small_fn small_pick(int opk)
 {
     switch (opk) {
-    case OP_REAL2: return k_solve_small<S, OP_REAL2>;
-    case OP_REAL3: return k_solve_small<S, OP_REAL3>;
-    case OP_SPIN2: return k_solve_small<S, OP_SPIN2>;
-    case OP_SPIN3: return k_solve_small<S, OP_SPIN3>;
-    case OP_CSR_R: return k_solve_small<S, OP_CSR_R>;
-    default: return k_solve_small<S, OP_CSR_C>;
+    case OP_REAL2: return k_solve_small<S, OP_REAL2, EPT>;
+    case OP_REAL3: return k_solve_small<S, OP_REAL3, EPT>;
+    case OP_SPIN2: return k_solve_small<S, OP_SPIN2, EPT>;
+    case OP_SPIN3: return k_solve_small<S, OP_SPIN3, EPT>;
+    case OP_CSR_R: return k_solve_small<S, OP_CSR_R, EPT>;
+    default: return k_solve_small<S, OP_CSR_C, EPT>;
     }
 }
-// `count` small solves of one operator class, one workgroup each, with
-// `lds` bytes of dynamic LDS (the largest of the group).
-kpm_status launch_small(int prec, int opk, const Inst *tab, uint32_t count, size_t lds, hipStream_t st)
+template <typename S>
+small_fn small_for(int opk, uint32_t ept)
 {
-    small_fn f = prec == KPM_F64 ? small_for<double>(opk) : small_for<float>(opk);
+    if (ept <= SMALL_EPT) return ept <= 1 ? small_pick<S, 1>(opk) : small_pick<S, 2>(opk);
+    return small_pick<S, 0>(opk);
+}
+// What one launch of few-site solves takes: the largest of its instances' groups, threads,
+// chunks per thread and dynamic LDS.
+struct SmallShape {
+    uint32_t groups = 1, tpb = 64, ept = 1;
+    size_t lds = 0;
+    void add(const Plan &p, int64_t N) { add(p.tbg, p.tpb, p.ept, p.tbw, N); }
+    void add(uint32_t g, uint32_t t, uint32_t e, uint32_t w, int64_t N)
+    {
+        groups = std::max(groups, g);
+        tpb = std::max(tpb, t);
+        ept = std::max(ept, e);
+        lds = std::max(lds, 2 * (size_t)N * w * 16);
+    }
+};
+SmallShape small_shape(const Inst &I)
+{
+    SmallShape sh;
+    sh.add(I.tbg, I.tpb, (I.N * I.tbw + I.tpb - 1) / I.tpb, I.tbw, I.N);
+    return sh;
+}
+kpm_status allow_small_lds(small_fn f)
+{
+    return hipFuncSetAttribute((const void *)f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)small_lds_limit()) ==
+                   hipSuccess
+               ? KPM_OK
+               : KPM_ERR_DEVICE;
+}
+small_fn get_small(int prec, int opk, uint32_t ept)
+{
+    return prec == KPM_F64 ? small_for<double>(opk, ept) : small_for<float>(opk, ept);
+}
+// Steps n0 .. n1 - 1 (n0 < 0: r_0 first) of `count` few-site solves of one operator class.
+kpm_status launch_small(int prec, int opk, const SmallShape &sh, const Inst *tab, uint32_t count, int32_t n0, int32_t n1,
+                        hipStream_t st)
+{
+    small_fn f = get_small(prec, opk, sh.ept);
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &cs) != hipSuccess) return KPM_ERR_DEVICE;
-    if (cs == hipStreamCaptureStatusNone &&
-        hipFuncSetAttribute((const void *)f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)small_lds_limit()) !=
-            hipSuccess)
-        return KPM_ERR_DEVICE;
-    hipLaunchKernelGGL(f, dim3(count), dim3(SMALL_BLOCK), lds, st, tab);
+    if (cs == hipStreamCaptureStatusNone && allow_small_lds(f) != KPM_OK) return KPM_ERR_DEVICE;
+    hipLaunchKernelGGL(f, dim3(count, sh.groups), dim3(sh.tpb), sh.lds, st, tab, n0, n1);
     return check_launch();
 }
 
@@ -1244,10 +1312,10 @@ kpm_status kpm_solve_begin(kpm_ham *h, int32_t M, int32_t R, int32_t vec, uint64
     kpm_status e = upload(s->tab_dev, &s->inst, sizeof(Inst), st);
     s->wide = p.wide;
     if (p.mode == MODE_SMALL) {
-        // the whole recursion runs now; its partials are reduced by finish
-        if (e == KPM_OK) e = launch_small(h->prec, h->opk, s->tab_dev, 1, 2 * (size_t)p.nel * 16, st);
-        s->next = p.K;
-        s->written = p.K + 1;
+        // the whole recursion runs now (its partials are reduced by finish), or r_0 alone
+        s->next = p.whole ? p.K : 0;
+        if (e == KPM_OK) e = launch_small(h->prec, h->opk, small_shape(s->inst), s->tab_dev, 1, -1, s->next, st);
+        s->written = s->next + 1;
         s->reduced = 0;
         if (e != KPM_OK) {
             delete s;
@@ -1335,6 +1403,20 @@ kpm_status kpm_solve_advance(kpm_solve *s, int32_t max_steps, void *stream, int3
     hipStream_t st = S(stream);
     const Inst &I = s->inst;
     kpm_status e = KPM_OK;
+    if (I.mode == MODE_SMALL) {
+        // as many steps per launch as the ring of partials has room for
+        for (int32_t left = std::min(max_steps, I.K - s->next); left > 0 && e == KPM_OK;) {
+            if (s->written - s->reduced >= I.pslots) e = solve_reduce_pending(s, st);
+            const int32_t adv = std::min(left, I.pslots - (s->written - s->reduced));
+            if (e == KPM_OK)
+                e = launch_small(s->h->prec, I.opk, small_shape(I), s->tab_dev, 1, s->next, s->next + adv, st);
+            s->next += adv;
+            s->written += adv;
+            left -= adv;
+        }
+        if (remaining) *remaining = I.K - s->next;
+        return e;
+    }
     if (I.mode == MODE_TB || I.mode == MODE_TB3) {
         // passes of tbh steps (the tiles' halo); a shorter one for the remainder or a
         // smaller budget
@@ -1632,7 +1714,7 @@ struct BatchGroup {
     uint32_t first, count;   // table range
     uint32_t blocks;         // grid size
     size_t map_off;          // offset into the block map (words)
-    size_t lds;              // single-workgroup solves: dynamic LDS bytes
+    SmallShape small;        // few-site solves
     uint32_t pfirst, pcount; // march groups: range of the table of pieces (place_even)
 };
 // Instances whose recursions run together, step by step, before the next wave
@@ -1654,6 +1736,13 @@ struct BatchLayout {
     int prec;
 };
 
+// Kernel class of an instance; few-site solves that keep their state between launches
+// apart from those that run in one.
+int group_key(const kpm_ham *h, const Plan &p)
+{
+    return 2 * kernel_key(h->opk, p.mode, p.wide, p.nt) + (p.mode == MODE_SMALL && !p.whole ? 1 : 0);
+}
+
 // Appends the groups of instances `ids` (one per kernel class, in order of
 // first appearance) to `groups`, their instances to L.order, and sizes their
 // block maps.
@@ -1661,20 +1750,20 @@ void add_groups(kpm_ham *const *h, const std::vector<int> &ids, BatchLayout &L, 
 {
     std::vector<int> keys;
     for (int i : ids) {
-        const int key = kernel_key(h[i]->opk, L.plans[i].mode, L.plans[i].wide, L.plans[i].nt);
+        const int key = group_key(h[i], L.plans[i]);
         if (std::find(keys.begin(), keys.end(), key) == keys.end()) keys.push_back(key);
     }
     for (int key : keys) {
-        BatchGroup g{0, 0, 0, 0, (uint32_t)L.order.size(), 0, 0, L.map_words, 0, L.pieces, 0};
+        BatchGroup g{0, 0, 0, 0, (uint32_t)L.order.size(), 0, 0, L.map_words, {}, L.pieces, 0};
         std::vector<Inst> ins;
         for (int i : ids) {
             const Plan &p = L.plans[i];
-            if (kernel_key(h[i]->opk, p.mode, p.wide, p.nt) != key) continue;
+            if (group_key(h[i], p) != key) continue;
             g.opk = h[i]->opk;
             g.mode = p.mode;
             g.wide = p.wide;
             g.nt = p.nt;
-            g.lds = std::max(g.lds, 2 * (size_t)p.nel * 16);
+            if (p.mode == MODE_SMALL) g.small.add(p, h[i]->N);
             Inst I;
             std::memset(&I, 0, sizeof(I));
             I.nb = p.nb;
@@ -1831,10 +1920,20 @@ kpm_status kpm_moments_batched(kpm_ham *const *h, int32_t count, const int32_t *
     }
     auto table = [&](const BatchGroup &g) { return g.mode == MODE_MARCH ? piece_dev + g.pfirst : tab_dev + g.first; };
     for (const BatchGroup &g : L.small) {
-        int32_t kmax = 0;
-        for (uint32_t t = g.first; t < g.first + g.count; ++t) kmax = std::max(kmax, L.plans[L.order[t]].K);
-        if (e == KPM_OK) e = launch_small(L.prec, g.opk, tab_dev + g.first, g.count, g.lds, st);
-        if (e == KPM_OK) e = launch_reduce(tab_dev + g.first, (int32_t)g.count, -1, kmax + 1, st);
+        int32_t kmax = 0, slots = INT32_MAX;   // steps of the group, steps its rings of partials hold
+        for (uint32_t t = g.first; t < g.first + g.count; ++t) {
+            const Plan &p = L.plans[L.order[t]];
+            kmax = std::max(kmax, p.K);
+            if (!p.whole && p.P_slots <= p.K) slots = std::min(slots, p.P_slots);
+        }
+        for (int32_t n = -1; n < kmax && e == KPM_OK;) {
+            // the first launch leaves one partial more, that of <r_0|r_0>
+            const int32_t to = (int32_t)std::min<int64_t>(kmax, (int64_t)n + slots);
+            e = launch_small(L.prec, g.opk, g.small, tab_dev + g.first, g.count, n, to, st);
+            if (e == KPM_OK) e = launch_reduce(tab_dev + g.first, (int32_t)g.count, n, to - n, st);
+            n = to;
+            if (kmax == 0) break;
+        }
     }
     for (const BatchWave &w : L.waves) {
         for (const BatchGroup &g : w.groups)
@@ -1948,7 +2047,7 @@ kpm_status kpm_batch_advance(kpm_batch *b, int32_t steps, void *stream)
     // member's pending reduction range
     std::vector<kpm_solve *> act;
     for (kpm_solve *s : b->members)
-        if (s->inst.mode != MODE_SMALL && (s->next < s->inst.K || s->written > s->reduced)) act.push_back(s);
+        if (s->next < s->inst.K || (s->inst.mode != MODE_SMALL && s->written > s->reduced)) act.push_back(s);
     if (act.empty() || steps == 0) return KPM_OK;
     // the members of one launch share the caches
     uint64_t state = 0;
@@ -1974,11 +2073,12 @@ kpm_status kpm_batch_advance(kpm_batch *b, int32_t steps, void *stream)
         size_t map_off;
         int tbh, maxfull;   // blocked groups: depth of the full passes, most full passes of a member
         uint32_t rems;      // blocked groups: bit r set if a member ends the chunk with a pass of depth r
+        SmallShape small;   // few-site solves
     };
     std::vector<Group> groups;
     int32_t max_red = 0;
     for (int key : keys) {
-        Group g{0, 0, 0, 0, (uint32_t)tab.size(), 0, 0, map.size(), 0, 0, 0u};
+        Group g{0, 0, 0, 0, (uint32_t)tab.size(), 0, 0, map.size(), 0, 0, 0u, {}};
         std::vector<Inst> ins;
         for (kpm_solve *s : act) {
             if (key_of(s) != key) continue;
@@ -1998,6 +2098,8 @@ kpm_status kpm_batch_advance(kpm_batch *b, int32_t steps, void *stream)
                 g.maxfull = std::max(g.maxfull, I.tbfull);
                 if (I.tbrem) g.rems |= 1u << I.tbrem;
             }
+            if (I.mode == MODE_SMALL)
+                g.small.add(I.tbg, I.tpb, (I.N * I.tbw + I.tpb - 1) / I.tpb, I.tbw, I.N);
             g.opk = I.opk;
             g.mode = I.mode;
             g.wide = s->wide;
@@ -2006,7 +2108,7 @@ kpm_status kpm_batch_advance(kpm_batch *b, int32_t steps, void *stream)
         }
         g.count = (uint32_t)ins.size();
         set_runs(ins);
-        g.blocks = place_blocks(ins, map);
+        if (g.mode != MODE_SMALL) g.blocks = place_blocks(ins, map);
         tab.insert(tab.end(), ins.begin(), ins.end());
         groups.push_back(g);
     }
@@ -2025,7 +2127,9 @@ kpm_status kpm_batch_advance(kpm_batch *b, int32_t steps, void *stream)
     for (int32_t k = 0; k < steps && e == KPM_OK; ++k)
         for (const Group &g : groups) {
             if (e != KPM_OK) break;
-            if (g.mode != MODE_TB && g.mode != MODE_TB3)
+            if (g.mode == MODE_SMALL) {   // all of the chunk's steps at once
+                if (k == 0) e = launch_small(prec, g.opk, g.small, tab_dev + g.first, g.count, 0, steps, st);
+            } else if (g.mode != MODE_TB && g.mode != MODE_TB3)
                 e = launch_step(prec, g.opk, g.mode, g.wide, g.nt, tab_dev + g.first, map_dev + g.map_off, g.blocks, k,
                                 st);
             else if (k % g.tbh == 0 && k / g.tbh < g.maxfull)
@@ -2070,10 +2174,9 @@ kpm_status kpm_graph_capture_batched(kpm_ham *const *h, int32_t count, const int
     for (int i = 0; i < count; ++i) {
         Plan p;
         if (h && h[i] && M && R && make_plan(h[i], M[i], R[i], vec, p, false) && p.mode == MODE_SMALL) {
-            small_fn f = h[i]->prec == KPM_F64 ? small_for<double>(h[i]->opk) : small_for<float>(h[i]->opk);
-            if (hipFuncSetAttribute((const void *)f, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    (int)small_lds_limit()) != hipSuccess)
-                return KPM_ERR_DEVICE;
+            // the launch takes the most chunks per thread of its group
+            for (uint32_t ept : {1u, SMALL_EPT, SMALL_EPT + 1})
+                if (allow_small_lds(get_small(h[i]->prec, h[i]->opk, ept)) != KPM_OK) return KPM_ERR_DEVICE;
         }
     }
     if (hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal) != hipSuccess) return KPM_ERR_DEVICE;

@@ -218,7 +218,7 @@ __global__ __launch_bounds__(TB3_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) 
                     hr[5] = bzp[0]; hi[5] = bzp[1];
                     out = apply_cplx<S, NS>(hd, d0[u], r0[u], nb, hr, hi);
                 }
-                if (!first) out = (S)2 * out - pv[u];
+                if (!first) out = two_minus(out, pv[u]);
                 v1[u] = out;
                 if (E.own && own_z1) {
                     G::template st_s<NT>(D == 2 ? outa : outb, cb + i, out);
@@ -262,7 +262,7 @@ __global__ __launch_bounds__(TB3_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) 
                             hr[5] = bzp[0]; hi[5] = bzp[1];
                             out = apply_cplx<S, NS>(hd, dm[u], vb[u], nb, hr, hi);
                         }
-                        out = (S)2 * out - rm[u];
+                        out = two_minus(out, rm[u]);
                         G::template st_s<NT>(outb, cb + i, out);
                         acc2.add(out, vb[u]);
                     }
