@@ -263,13 +263,10 @@ template <> struct Dots<float> {
 // FP64 sums of any magnitude (vectors that are not near 1): ten operations per product.
 struct DotsWide {
     double s0 = 0.0, c0 = 0.0, s1 = 0.0, c1 = 0.0;
-    __device__ __forceinline__ void add(V16<double>::T o, V16<double>::T v)
+    __device__ __forceinline__ void dot(V16<double>::T o, V16<double>::T v)
     {
 #pragma unroll
-        for (int l = 0; l < 2; ++l) {
-            dot2_acc(s0, c0, o[l], o[l]);
-            dot2_acc(s1, c1, o[l], v[l]);
-        }
+        for (int l = 0; l < 2; ++l) dot2_acc(s1, c1, o[l], v[l]);
     }
     __device__ __forceinline__ void norm_only(V16<double>::T o)
     {
@@ -847,9 +844,10 @@ __global__ __launch_bounds__(BLOCK) void k_step_march(const Inst *__restrict__ t
 // ---------------------------------------------------------------------------
 // the fused recursion step, flat form (CSR; lattices on request)
 // ---------------------------------------------------------------------------
-template <typename S, int OPK, bool WIDE, typename A_>
-__device__ __forceinline__ void flat_elem(const Inst &I, uint32_t e, const void *cur, void *nxt, bool first, S hop,
-                                          A_ &acc)
+// H~ r on chunk e, r read through ld(chunk index); v receives the chunk itself.
+template <typename S, int OPK, bool WIDE, typename LD>
+__device__ __forceinline__ typename V16<S>::T flat_apply(const Inst &I, uint32_t e, S hop, const LD &ld,
+                                                         typename V16<S>::T &v)
 {
     typedef typename V16<S>::T T;
     typedef Mem<S, WIDE> G;
@@ -859,7 +857,7 @@ __device__ __forceinline__ void flat_elem(const Inst &I, uint32_t e, const void 
     const uint32_t C = I.C;
     const uint32_t i = fdiv(e, I.fC);
     const uint32_t c = e - i * C;
-    const T v = G::ld(cur, e);
+    v = ld(e);
     T out;
     if constexpr (OPK <= OP_SPIN3) {
         constexpr bool D3 = (OPK == OP_REAL3 || OPK == OP_SPIN3);
@@ -886,7 +884,7 @@ __device__ __forceinline__ void flat_elem(const Inst &I, uint32_t e, const void 
         }
         T nb[NS];
 #pragma unroll
-        for (int s = 0; s < NS; ++s) nb[s] = G::ld(cur, nbi[s] * C + c);
+        for (int s = 0; s < NS; ++s) nb[s] = ld(nbi[s] * C + c);
         const bool hd = I.has_diag;
         const S d = hd ? G::lds(I.diag, i) : (S)0;
         if (!SPIN) {
@@ -912,7 +910,7 @@ __device__ __forceinline__ void flat_elem(const Inst &I, uint32_t e, const void 
         for (int64_t kk = kb; kk < ke; ++kk) {
             const uint32_t jj = (uint32_t)I.col[kk];
             if (jj == i) continue;
-            const T vj = G::ld(cur, jj * C + c);
+            const T vj = ld(jj * C + c);
             if constexpr (OPK == OP_CSR_R) {
                 a = A::mac(a, ((const S *)I.val)[kk], vj);
             } else {
@@ -928,12 +926,7 @@ __device__ __forceinline__ void flat_elem(const Inst &I, uint32_t e, const void 
         }
         out = a;
     }
-    if (!first) {
-        const T p = G::ld_nt(nxt, e);
-        out = two_minus(out, p);
-    }
-    G::st_nt(nxt, e, out);
-    acc.add(out, v);
+    return out;
 }
 
 template <typename S, int OPK, bool WIDE>
@@ -957,7 +950,13 @@ __global__ __launch_bounds__(BLOCK) void k_step_flat(const Inst *__restrict__ ta
         Dots<S> acc;
         for (int u = 0; u < I.tpt; ++u) {
             const uint32_t e = t * (uint32_t)(BLOCK * I.tpt) + (uint32_t)(u * BLOCK) + threadIdx.x;
-            if (e < I.nel) flat_elem<S, OPK, WIDE>(I, e, cur, nxt, first, hop, acc);
+            if (e < I.nel) {
+                typename V16<S>::T v;
+                auto out = flat_apply<S, OPK, WIDE>(I, e, hop, [&](uint32_t q) { return Mem<S, WIDE>::ld(cur, q); }, v);
+                if (!first) out = two_minus(out, Mem<S, WIDE>::ld_nt(nxt, e));
+                Mem<S, WIDE>::st_nt(nxt, e, out);
+                acc.add(out, v);
+            }
         }
         block_reduce_store(acc, part + (size_t)t * 4);
     }

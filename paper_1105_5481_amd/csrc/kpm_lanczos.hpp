@@ -13,10 +13,16 @@
 //     u = H~ v_j,  alpha_j = Re <v_j|u>,
 //     w = (u - alpha_j v_j) - beta_{j-1} v_{j-1}   (last term absent for j = 0),
 //     beta_j = ||w||,  v_{j+1} = w / beta_j        (0 if beta_j = 0)
+// Two launches per step: the vectors are kept as w_j and divided by their norm where
+// they are read, and each kernel sums the partial dots of the one before it itself, every
+// block all of them (at most LZ_BLOCKS) in the same order.  A step is a handful of
+// launches' latency: with the sums and the division in launches of their own it took
+// 27 us at 64^3 sites (five launches), the tridiagonal solve on one thread 870 us; the
+// whole interval with k = 100 went from 3.6 to 1.8 ms (20^3: 32 to 13 us per step).
 // The scalars stay on the device, in the instance's dots array, as
 // double-double sums (each used as its rounded high part):
 //   index 0       <xi|xi>
-//   index 2j + 1  (||u||^2, Re<u|v_j>)   alpha_j = the second sum
+//   index 2j + 1  (0, Re<u|v_j>)         alpha_j = the second sum
 //   index 2j + 2  (||w||^2, 0)           beta_j = sqrt(the first sum)
 #pragma once
 
@@ -25,77 +31,113 @@ namespace kpm {
 constexpr int LZ_KMAX = 512;       // Lanczos steps per call (LDS of the tridiagonal solve)
 constexpr double LZ_BREAKDOWN = 1e-12;
 
-// u = H~ v_j and the partial sums of ||u||^2 and Re<u|v_j> (dots index idx).
+constexpr uint32_t LZ_BLOCKS = 2048;   // most blocks (= partial dots) per launch
+
+// Chunks [base, end) of the block's XCD (block b runs on XCD b mod 8) and its first one and
+// stride: neighbouring rows and planes of a large lattice meet in one L2.
+struct LzRange {
+    uint32_t first, stride, end;
+};
+__device__ __forceinline__ LzRange lz_range(uint32_t nel)
+{
+    if (gridDim.x % 8) return LzRange{blockIdx.x * BLOCK + threadIdx.x, gridDim.x * BLOCK, nel};
+    const uint32_t x = blockIdx.x & 7u, base = (uint32_t)(((uint64_t)nel * x) >> 3);
+    return LzRange{base + (blockIdx.x >> 3) * BLOCK + threadIdx.x, (gridDim.x >> 3) * BLOCK,
+                   (uint32_t)(((uint64_t)nel * (x + 1)) >> 3)};
+}
+
+// The sum of the blocks' partials `part` ([blocks][2]), the same in every thread.
+__device__ __forceinline__ double lz_total(const double *part, uint32_t blocks, double &lo)
+{
+    __shared__ double sum[4];
+    double a = 0.0, b = 0.0;
+    for (uint32_t t = threadIdx.x; t < blocks; t += BLOCK) {
+        const dd s = dd_sum(dd{a, b}, dd{part[2 * t], part[2 * t + 1]});
+        a = s.hi;
+        b = s.lo;
+    }
+    block_reduce_store<true>(a, b, 0.0, 0.0, sum);
+    const dd s = dd_fast_two_sum(sum[0], sum[1]);
+    lo = s.lo;
+    return s.hi;
+}
+// y / ||w||, or 0
+__device__ __forceinline__ V16<double>::T lz_unit(V16<double>::T y, double nrm)
+{
+#pragma unroll
+    for (int l = 0; l < 2; ++l) y[l] = nrm > 0.0 ? y[l] / nrm : 0.0;
+    return y;
+}
+
+// u = H~ v_j, v_j = w / ||w||, and the partials of Re<u|v_j> in pout.  ||w||^2 is the sum of
+// `pin` (j > 0; block 0 leaves it at dots index 2j) or dots index 0.
 template <int OPK, bool WIDE>
-__global__ __launch_bounds__(BLOCK) void k_lz_matvec(const Inst *__restrict__ tab, const void *v, void *u,
-                                                     int32_t idx)
+__global__ __launch_bounds__(BLOCK) void k_lz_matvec(const Inst *__restrict__ tab, const void *w, void *u, int32_t j,
+                                                     const double *pin, double *pout)
 {
+    typedef Mem<double, WIDE> G;
+    typedef V16<double>::T T;
     const Inst I = tab[0];
+    double n2 = I.dots[0], lo = 0.0;
+    if (j > 0) {
+        n2 = lz_total(pin, gridDim.x, lo);
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            I.dots[(size_t)(2 * j) * 4 + 0] = n2;
+            I.dots[(size_t)(2 * j) * 4 + 1] = lo;
+        }
+    }
+    const double nrm = sqrt(n2);
     double hop = 0.0;
-    if (OPK == OP_REAL2 || OPK == OP_REAL3) hop = Mem<double, WIDE>::lds(I.hop, 0);
-    double *part = I.partial + (size_t)(idx % I.pslots) * I.tiles * 4;
-    const ItemRange ir = item_range(I, I.tiles, 1);
-    for (uint32_t it = ir.first; it < ir.count; it += ir.stride) {
-        const uint32_t t = ir.ub + it;
-        DotsWide acc;
-        for (int q = 0; q < I.tpt; ++q) {
-            const uint32_t e = t * (uint32_t)(BLOCK * I.tpt) + (uint32_t)(q * BLOCK) + threadIdx.x;
-            if (e < I.nel) flat_elem<double, OPK, WIDE>(I, e, v, u, true, hop, acc);
-        }
-        block_reduce_store(acc, part + (size_t)t * 4);
+    if (OPK == OP_REAL2 || OPK == OP_REAL3) hop = G::lds(I.hop, 0);
+    DotsWide acc;
+    const LzRange r = lz_range(I.nel);
+    for (uint32_t e = r.first; e < r.end; e += r.stride) {
+        T v;
+        const T out = flat_apply<double, OPK, WIDE>(I, e, hop, [&](uint32_t q) { return lz_unit(G::ld(w, q), nrm); }, v);
+        G::st(u, e, out);
+        acc.dot(out, v);
     }
+    __shared__ double sum[4];
+    block_reduce_store(acc, sum);
+    if (threadIdx.x < 2) pout[2 * blockIdx.x + threadIdx.x] = sum[2 + threadIdx.x];
 }
 
-// w = (u - alpha_j v_j) - beta_{j-1} v_{j-1}, written over v_{j-1}, and the
-// partial sums of ||w||^2 (dots index 2j + 2).
+// w_{j+1} = (u - alpha_j v_j) - beta_{j-1} v_{j-1}, written over w_{j-1} (wp), and the partials
+// of its squared norm in pout; alpha_j is the sum of pin (block 0 leaves it at dots index
+// 2j + 1).
 template <bool WIDE>
-__global__ __launch_bounds__(BLOCK) void k_lz_update(const Inst *__restrict__ tab, const void *u, const void *v,
-                                                     void *vp, int32_t j)
+__global__ __launch_bounds__(BLOCK) void k_lz_update(const Inst *__restrict__ tab, const void *u, const void *w,
+                                                     void *wp, int32_t j, const double *pin, double *pout)
 {
     typedef Mem<double, WIDE> G;
     typedef V16<double>::T T;
     const Inst I = tab[0];
-    const double al = I.dots[(size_t)(2 * j + 1) * 4 + 2];
-    const double be = j > 0 ? sqrt(I.dots[(size_t)(2 * j) * 4 + 0]) : 0.0;
-    double *part = I.partial + (size_t)((2 * j + 2) % I.pslots) * I.tiles * 4;
-    const ItemRange ir = item_range(I, I.tiles, 1);
-    for (uint32_t it = ir.first; it < ir.count; it += ir.stride) {
-        const uint32_t t = ir.ub + it;
-        DotsWide acc;
-        for (int q = 0; q < I.tpt; ++q) {
-            const uint32_t e = t * (uint32_t)(BLOCK * I.tpt) + (uint32_t)(q * BLOCK) + threadIdx.x;
-            if (e < I.nel) {
-                const T uu = G::ld(u, e), vv = G::ld(v, e);
-                T w;
+    double lo;
+    const double al = lz_total(pin, gridDim.x, lo);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        I.dots[(size_t)(2 * j + 1) * 4 + 2] = al;
+        I.dots[(size_t)(2 * j + 1) * 4 + 3] = lo;
+    }
+    const double nrm = sqrt(I.dots[(size_t)(2 * j) * 4 + 0]);                      // of w_j: beta_{j-1} for j > 0
+    const double nrp = j > 0 ? sqrt(I.dots[(size_t)(2 * j - 2) * 4 + 0]) : 0.0;    // of w_{j-1}
+    DotsWide acc;
+    const LzRange r = lz_range(I.nel);
+    for (uint32_t e = r.first; e < r.end; e += r.stride) {
+        const T uu = G::ld(u, e), vv = lz_unit(G::ld(w, e), nrm);
+        T x;
 #pragma unroll
-                for (int l = 0; l < 2; ++l) w[l] = uu[l] - al * vv[l];
-                if (j > 0) {
-                    const T pp = G::ld(vp, e);
+        for (int l = 0; l < 2; ++l) x[l] = uu[l] - al * vv[l];
+        if (j > 0) {
+            const T pp = lz_unit(G::ld(wp, e), nrp);
 #pragma unroll
-                    for (int l = 0; l < 2; ++l) w[l] = w[l] - be * pp[l];
-                }
-                G::st(vp, e, w);
-                acc.norm_only(w);
-            }
+            for (int l = 0; l < 2; ++l) x[l] = x[l] - nrm * pp[l];
         }
-        block_reduce_store(acc, part + (size_t)t * 4);
+        G::st(wp, e, x);
+        acc.norm_only(x);
     }
-}
-
-// x = x / sqrt(first sum of dots index idx) (x = 0 if that sum is 0).
-template <bool WIDE>
-__global__ __launch_bounds__(BLOCK) void k_lz_scale(const Inst *__restrict__ tab, void *x, int32_t idx)
-{
-    typedef Mem<double, WIDE> G;
-    typedef V16<double>::T T;
-    const Inst I = tab[0];
-    const double nrm = sqrt(I.dots[(size_t)idx * 4 + 0]);
-    for (uint32_t e = blockIdx.x * BLOCK + threadIdx.x; e < I.nel; e += gridDim.x * BLOCK) {
-        T y = G::ld(x, e);
-#pragma unroll
-        for (int l = 0; l < 2; ++l) y[l] = nrm > 0.0 ? y[l] / nrm : 0.0;
-        G::st(x, e, y);
-    }
+    __shared__ double sum[4];
+    block_reduce_store(acc, sum);
+    if (threadIdx.x < 2) pout[2 * blockIdx.x + threadIdx.x] = sum[threadIdx.x];
 }
 
 // ---------------------------------------------------------------------------
@@ -117,10 +159,28 @@ __device__ inline int lz_count_below(const double *al, const double *b2, int m, 
     return c;
 }
 
-// Eigenvalue number `which` (0 = smallest) of T by bisection on the count.
-__device__ inline double lz_bisect(const double *al, const double *b2, int m, int which, double lo, double hi,
-                                   double pivmin)
+// Eigenvalue number `which` (0 = smallest) of T: the adjacent doubles between which the
+// count passes it, found by LZ_SECTIONS lanes counting at as many points of the interval
+// at once (seven rounds for 49 bits), the last few by bisection.  All lanes of the group
+// (`lane` < LZ_SECTIONS, one group of waves per eigenvalue) call it; `below`: LDS of the group.
+constexpr int LZ_SECTIONS = 128;
+__device__ inline double lz_section(const double *al, const double *b2, int m, int which, double lo, double hi,
+                                    double pivmin, int lane, int *below)
 {
+    for (int round = 0; round < 7; ++round) {
+        const double h = (hi - lo) / (double)(LZ_SECTIONS + 1);
+        const double x = fmin(fmax(lo + h * (double)(lane + 1), lo), hi);
+        below[lane] = lz_count_below(al, b2, m, x, pivmin) >= which + 1 ? 1 : 0;
+        __syncthreads();
+        int first = LZ_SECTIONS;   // the first point at or above the eigenvalue
+        for (int t = LZ_SECTIONS - 1; t >= 0; --t)
+            if (below[t]) first = t;
+        const double nlo = first > 0 ? fmin(fmax(lo + h * (double)first, lo), hi) : lo;
+        const double nhi = first < LZ_SECTIONS ? fmin(fmax(lo + h * (double)(first + 1), lo), hi) : hi;
+        lo = nlo;
+        hi = nhi;
+        __syncthreads();
+    }
     for (int it = 0; it < 256; ++it) {
         const double mid = 0.5 * (lo + hi);
         if (mid <= lo || mid >= hi) break;   // adjacent doubles
@@ -206,22 +266,28 @@ __device__ inline double lz_last_component(const double *al, const double *be, i
 // out[4..5]  r_min, r_max (residual bounds, units of H~)
 // out[6]     m, the number of Lanczos steps used (a breakdown stops early)
 // out[8 + j], out[8 + k + j]  alpha_j, beta_j for j < k
-__global__ __launch_bounds__(64) void k_lz_tridiag(const Inst *__restrict__ tab, int32_t k, double pad, double a,
-                                                   double b, double clamp_lo, double clamp_hi, double *out)
+// The lower and the upper half of the block work on the two ends of the spectrum.
+__global__ __launch_bounds__(2 * LZ_SECTIONS) void k_lz_tridiag(const Inst *__restrict__ tab, int32_t k, double pad,
+                                                                double a, double b, double clamp_lo, double clamp_hi,
+                                                                const double *pin, uint32_t blocks, double *out)
 {
     __shared__ double al[LZ_KMAX], be[LZ_KMAX], b2[LZ_KMAX];
-    __shared__ double d[LZ_KMAX], dl[LZ_KMAX], du[LZ_KMAX], du2[LZ_KMAX], x[LZ_KMAX];
-    __shared__ unsigned char piv[LZ_KMAX];
+    __shared__ double d[2][LZ_KMAX], dl[2][LZ_KMAX], du[2][LZ_KMAX], du2[2][LZ_KMAX], x[2][LZ_KMAX];
+    __shared__ unsigned char piv[2][LZ_KMAX];
+    __shared__ int below[2][LZ_SECTIONS];
+    __shared__ double th[2], res[2];
     const Inst I = tab[0];
+    double lo;
+    const double last = lz_total(pin, blocks, lo);   // ||w_k||^2
     for (int j = threadIdx.x; j < k; j += blockDim.x) {
         al[j] = I.dots[(size_t)(2 * j + 1) * 4 + 2];
-        be[j] = sqrt(I.dots[(size_t)(2 * j + 2) * 4 + 0]);
+        be[j] = sqrt(j + 1 < k ? I.dots[(size_t)(2 * j + 2) * 4 + 0] : last);
         b2[j] = be[j] * be[j];
         out[8 + j] = al[j];
         out[8 + k + j] = be[j];
     }
     __syncthreads();
-    if (threadIdx.x != 0) return;
+    const int side = threadIdx.x / LZ_SECTIONS, lane = threadIdx.x % LZ_SECTIONS;
     int m = k;
     bool stop = false;
     double scale = 0.0;
@@ -245,23 +311,25 @@ __global__ __launch_bounds__(64) void k_lz_tridiag(const Inst *__restrict__ tab,
     const double margin = 4.440892098500626e-16 * (tnorm > 0.0 ? tnorm : 1.0) + pivmin;
     glo -= margin;
     ghi += margin;
-    const double th_lo = lz_bisect(al, b2, m, 0, glo, ghi, pivmin);
-    const double th_hi = lz_bisect(al, b2, m, m - 1, glo, ghi, pivmin);
+    const double theta = lz_section(al, b2, m, side ? m - 1 : 0, glo, ghi, pivmin, lane, below[side]);
     const double blast = stop ? 0.0 : be[m - 1];
-    double r_lo = 0.0, r_hi = 0.0;
-    if (blast > 0.0) {
-        r_lo = blast * lz_last_component(al, be, m, th_lo, tnorm, d, dl, du, du2, piv, x);
-        r_hi = blast * lz_last_component(al, be, m, th_hi, tnorm, d, dl, du, du2, piv, x);
+    if (lane == 0) {
+        th[side] = theta;
+        res[side] = blast > 0.0 ? blast * lz_last_component(al, be, m, theta, tnorm, d[side], dl[side], du[side],
+                                                            du2[side], piv[side], x[side])
+                                : 0.0;
     }
-    const double width = th_hi - th_lo;
-    const double lo = th_lo - fmax(r_lo, pad * width);
-    const double hi = th_hi + fmax(r_hi, pad * width);
-    out[0] = fmax(a * lo + b, clamp_lo);
-    out[1] = fmin(a * hi + b, clamp_hi);
-    out[2] = th_lo;
-    out[3] = th_hi;
-    out[4] = r_lo;
-    out[5] = r_hi;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    const double width = th[1] - th[0];
+    const double e_lo = th[0] - fmax(res[0], pad * width);
+    const double e_hi = th[1] + fmax(res[1], pad * width);
+    out[0] = fmax(a * e_lo + b, clamp_lo);
+    out[1] = fmin(a * e_hi + b, clamp_hi);
+    out[2] = th[0];
+    out[3] = th[1];
+    out[4] = res[0];
+    out[5] = res[1];
     out[6] = (double)m;
     out[7] = 0.0;
 }

@@ -2224,7 +2224,7 @@ void kpm_graph_free(kpm_graph *g)
 // ---------------------------------------------------------------------------
 extern "C++" {
 namespace {
-typedef void (*lz_matvec_fn)(const Inst *, const void *, void *, int32_t);
+typedef void (*lz_matvec_fn)(const Inst *, const void *, void *, int32_t, const double *, double *);
 template <bool WIDE>
 lz_matvec_fn lz_matvec_for(int opk)
 {
@@ -2251,7 +2251,8 @@ bool lanczos_plan(const kpm_ham *h, int32_t k, Plan &p, int32_t &vec)
     p.nb = std::min<uint32_t>((p.tiles + 7) / 8 * 8, (uint32_t)g_max_blocks);
     p.K = 2 * k + 2;
     p.P_slots = 2;
-    p.part_bytes = align256((size_t)p.P_slots * p.tiles * 4 * sizeof(double));
+    // the start vector's partials, and later two sets of a launch's
+    p.part_bytes = align256(std::max<size_t>((size_t)p.P_slots * p.tiles * 4, 4 * LZ_BLOCKS) * sizeof(double));
     p.dots_bytes = align256((size_t)(p.K + 1) * 4 * sizeof(double));
     p.buf_bytes = align256((size_t)h->N * p.Rs * p.esz);
     return true;
@@ -2289,34 +2290,27 @@ kpm_status kpm_bounds_lanczos(kpm_ham *h, int32_t k, uint64_t seed, double pad, 
     const bool wide = p.wide != 0;
     const lz_matvec_fn mv = wide ? lz_matvec_for<true>(h->opk) : lz_matvec_for<false>(h->opk);
     auto update = wide ? k_lz_update<true> : k_lz_update<false>;
-    auto scale = wide ? k_lz_scale<true> : k_lz_scale<false>;
-    const dim3 grid(p.nb), blk(BLOCK);
+    // two blocks per CU, the fewest partials to sum; more only where each still has many chunks
+    const uint32_t blocks = std::min<uint32_t>((p.nel + BLOCK - 1) / BLOCK, p.nel > (1u << 21) ? LZ_BLOCKS : 512);
+    const dim3 grid(blocks), blk(BLOCK);
     kpm_status e = upload(tab, &I, sizeof(Inst), st);
     if (e == KPM_OK) e = launch_init(KPM_F64, p.wide, tab, nullptr, p.nb, st);       // xi, <xi|xi> partials
     if (e == KPM_OK) e = launch_reduce(tab, 1, -1, 1, st);                          // dots[0]
-    if (e == KPM_OK) {
-        hipLaunchKernelGGL(scale, grid, blk, 0, st, tab, vb[0], 0);                  // v_0
-        e = check_launch();
-    }
+    double *pa = I.partial, *pw = I.partial + 2 * LZ_BLOCKS;   // partials of alpha, of ||w||^2
     int cur = 0;
     for (int32_t j = 0; j < k && e == KPM_OK; ++j) {
-        hipLaunchKernelGGL(mv, grid, blk, 0, st, tab, (const void *)vb[cur], ub, 2 * j + 1);
+        hipLaunchKernelGGL(mv, grid, blk, 0, st, tab, (const void *)vb[cur], ub, j, (const double *)pw, pa);
         e = check_launch();
-        if (e == KPM_OK) e = launch_reduce(tab, 1, 2 * j, 1, st);
         if (e == KPM_OK) {
-            hipLaunchKernelGGL(update, grid, blk, 0, st, tab, (const void *)ub, (const void *)vb[cur], vb[cur ^ 1], j);
-            e = check_launch();
-        }
-        if (e == KPM_OK) e = launch_reduce(tab, 1, 2 * j + 1, 1, st);
-        if (e == KPM_OK) {
-            hipLaunchKernelGGL(scale, grid, blk, 0, st, tab, vb[cur ^ 1], 2 * j + 2);
+            hipLaunchKernelGGL(update, grid, blk, 0, st, tab, (const void *)ub, (const void *)vb[cur], vb[cur ^ 1], j,
+                               (const double *)pa, pw);
             e = check_launch();
         }
         cur ^= 1;
     }
     if (e == KPM_OK) {
-        hipLaunchKernelGGL(k_lz_tridiag, dim3(1), dim3(64), 0, st, tab, k, pad, h->a, h->b, clamp_lo, clamp_hi,
-                           out_dev);
+        hipLaunchKernelGGL(k_lz_tridiag, dim3(1), dim3(2 * LZ_SECTIONS), 0, st, tab, k, pad, h->a, h->b, clamp_lo, clamp_hi,
+                           (const double *)pw, blocks, out_dev);
         e = check_launch();
     }
     return e;
