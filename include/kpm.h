@@ -276,6 +276,18 @@ kpm_status kpm_moments_batched(kpm_ham *const *h, int32_t count, const int32_t *
                                const uint64_t *instance, void *workspace_dev, size_t ws_bytes,
                                double *const *mu_dev, void *stream);
 
+/* Moments <j|T_n(H~)|j> of the local density of states at `count` sites (site: host
+ * array, entries below N), the unit start vectors as the columns of one solve with the
+ * dot products of every column kept apart: mu_dev[count][M], per site those of
+ * kpm_moments with KPM_VEC_UNIT, R = 1, instance = site (the same vectors; FP64 dots
+ * agree to rounding, FP32 solves sum their FP64 partials in another order).
+ * kpm_site_workspace_bytes gives the workspace (256-byte aligned); 0, and
+ * KPM_ERR_UNSUPPORTED from the call, for CSR operators, lattices of few sites (mode 2)
+ * and fewer than two sites: use kpm_moments_batched there. */
+size_t kpm_site_workspace_bytes(const kpm_ham *h, int32_t count, int32_t M);
+kpm_status kpm_site_moments(kpm_ham *h, int32_t count, const uint64_t *site, int32_t M, void *workspace_dev,
+                            size_t ws_bytes, double *mu_dev, void *stream);
+
 /* Steps a begun solve still has to run (0 once all floor(M/2) products are done). */
 kpm_status kpm_solve_remaining(const kpm_solve *s, int32_t *remaining);
 

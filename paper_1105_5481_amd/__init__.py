@@ -103,6 +103,8 @@ def lib():
         "kpm_last_hip_error": (ctypes.c_char_p, []),
         "kpm_solve_mode": (i32, [P]),
         "kpm_solve_depth": (i32, [P]),
+        "kpm_site_workspace_bytes": (sz, [P, i32, i32]),
+        "kpm_site_moments": (i32, [P, i32, P, i32, P, sz, P, P]),
         "kpm_dense_workspace_bytes": (sz, [i64, i32, i32]),
         "kpm_dense_moments": (i32, [P, i64, f64, f64, i32, i32, i32, u64, u64, P, sz, P, P]),
         "kpm_bounds_lanczos": (i32, [P, i32, u64, f64, f64, f64, P, sz, P, P]),
@@ -569,15 +571,25 @@ def green(mu, K: int, a: float, b: float, kernel: int = KERNEL_LORENTZ, lam: flo
 
 @_stream_scoped
 def site_moments(ham: "Hamiltonian", sites, M: int, stream=None) -> List:
-    """Moments <i|T_n(H~)|i> of the local DoS at each site i (unit start vector e_i): one batched
-    solve with R = 1 per site (KPM_VEC_UNIT with instance = i)."""
+    """Moments <i|T_n(H~)|i> of the local DoS at each site i (unit start vector e_i): the sites as the
+    columns of one solve (kpm_site_moments), or, for CSR operators and lattices of few sites, one
+    batched solve with R = 1 per site (KPM_VEC_UNIT with instance = i)."""
+    torch = _torch()
     sites = [int(i) for i in sites]
     if not sites:
         return []
     N = ham.N
     if min(sites) < 0 or max(sites) >= N:
         raise KPMError(f"site index out of range [0, {N})")
-    return moments_batched([ham] * len(sites), M, 1, VEC_UNIT, [0] * len(sites), sites, stream=stream)
+    n = len(sites)
+    nb = lib().kpm_site_workspace_bytes(ham.handle, n, int(M))
+    if nb:
+        ws = _workspace(nb, ham.device)
+        mu = torch.empty(n, int(M), dtype=torch.float64, device=ham.device)
+        _check(lib().kpm_site_moments(ham.handle, n, (ctypes.c_uint64 * n)(*sites), int(M), ws.data_ptr(), nb,
+                                      mu.data_ptr(), _stream(stream)), "kpm_site_moments")
+        return list(mu)
+    return moments_batched([ham] * n, M, 1, VEC_UNIT, [0] * n, sites, stream=stream)
 
 
 @_stream_scoped

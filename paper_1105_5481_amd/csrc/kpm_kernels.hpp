@@ -38,6 +38,8 @@
 // XCD x owns the x-th eighth of the column tiles (march) or tiles (flat).
 #pragma once
 
+#include <type_traits>
+
 #include "kpm_device.hpp"
 
 #define KPM_GLOBAL __attribute__((address_space(1)))
@@ -95,6 +97,7 @@ struct Inst {
     double *partial;   // [pslots][tiles][4]
     double *dots;      // [K+1][4] = (nn.hi, nn.lo, nm.hi, nm.lo)
     double *mu;        // [M]
+    const uint32_t *colsite;   // column solves: the site of each column's unit start vector
 };
 
 // ---------------------------------------------------------------------------
@@ -260,6 +263,43 @@ template <> struct Dots<float> {
     __device__ __forceinline__ double x3() const { return 0.0; }
     static constexpr bool DD = false;
 };
+// The dot products of each vector of a chunk by itself (NV vectors): for FP64 vectors two
+// (sum, error) pairs each, for FP32 vectors two sums.  value(k): vector k / V1, value k % V1 of
+// V1 = 4 or 2.
+template <typename S, bool CPLX> struct ColDots;
+template <bool CPLX> struct ColDots<float, CPLX> {
+    static constexpr int NV = CPLX ? 2 : 4, V1 = 2;
+    double s[NV][2] = {};
+    __device__ __forceinline__ void add(V16<float>::T o, V16<float>::T v)
+    {
+#pragma unroll
+        for (int l = 0; l < 4; ++l) {
+            double *a = s[CPLX ? l / 2 : l];
+            a[0] = fma((double)o[l], (double)o[l], a[0]);
+            a[1] = fma((double)o[l], (double)v[l], a[1]);
+        }
+    }
+    __device__ __forceinline__ double value(int k) const { return s[k / 2][k % 2]; }
+};
+template <bool CPLX> struct ColDots<double, CPLX> {
+    static constexpr int NV = CPLX ? 1 : 2, V1 = 4;
+    Dots<double> d[NV];
+    __device__ __forceinline__ void add(V16<double>::T o, V16<double>::T v)
+    {
+#pragma unroll
+        for (int l = 0; l < 2; ++l) {
+            Dots<double> &a = d[CPLX ? 0 : l];
+            dot2_acc_biased(a.s0, a.c0, o[l], o[l]);
+            dot2_acc_biased(a.s1, a.c1, o[l], v[l]);
+        }
+    }
+    __device__ __forceinline__ double value(int k) const
+    {
+        const Dots<double> &a = d[k / 4];
+        return k % 4 == 0 ? a.x0() : (k % 4 == 1 ? a.x1() : (k % 4 == 2 ? a.x2() : a.x3()));
+    }
+};
+
 // FP64 sums of any magnitude (vectors that are not near 1): ten operations per product.
 struct DotsWide {
     double s0 = 0.0, c0 = 0.0, s1 = 0.0, c1 = 0.0;
@@ -711,10 +751,35 @@ __device__ __forceinline__ typename V16<S>::T apply_cplx(bool hd, S d, typename 
     return out;
 }
 
+// Column solves: the sums of each vector over the block's threads, to dst[column][4].  The
+// threads of chunk c of their site are C apart; the values go through the LDS.
+template <typename A, int NB>
+__device__ __forceinline__ void column_sums(const Inst &I, const A &acc, double (&lds)[NB][BLOCK], uint32_t ct, double *dst)
+{
+#pragma unroll
+    for (int k = 0; k < NB; ++k) lds[k][threadIdx.x] = acc.value(k);
+    __syncthreads();
+    const uint32_t C = I.C, c0 = (ct * BLOCK) % C;   // the chunk of thread 0
+    for (uint32_t q = threadIdx.x; q < C * A::NV * 2; q += BLOCK) {
+        const uint32_t c = q / (A::NV * 2), v = (q / 2) % A::NV, o = q & 1u, col = c * A::NV + v;
+        const uint32_t k = v * A::V1 + o * (A::V1 / 2);
+        dd a{0.0, 0.0};
+        for (uint32_t t = (c + C - c0) % C; t < BLOCK; t += C)
+            a = dd_sum(a, dd{lds[k][t], A::V1 == 4 ? lds[k + A::V1 / 4][t] : 0.0});
+        if (col < (uint32_t)I.R) {
+            dst[col * 4 + 2 * o] = a.hi;
+            dst[col * 4 + 2 * o + 1] = a.lo;
+        }
+    }
+    __syncthreads();
+}
+
 // ---------------------------------------------------------------------------
 // the fused recursion step, march form (lattices)
 // ---------------------------------------------------------------------------
-template <typename S, int OPK, bool WIDE, bool NT>
+// COLS: the dot products of every vector by itself (unit start vectors at chosen sites, R of
+// them in one solve), one partial per item and column; an item is one segment.
+template <typename S, int OPK, bool WIDE, bool NT, bool COLS = false>
 __global__ __launch_bounds__(BLOCK) void k_step_march(const Inst *__restrict__ tab,
                                                       const uint32_t *__restrict__ bmap, int32_t k)
 {
@@ -736,13 +801,14 @@ __global__ __launch_bounds__(BLOCK) void k_step_march(const Inst *__restrict__ t
     const bool hd = I.has_diag;
     S hop = 0;
     if (!SPIN) hop = G::lds(I.hop, 0);
-    double *part = I.partial + (size_t)((n + 1) % I.pslots) * I.tiles * 4;
+    double *part = I.partial + (size_t)((n + 1) % I.pslots) * I.tiles * 4 * (COLS ? (uint32_t)I.R : 1u);
     const uint32_t C = I.C, P = I.P, Lx = I.Lx, Ly = I.Ly, Lm = I.Lm;
     const uint32_t PC = P * C;
-    __shared__ double red[RUN_MAX][BLOCK / 64][4];   // wave sums of the run's segments
+    typedef std::conditional_t<COLS, ColDots<S, SPIN>, Dots<S>> Acc;
+    __shared__ double red[COLS ? 1 : RUN_MAX][BLOCK / 64][4];   // wave sums of the run's segments
     // a thread's sums of the even segment of a pair, reduced with the odd one's (in the LDS:
     // four more VGPRs would cost the FP32 3D spin kernel one of its 7 waves per SIMD)
-    __shared__ double held[Dots<S>::NV][BLOCK];
+    __shared__ double held[COLS ? ColDots<S, SPIN>::NV * ColDots<S, SPIN>::V1 : Dots<S>::NV][BLOCK];
     const ItemRange ir = item_range(I, I.nct, (I.nseg + I.run - 1) / I.run);
     for (uint32_t it = ir.first; it < ir.count; it += ir.stride) {
         uint32_t ct, rn;
@@ -777,7 +843,7 @@ __global__ __launch_bounds__(BLOCK) void k_step_march(const Inst *__restrict__ t
         S2 bb = {0, 0};
         if (SPIN) bb = G::ldc(I.bond, (p + P * (down ? mfirst : mbefore)) * DIM + (DIM - 1));
         for (uint32_t sg = s0; sg < s1; ++sg) {
-            Dots<S> acc;
+            Acc acc;
             const uint32_t m0 = sg * I.S, m1 = min(m0 + I.S, Lm);
             if (active)
                 for (uint32_t s_ = 0; s_ < m1 - m0; ++s_) {
@@ -830,14 +896,20 @@ __global__ __launch_bounds__(BLOCK) void k_step_march(const Inst *__restrict__ t
                     vb = v0;
                     v0 = va;
                 }
-            const uint32_t k = sg - s0, w = threadIdx.x >> 6;
-            if (k & 1u) wave_reduce_store(Dots<S>(held), acc, red[k - 1][w], red[k][w]);
-            else if (sg + 1 < s1) acc.save(held);
-            else wave_reduce_store(acc, red[k][w]);
+            if constexpr (COLS) {
+                column_sums(I, acc, held, ct, part + (size_t)(sg * I.nct + ct) * I.R * 4);
+            } else {
+                const uint32_t k = sg - s0, w = threadIdx.x >> 6;
+                if (k & 1u) wave_reduce_store(Dots<S>(held), acc, red[k - 1][w], red[k][w]);
+                else if (sg + 1 < s1) acc.save(held);
+                else wave_reduce_store(acc, red[k][w]);
+            }
         }
-        __syncthreads();
-        reduce_run<Dots<S>::DD>(red, s1 - s0, part + (size_t)(s0 * I.nct + ct) * 4, (size_t)I.nct * 4);
-        __syncthreads();
+        if constexpr (!COLS) {
+            __syncthreads();
+            reduce_run<Dots<S>::DD>(red, s1 - s0, part + (size_t)(s0 * I.nct + ct) * 4, (size_t)I.nct * 4);
+            __syncthreads();
+        }
     }
 }
 
@@ -1284,6 +1356,66 @@ __global__ __launch_bounds__(BLOCK) void k_moments(const Inst *__restrict__ tab)
     }
     const dd q = dd_div_d(v, I->norm);
     I->mu[m] = q.hi + q.lo;
+}
+
+// ---------------------------------------------------------------------------
+// column solves: unit start vectors e_{site[r]}, r < R, dots [R][K + 1][4]
+// ---------------------------------------------------------------------------
+template <typename S> __global__ __launch_bounds__(BLOCK) void k_cols_init(const Inst *__restrict__ tab)
+{
+    constexpr int W = V16<S>::W;
+    const Inst I = tab[0];
+    for (uint64_t e = (uint64_t)blockIdx.x * BLOCK + threadIdx.x; e < I.nel; e += (uint64_t)gridDim.x * BLOCK) {
+        const uint32_t i = fdiv((uint32_t)e, I.fC), c = (uint32_t)e - i * I.C;
+        typename V16<S>::T v;
+#pragma unroll
+        for (int l = 0; l < W; ++l) {
+            const uint32_t k = c * W + l, r = I.cplx ? k / 2 : k;
+            v[l] = (r < (uint32_t)I.R && (!I.cplx || (k & 1u) == 0) && I.colsite[r] == i) ? (S)1 : (S)0;
+        }
+        ((typename V16<S>::T *)I.buf0)[e] = v;
+    }
+}
+// Dots indices lo .. lo + gridDim.x - 1 of sixteen columns (blockIdx.y): eight threads per sum
+// over the items, their sums added in order.
+__global__ __launch_bounds__(BLOCK) void k_cols_reduce(const Inst *__restrict__ tab, int32_t lo)
+{
+    const Inst *I = tab;
+    const int32_t idx = lo + (int32_t)blockIdx.x;
+    const uint32_t R = (uint32_t)I->R, tl = threadIdx.x >> 5, pr = threadIdx.x & 31u;
+    const uint32_t col = blockIdx.y * 16 + (pr >> 1), o = (pr & 1u) * 2;
+    __shared__ double red[8][32][2];
+    dd a{0.0, 0.0};
+    if (col < R) {
+        const double *p = I->partial + (size_t)(idx % I->pslots) * I->tiles * R * 4 + col * 4 + o;
+        for (uint32_t t = tl; t < I->tiles; t += 8) a = dd_sum(a, dd{p[(size_t)t * R * 4], p[(size_t)t * R * 4 + 1]});
+    }
+    red[tl][pr][0] = a.hi;
+    red[tl][pr][1] = a.lo;
+    __syncthreads();
+    if (tl == 0 && col < R) {
+        for (int k = 1; k < 8; ++k) a = dd_sum(a, dd{red[k][pr][0], red[k][pr][1]});
+        double *d = I->dots + ((size_t)col * (I->K + 1) + idx) * 4 + o;
+        d[0] = a.hi;
+        d[1] = a.lo;
+    }
+}
+// mu[column][m] as k_moments forms them, <r_0|r_0> = 1.
+__global__ __launch_bounds__(BLOCK) void k_cols_moments(const Inst *__restrict__ tab)
+{
+    const Inst *I = tab;
+    const int32_t m = blockIdx.x * BLOCK + threadIdx.x;
+    if (m >= I->M) return;
+    const double *D = I->dots + (size_t)blockIdx.y * (I->K + 1) * 4;
+    dd v{1.0, 0.0};
+    if (m == 1) {
+        v = dd{D[4 + 2], D[4 + 3]};
+    } else if (m > 1 && (m & 1) == 0) {
+        v = dd_add(dd{2.0 * D[(m / 2) * 4 + 0], 2.0 * D[(m / 2) * 4 + 1]}, dd{-1.0, 0.0});
+    } else if (m > 1) {
+        v = dd_add(dd{2.0 * D[(m / 2 + 1) * 4 + 2], 2.0 * D[(m / 2 + 1) * 4 + 3]}, dd{-D[4 + 2], -D[4 + 3]});
+    }
+    I->mu[(size_t)blockIdx.y * I->M + m] = v.hi + v.lo;
 }
 
 }  // namespace kpm

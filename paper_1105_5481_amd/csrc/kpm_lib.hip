@@ -1957,6 +1957,120 @@ kpm_status kpm_moments_batched(kpm_ham *const *h, int32_t count, const int32_t *
 }
 
 // ---------------------------------------------------------------------------
+// site moments: unit start vectors at chosen sites as the columns of one solve
+// ---------------------------------------------------------------------------
+extern "C++" {
+namespace {
+// Columns per solve: the vectors of one solve share each site's bonds, and fill the chunks
+// that a solve of one vector leaves half or three quarters empty; as many as keep the
+// state in the Infinity Cache, at most COLS_MAX.
+constexpr int32_t COLS_MAX = 64, COLS_SLOTS = 16;
+struct ColsLayout {
+    Plan p;
+    int32_t cols, solves;       // columns of the largest solve, number of solves
+    size_t site_off, part_off, dots_off, buf_off, total;
+};
+bool cols_layout(const kpm_ham *h, int32_t count, int32_t M, ColsLayout &L)
+{
+    // lattices whose solve of one vector marches (few-site solves take a workgroup per site)
+    if (!h || h->dim == 0 || count < 2 || M < 1 || !make_plan(h, M, 1, KPM_VEC_UNIT, L.p, false) || L.p.mode != MODE_MARCH)
+        return false;
+    const double per = 2.0 * (double)h->N * (h->cplx_op ? 2 : 1) * L.p.esz;
+    const int32_t most = std::max<int32_t>((int32_t)L.p.W, (int32_t)std::min<double>(COLS_MAX, (224.0 * 1048576.0) / per));
+    L.solves = (count + most - 1) / most;
+    L.cols = (count + L.solves - 1) / L.solves;
+    L.solves = (count + L.cols - 1) / L.cols;
+    if (!make_plan(h, M, L.cols, KPM_VEC_UNIT, L.p, false) || L.p.mode != MODE_MARCH) return false;
+    L.p.P_slots = std::min(L.p.K + 1, COLS_SLOTS);
+    L.site_off = align256(sizeof(Inst));
+    L.part_off = L.site_off + align256((size_t)count * 4);
+    // the last solve may have fewer columns, and other tiles
+    Plan last;
+    const int32_t rest = count - (L.solves - 1) * L.cols;
+    if (rest < 1 || !make_plan(h, M, rest, KPM_VEC_UNIT, last, false) || last.mode != MODE_MARCH) return false;
+    L.dots_off = L.part_off + align256((size_t)L.p.P_slots * 32 *
+                                       std::max((size_t)L.p.tiles * L.cols, (size_t)last.tiles * rest));
+    L.buf_off = L.dots_off + align256((size_t)L.cols * (L.p.K + 1) * 32);
+    L.total = L.buf_off + 2 * L.p.buf_bytes;
+    return true;
+}
+template <typename S, bool WIDE>
+step_fn cols_for(int opk, int nt)
+{
+    switch (opk) {
+    case OP_REAL2: return nt ? k_step_march<S, OP_REAL2, WIDE, true, true> : k_step_march<S, OP_REAL2, WIDE, false, true>;
+    case OP_REAL3: return nt ? k_step_march<S, OP_REAL3, WIDE, true, true> : k_step_march<S, OP_REAL3, WIDE, false, true>;
+    case OP_SPIN2: return nt ? k_step_march<S, OP_SPIN2, WIDE, true, true> : k_step_march<S, OP_SPIN2, WIDE, false, true>;
+    default: return nt ? k_step_march<S, OP_SPIN3, WIDE, true, true> : k_step_march<S, OP_SPIN3, WIDE, false, true>;
+    }
+}
+}  // namespace
+}  // extern "C++"
+
+size_t kpm_site_workspace_bytes(const kpm_ham *h, int32_t count, int32_t M)
+{
+    ColsLayout L;
+    return cols_layout(h, count, M, L) ? L.total : 0;
+}
+
+kpm_status kpm_site_moments(kpm_ham *h, int32_t count, const uint64_t *site, int32_t M, void *ws, size_t ws_bytes,
+                            double *mu_dev, void *stream)
+{
+    if (!h || !site || !mu_dev || count < 1 || M < 1) return KPM_ERR_INVALID_ARG;
+    for (int32_t r = 0; r < count; ++r)
+        if (site[r] >= (uint64_t)h->N) return KPM_ERR_INVALID_ARG;
+    ColsLayout L;
+    if (!cols_layout(h, count, M, L)) return KPM_ERR_UNSUPPORTED;
+    if (!ws || ((uintptr_t)ws & 255) || ws_bytes < L.total) return KPM_ERR_WORKSPACE;
+    hipStream_t st = S(stream);
+    char *base = (char *)ws;
+    Inst *tab = (Inst *)base;
+    std::vector<uint32_t> ids(site, site + count);
+    kpm_status e = upload(base + L.site_off, ids.data(), (size_t)count * 4, st);
+    for (int32_t q = 0; q < count && e == KPM_OK; q += L.cols) {
+        const int32_t R = std::min(L.cols, count - q);
+        Plan p;
+        if (!make_plan(h, M, R, KPM_VEC_UNIT, p, false) || p.mode != MODE_MARCH) return KPM_ERR_UNSUPPORTED;
+        p.P_slots = L.p.P_slots;
+        Inst I;
+        fill_inst(h, p, M, R, KPM_VEC_UNIT, 0, 0, base, I);
+        I.partial = (double *)(base + L.part_off);
+        I.dots = (double *)(base + L.dots_off);
+        I.buf0 = base + L.buf_off;
+        I.buf1 = base + L.buf_off + L.p.buf_bytes;
+        I.colsite = (const uint32_t *)(base + L.site_off) + q;
+        I.mu = mu_dev + (size_t)q * M;
+        e = upload(tab, &I, sizeof(Inst), st);
+        const uint32_t ib = (uint32_t)std::min<uint64_t>(((uint64_t)p.nel + BLOCK - 1) / BLOCK, 4096);
+        if (h->prec == KPM_F64) hipLaunchKernelGGL(k_cols_init<double>, dim3(ib), dim3(BLOCK), 0, st, tab);
+        else hipLaunchKernelGGL(k_cols_init<float>, dim3(ib), dim3(BLOCK), 0, st, tab);
+        if (e == KPM_OK) e = check_launch();
+        const step_fn f = h->prec == KPM_F64
+                              ? (p.wide ? cols_for<double, true>(h->opk, p.nt) : cols_for<double, false>(h->opk, p.nt))
+                              : (p.wide ? cols_for<float, true>(h->opk, p.nt) : cols_for<float, false>(h->opk, p.nt));
+        int32_t reduced = 1;   // dots index 0 is 1 for every column
+        auto reduce_to = [&](int32_t to) {
+            if (to <= reduced) return KPM_OK;
+            hipLaunchKernelGGL(k_cols_reduce, dim3(to - reduced, (R + 15) / 16), dim3(BLOCK), 0, st, tab, reduced);
+            reduced = to;
+            return check_launch();
+        };
+        for (int32_t n = 0; n < p.K && e == KPM_OK; ++n) {
+            if (n + 1 - reduced >= p.P_slots) e = reduce_to(n + 1);
+            if (e != KPM_OK) break;
+            hipLaunchKernelGGL(f, dim3(p.nb), dim3(BLOCK), 0, st, (const Inst *)tab, (const uint32_t *)nullptr, n);
+            e = check_launch();
+        }
+        if (e == KPM_OK) e = reduce_to(p.K + 1);
+        if (e == KPM_OK) {
+            hipLaunchKernelGGL(k_cols_moments, dim3((M + BLOCK - 1) / BLOCK, R), dim3(BLOCK), 0, st, tab);
+            e = check_launch();
+        }
+    }
+    return e;
+}
+
+// ---------------------------------------------------------------------------
 // dynamic batches: begun solves advanced together, each at its own step
 // ---------------------------------------------------------------------------
 struct kpm_batch {
