@@ -370,7 +370,8 @@ kpm_status kpm_start_vectors(int32_t vec, int32_t complex_layout, uint64_t seed,
 
 /* Launch-shape tuning (host state, process-wide; applies to solves begun
  * afterwards).  Keys:
- *   KPM_LAUNCH_ELEMS_PER_THREAD  flat kernels: 16-byte chunks per thread per tile (1, 2 or 4)
+ *   KPM_LAUNCH_ELEMS_PER_THREAD  flat kernels: 16-byte chunks per thread per tile (1, 2 or 4;
+ *                                at the default, 4, CSR solves of up to 2^22 chunks take 1)
  *   KPM_LAUNCH_MAX_BLOCKS        blocks per instance per launch (multiple of 8, >= 8; default
  *                                2048)
  *   KPM_LAUNCH_MARCH             1: lattices use the march kernels; 0: the flat kernels

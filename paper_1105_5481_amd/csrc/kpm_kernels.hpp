@@ -916,6 +916,21 @@ __global__ __launch_bounds__(BLOCK) void k_step_march(const Inst *__restrict__ t
 // ---------------------------------------------------------------------------
 // the fused recursion step, flat form (CSR; lattices on request)
 // ---------------------------------------------------------------------------
+// CSR rows are walked CSR_AHEAD entries at a time: their columns and values first, then
+// the gathers of r_n, all in flight together (each entry used to wait for its column, then
+// for its gather: a chain of 2 nnz/N latencies with a wave's only loads).  A lane past its
+// row's end, or at the stored diagonal, gathers nothing: a clamped gather repeated the last
+// one from the L2 (100000 rows of 13, FP64 R = 16: 60 -> 72 us).  Entries are added in
+// stored order.  Once enough waves run, the gathers are bound by the lines that the
+// Infinity Cache delivers; groups of chunks per XCD, so that a group's r_n fits the L2,
+// paid more for their narrower gathers than they saved, and non-temporal loads of the
+// entries lost the lines that neighbouring rows share.  us per step, 1 -> 4 -> 8 entries
+// at one chunk per thread and tile (before: 1 entry at four):
+//   100000 rows of 13, complex FP32, R = 16     30.9 -> 29.1 -> 28.1   (45.7)
+//   the same in FP64                            60.6 -> 61.2 -> 55.5   (60.1)
+//   200000 rows of 17, complex FP32, R = 8     100.2 -> 74.4 -> 70.3   (70.3)
+//   30000 rows of 13, complex FP32, R = 16      14.1 ->  9.9 -> 10.2   (38.0)
+constexpr int CSR_AHEAD = 8;
 // H~ r on chunk e, r read through ld(chunk index); v receives the chunk itself.
 template <typename S, int OPK, bool WIDE, typename LD>
 __device__ __forceinline__ typename V16<S>::T flat_apply(const Inst &I, uint32_t e, S hop, const LD &ld,
@@ -979,20 +994,35 @@ __device__ __forceinline__ typename V16<S>::T flat_apply(const Inst &I, uint32_t
         T a;
 #pragma unroll
         for (int l = 0; l < W; ++l) a[l] = d * v[l];
-        for (int64_t kk = kb; kk < ke; ++kk) {
-            const uint32_t jj = (uint32_t)I.col[kk];
-            if (jj == i) continue;
-            const T vj = ld(jj * C + c);
-            if constexpr (OPK == OP_CSR_R) {
-                a = A::mac(a, ((const S *)I.val)[kk], vj);
-            } else {
-                const S hr = ((const S *)I.val)[2 * kk], hi = ((const S *)I.val)[2 * kk + 1];
+        for (int64_t kk = kb; kk < ke; kk += CSR_AHEAD) {
+            uint32_t jj[CSR_AHEAD];
+            S2 h[CSR_AHEAD];
+            T vj[CSR_AHEAD];
 #pragma unroll
-                for (int l = 0; l < W / 2; ++l) {
-                    S ar = a[2 * l], ai = a[2 * l + 1];
-                    A::cmac(ar, ai, hr, hi, vj[2 * l], vj[2 * l + 1]);
-                    a[2 * l] = ar;
-                    a[2 * l + 1] = ai;
+            for (int z = 0; z < CSR_AHEAD; ++z) {
+                const int64_t o = min(kk + z, ke - 1);
+                jj[z] = kk + z < ke ? (uint32_t)I.col[o] : i;   // i: an entry not added
+                if constexpr (OPK == OP_CSR_R) h[z] = S2{((const S *)I.val)[o], (S)0};
+                else h[z] = ((const S2 *)I.val)[o];
+            }
+#pragma unroll
+            for (int z = 0; z < CSR_AHEAD; ++z) {
+                vj[z] = (T)(S)0;
+                if (jj[z] != i) vj[z] = ld(jj[z] * C + c);
+            }
+#pragma unroll
+            for (int z = 0; z < CSR_AHEAD; ++z) {
+                if (jj[z] == i) continue;
+                if constexpr (OPK == OP_CSR_R) {
+                    a = A::mac(a, h[z][0], vj[z]);
+                } else {
+#pragma unroll
+                    for (int l = 0; l < W / 2; ++l) {
+                        S ar = a[2 * l], ai = a[2 * l + 1];
+                        A::cmac(ar, ai, h[z][0], h[z][1], vj[z][2 * l], vj[z][2 * l + 1]);
+                        a[2 * l] = ar;
+                        a[2 * l + 1] = ai;
+                    }
                 }
             }
         }

@@ -21,7 +21,8 @@ using namespace kpm;
 namespace {
 
 constexpr int PSLOTS_MAX = 64;          // ring slots of per-tile partials between reductions
-int g_tpt = 4;                          // flat kernels: chunks per thread per tile
+constexpr int TPT_DEFAULT = 4;
+int g_tpt = TPT_DEFAULT;                // flat kernels: chunks per thread per tile
 int g_max_blocks = 2048;                // blocks per instance per launch (multiple of 8)
 int g_march = 1;                        // lattices use the march kernels
 int g_march_items = 512;                // target work items per instance when choosing march segments
@@ -689,6 +690,7 @@ bool small_plan(const kpm_ham *h, Plan &p, int32_t M)
     return true;
 }
 
+constexpr uint32_t CSR_FINE = 1u << 14;
 constexpr uint32_t RUN_PLANES = 4;   // planes a run of short segments covers
 
 bool make_plan(const kpm_ham *h, int32_t M, int32_t R, int32_t vec, Plan &p, bool allow_tb = true)
@@ -771,6 +773,13 @@ bool make_plan(const kpm_ham *h, int32_t M, int32_t R, int32_t vec, Plan &p, boo
         p.alt = p.S >= RUN_PLANES ? g_alternate : 0;   // shorter segments may be walked in runs
     } else {
         p.mode = MODE_FLAT;
+        // CSR tiles of one chunk per thread up to CSR_FINE tiles: the gathers want every
+        // wave the chip holds, and four chunks left 100000 x 8 chunks on 781 blocks, 5000 x
+        // 2 on ten.  us per step, 4 -> 1 (eight entries ahead): 100000 rows, R = 16 complex
+        // FP32 31.0 -> 28.1, 30000 17.1 -> 10.2, 100000 rows R = 4 real 22.0 -> 12.3.  With
+        // more tiles than that the launch has eight rounds of blocks anyway, and tiles of
+        // four keep the partials small.
+        if (!h->dim && g_tpt == TPT_DEFAULT && nel <= (uint64_t)CSR_FINE * BLOCK) p.tpt = 1;
         const uint64_t per_tile = (uint64_t)BLOCK * p.tpt;
         p.tiles = (uint32_t)((nel + per_tile - 1) / per_tile);
         p.xcd = p.tiles >= XCD_MIN_ITEMS ? 1 : 0;
