@@ -20,7 +20,7 @@
 // 27 us at 64^3 sites (five launches), the tridiagonal solve on one thread 870 us; the
 // whole interval with k = 100 went from 3.6 to 1.8 ms (20^3: 32 to 13 us per step).
 // The scalars stay on the device, in the instance's dots array, as
-// double-double sums (each used as its rounded high part):
+// double-double sums (each used rounded to a double):
 //   index 0       <xi|xi>
 //   index 2j + 1  (0, Re<u|v_j>)         alpha_j = the second sum
 //   index 2j + 2  (||w||^2, 0)           beta_j = sqrt(the first sum)
@@ -69,6 +69,13 @@ __device__ __forceinline__ V16<double>::T lz_unit(V16<double>::T y, double nrm)
     return y;
 }
 
+// The first sum at dots index idx, rounded: <xi|xi> comes as a pair whose high part alone is
+// a multiple of 2^-36 (biased sums), 16 ulps at 4096 sites; later ones are rounded already.
+__device__ __forceinline__ double lz_norm2(const Inst &I, int32_t idx)
+{
+    return I.dots[(size_t)idx * 4] + I.dots[(size_t)idx * 4 + 1];
+}
+
 // u = H~ v_j, v_j = w / ||w||, and the partials of Re<u|v_j> in pout.  ||w||^2 is the sum of
 // `pin` (j > 0; block 0 leaves it at dots index 2j) or dots index 0.
 template <int OPK, bool WIDE>
@@ -78,7 +85,7 @@ __global__ __launch_bounds__(BLOCK) void k_lz_matvec(const Inst *__restrict__ ta
     typedef Mem<double, WIDE> G;
     typedef V16<double>::T T;
     const Inst I = tab[0];
-    double n2 = I.dots[0], lo = 0.0;
+    double n2 = lz_norm2(I, 0), lo = 0.0;
     if (j > 0) {
         n2 = lz_total(pin, gridDim.x, lo);
         if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -118,8 +125,8 @@ __global__ __launch_bounds__(BLOCK) void k_lz_update(const Inst *__restrict__ ta
         I.dots[(size_t)(2 * j + 1) * 4 + 2] = al;
         I.dots[(size_t)(2 * j + 1) * 4 + 3] = lo;
     }
-    const double nrm = sqrt(I.dots[(size_t)(2 * j) * 4 + 0]);                      // of w_j: beta_{j-1} for j > 0
-    const double nrp = j > 0 ? sqrt(I.dots[(size_t)(2 * j - 2) * 4 + 0]) : 0.0;    // of w_{j-1}
+    const double nrm = sqrt(lz_norm2(I, 2 * j));                      // of w_j: beta_{j-1} for j > 0
+    const double nrp = j > 0 ? sqrt(lz_norm2(I, 2 * j - 2)) : 0.0;    // of w_{j-1}
     DotsWide acc;
     const LzRange r = lz_range(I.nel);
     for (uint32_t e = r.first; e < r.end; e += r.stride) {

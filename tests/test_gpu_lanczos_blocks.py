@@ -25,3 +25,17 @@ def test_lanczos_block_counts(L, k):
     assert np.abs(got["beta"][:m - 1] - be[:m - 1]).max(initial=0.0) <= COEF_TOL
     lo, hi = gu.oracle_bounds(op)
     assert lo - 0.1 <= got["e_lo"] < got["e_hi"] <= hi + 0.1
+
+
+@pytest.mark.parametrize("L", [(16, 12, 20), (61, 43)], ids=str)
+def test_lanczos_phase_start_is_normalised_exactly(L):
+    """<xi|xi> of phase vectors is no whole number: with it and every later sum rounded once, the
+    coefficients are the oracle's bit for bit, also where rounding errors have grown."""
+    theta, phi = wl.spins_uniform(int(np.prod(L)), 23)
+    op = wl.Lattice(dim=len(L), L=L + (1,) * (3 - len(L)), t=1.0, hop=wl.HOP_SPIN, spinor=wl.spinor_of(theta, phi))
+    h = kpm.Hamiltonian(op, 4.0, 0.0, kpm.F64)
+    got = kpm.lanczos_bounds(h, 150, 3, 0.005, clamp=None)
+    h.free()
+    al, be = _oracle_lanczos(op, 4.0, 0.0, 150, 3)
+    assert np.array_equal(got["alpha"], al[:len(got["alpha"])])
+    assert np.array_equal(got["beta"], be[:len(got["beta"])])
