@@ -602,7 +602,8 @@ bool tb3_plan(const kpm_ham *h, Plan &p)
 // split by tiles and 3 or 4 steps per pass: 2048^2 R = 64 FP32 235 -> 166 us, FP64
 // 636 -> 405; 1024^2 spin R = 32 FP32 112 -> 79; 339^2 spin R = 34 18.1 -> 11.5;
 // 1001 x 750 R = 21 FP64 65 -> 30; 512^2 R = 16 7.6 -> 5.4.
-void tb_plan(const kpm_ham *h, Plan &p)
+// Tilings of more than max_tiles items are passed over; false if none is left.
+bool tb_plan(const kpm_ham *h, Plan &p, uint64_t max_tiles = ~0ull)
 {
     const uint32_t Lx = (uint32_t)h->L[0], Ly = (uint32_t)h->L[1], C = p.C;
     const bool f64 = h->prec == KPM_F64, spin = h->opk == OP_SPIN2;
@@ -612,11 +613,12 @@ void tb_plan(const kpm_ham *h, Plan &p)
     const int dlo = g_tblock < 0 ? 3 : (g_tblock >= 3 ? g_tblock : 2), dhi = g_tblock < 0 ? TB_DMAX : dlo;
     // groups of at least this many chunks (0: as few groups as leave a window of 8 sites)
     const uint32_t gmin = g_tb_group < 0 ? 1 : (g_tb_group == 0 ? TB_BLOCK / 8 : (uint32_t)g_tb_group);
+    const bool bounded = max_tiles != ~0ull;
     double best = 1e300;
     for (uint32_t Cg = std::min(C, TB_BLOCK / 8); Cg >= 1; --Cg) {
         if (TB_BLOCK / Cg > Lx) break;                                      // the window must fit the row
         if (Cg < std::min({gmin, C, TB_BLOCK / 8}) && best < 1e300) break;
-        if (Cg > 8 && C > 8 && g_tb_group < 0 && TB_BLOCK / (Cg - 1) <= Lx) continue;   // far too narrow
+        if (Cg > 8 && C > 8 && g_tb_group < 0 && !bounded && TB_BLOCK / (Cg - 1) <= Lx) continue;   // far too narrow
         const uint32_t G = (C + Cg - 1) / Cg, Wn = TB_BLOCK / Cg;
         for (int D = dlo; D <= dhi || D == dlo; ++D) {
             const int d = std::max(2, std::min({D, (int)(Wn / 4), (int)(Ly / 2)}));
@@ -626,13 +628,14 @@ void tb_plan(const kpm_ham *h, Plan &p)
             const uint32_t bpc = (uint32_t)TB_WAVES_PER_EU(f64, spin, d);
             const uint64_t slots = std::max<uint64_t>(1, 256ull * bpc * (uint64_t)g_march_items / 512);
             uint32_t seen = 0;
-            for (uint64_t r = 1; r <= 8; ++r) {
-                uint32_t nseg = (uint32_t)std::max<uint64_t>(1, r * slots / units);
+            for (uint64_t r = bounded ? 0 : 1; r <= 8; ++r) {
+                uint32_t nseg = (uint32_t)std::max<uint64_t>(1, (r ? r * slots : max_tiles) / units);
                 nseg = std::min<uint32_t>(nseg, std::max<uint32_t>(1, Ly / 4));
                 const uint32_t S = (Ly + nseg - 1) / nseg;
                 nseg = (Ly + S - 1) / S;
                 if (nseg == seen) continue;
                 seen = nseg;
+                if (units * nseg > max_tiles) continue;
                 const uint64_t items = units * nseg, full = items / slots, rest = items % slots;
                 auto iter = [&](double b) { return std::max(lat + b * w * d, b * mem); };
                 const double t = full * iter((double)bpc) + (rest ? iter(std::ceil((double)rest / 256.0)) : 0.0);
@@ -653,6 +656,7 @@ void tb_plan(const kpm_ham *h, Plan &p)
     p.P = Lx;
     p.Lm = Ly;
     p.xcd = p.tiles >= XCD_MIN_ITEMS ? 3 : 0;
+    return best < 1e300;
 }
 
 // Solves of few sites (k_solve_small): those whose whole vector blocks fit the LDS of one CU
@@ -713,6 +717,18 @@ bool make_plan(const kpm_ham *h, int32_t M, int32_t R, int32_t vec, Plan &p, boo
     const uint64_t bond_bytes = (uint64_t)h->N * (h->dim ? h->dim : 1) * 2 * p.esz;
     p.wide = (nel * 16 >= (1ull << 32) || bond_bytes >= (1ull << 32)) ? 1 : 0;
     p.nbuf = 2;
+    p.K = M / 2;
+    p.P_slots = std::min(p.K + 1, PSLOTS_MAX);
+    p.dots_bytes = align256((size_t)(p.K + 1) * 4 * sizeof(double));
+    p.buf_bytes = align256((size_t)h->N * p.Rs * p.esz);
+    // work items whose partials still fit the static scratch beside nbuf vector buffers: a
+    // solve that fits it with coarser tiles takes those (kpm_moments_static)
+    auto scratch_tiles = [&](size_t nbuf) {
+        const size_t rest = align256(sizeof(Inst)) + p.dots_bytes + nbuf * p.buf_bytes;
+        return rest >= KPM_STATIC_SCRATCH_BYTES
+                   ? (uint64_t)0
+                   : (KPM_STATIC_SCRATCH_BYTES - rest) / ((uint64_t)p.P_slots * 4 * sizeof(double));
+    };
     if (g_small && small_plan(h, p, M)) {
         p.mode = MODE_SMALL;
     } else if (allow_tb && g_tblock && g_march && (h->opk == OP_REAL2 || h->opk == OP_SPIN2) &&
@@ -727,6 +743,9 @@ bool make_plan(const kpm_ham *h, int32_t M, int32_t R, int32_t vec, Plan &p, boo
         p.mode = MODE_TB;
         p.nbuf = 4;
         tb_plan(h, p);
+        const uint64_t most = scratch_tiles(p.nbuf);
+        Plan q = p;
+        if (most && p.tiles > most && tb_plan(h, q, most)) p = q;
     } else if (allow_tb && g_tblock && g_march &&
                (g_tb3 > 0 ? (h->opk == OP_REAL3 || h->opk == OP_SPIN3)
                           : (g_tb3 < 0 && h->opk == OP_REAL3 && h->prec == KPM_F32)) &&
@@ -779,18 +798,17 @@ bool make_plan(const kpm_ham *h, int32_t M, int32_t R, int32_t vec, Plan &p, boo
         // FP32 31.0 -> 28.1, 30000 17.1 -> 10.2, 100000 rows R = 4 real 22.0 -> 12.3.  With
         // more tiles than that the launch has eight rounds of blocks anyway, and tiles of
         // four keep the partials small.
-        if (!h->dim && g_tpt == TPT_DEFAULT && nel <= (uint64_t)CSR_FINE * BLOCK) p.tpt = 1;
+        const uint64_t fine = (nel + BLOCK - 1) / BLOCK, most = scratch_tiles(p.nbuf);
+        if (!h->dim && g_tpt == TPT_DEFAULT && fine <= CSR_FINE &&
+            (fine <= most || (fine + TPT_DEFAULT - 1) / TPT_DEFAULT > most))
+            p.tpt = 1;
         const uint64_t per_tile = (uint64_t)BLOCK * p.tpt;
         p.tiles = (uint32_t)((nel + per_tile - 1) / per_tile);
         p.xcd = p.tiles >= XCD_MIN_ITEMS ? 1 : 0;
     }
     const uint32_t nb = (p.tiles + 7) / 8 * 8;
     p.nb = std::min<uint32_t>(nb, p.grid_cap ? p.grid_cap : (uint32_t)g_max_blocks);
-    p.K = M / 2;
-    p.P_slots = std::min(p.K + 1, PSLOTS_MAX);
     p.part_bytes = align256((size_t)p.P_slots * p.tiles * 4 * sizeof(double));
-    p.dots_bytes = align256((size_t)(p.K + 1) * 4 * sizeof(double));
-    p.buf_bytes = align256((size_t)h->N * p.Rs * p.esz);
     if (p.mode == MODE_SMALL) {
         p.P_slots = small_slots(p);
         p.part_bytes = align256((size_t)p.P_slots * p.tiles * 4 * sizeof(double));
@@ -1565,15 +1583,11 @@ namespace {
 // the per-block map (instance index within the group, NO_INSTANCE for idle
 // blocks); returns the grid size.
 //
-// The waves of a static batch (wave = true) run many instances through all
-// their steps together: there, with at least 8 instances, one-step march
-// instances are balanced whole over the XCDs even where their own plan would
-// split them (all column tiles of an instance then share one L2 for their
-// in-plane neighbour reads), with 25% slack over the even share before one is
-// split.  Measured on the batch of 256 spin cubes (L = 16 .. 48): 193.6 ->
-// 183.7 ms per batched solve (only the instances without a split of their own,
-// 10% slack: 192.3 ms).  Dynamic batches, whose few members differ widely in
-// size, measured 1-2% slower under that rule and keep the one above.
+// wave = true: with at least 8 instances, one-step march instances are balanced
+// whole over the XCDs even where their own plan would split them, with 25% slack
+// over the even share before one is split.  The march instances of a static
+// batch, for which this was, are placed by place_even below, so only its flat
+// instances come here with it (their work is split as above, with that slack).
 // Runs of the march instances of one launch: short segments (fewer than RUN_PLANES
 // planes) are walked in runs of about that many planes once the launch has more than
 // RUN_BLOCKS blocks without them (4 per CU); below that the blocks are what is missing.
@@ -1972,7 +1986,9 @@ extern "C++" {
 namespace {
 // Columns per solve: the vectors of one solve share each site's bonds, and fill the chunks
 // that a solve of one vector leaves half or three quarters empty; as many as keep the
-// state in the Infinity Cache, at most COLS_MAX.
+// state in the Infinity Cache, at most COLS_MAX.  64 sites of a 48^3 spin lattice, FP32,
+// M = 1024: 42.4 ms as 64 solves of one vector, 21.6 ms as one of 64 columns (38.4 us per
+// step, two vector blocks of 113 MB: 8.8 TB/s from the caches).
 constexpr int32_t COLS_MAX = 64, COLS_SLOTS = 16;
 struct ColsLayout {
     Plan p;

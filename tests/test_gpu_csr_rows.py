@@ -10,6 +10,7 @@ from paper_1105_5481_amd import workloads as wl
 from tests import gpu_util as gu
 
 pytestmark = pytest.mark.gpu
+STATIC = 64 << 20   # bytes of the library's own scratch
 
 
 def _rows(n, cplx, seed):
@@ -59,4 +60,31 @@ def test_csr_rows(n, cplx, R, tpt, prec):
             s.close()
         got = kpm.moments_batched([h, h], [M, M], [R, R], vec, [5, 5], [2, 2])
         assert all(np.array_equal(g.cpu().numpy(), mu) for g in got)
+    h.free()
+
+
+@pytest.mark.parametrize("kind,R,M", [("csr", 71, 75), ("spin", 8, 551), ("real", 2, 62)])
+def test_scratch_limit(kind, R, M):
+    """Solves that fit the static scratch with coarse tiles only: they take those, and run there."""
+    if kind == "csr":
+        n = 103733
+        op = wl.CSR(n=n, row_ptr=np.arange(n + 1, dtype=np.int64), col=((np.arange(n) ^ 1) % n).astype(np.int32),
+                    val_re=np.full(n, 0.5))
+        op.col[-1], op.val_re[-1] = n - 1, 0.25
+    else:
+        L = (353, 731) if kind == "spin" else (890, 1172)
+        N = L[0] * L[1]
+        op = wl.Lattice(dim=2, L=L + (1,), t=1.0, onsite=wl.anderson_onsite(N, 1.0, 3))
+        if kind == "spin":
+            theta, phi = wl.spins_uniform(N, 3)
+            op.hop, op.spinor, op.theta, op.phi = wl.HOP_SPIN, wl.spinor_of(theta, phi), theta, phi
+    vec = wl.VEC_RADEMACHER if kind == "csr" else wl.VEC_PHASE
+    a, b = oracle.scale_from_bounds(*gu.oracle_bounds(op), 0.01)
+    h = kpm.Hamiltonian(op, a, b, kpm.F32)
+    size = h.workspace_bytes(M, R, vec)
+    assert 0.9 * STATIC < size <= STATIC
+    mu = kpm.moments(h, M, R, vec, 5, 2).cpu().numpy()
+    assert np.array_equal(kpm.moments_static(h, M, R, vec, 5, 2).cpu().numpy(), mu)
+    with kpm.launch_settings(tblock=0, elems_per_thread=2):   # one step per launch, other tiles
+        gu.assert_fp32(kpm.moments(h, M, R, vec, 5, 2).cpu().numpy(), mu, "scratch limit")
     h.free()
