@@ -1988,7 +1988,7 @@ namespace {
 // that a solve of one vector leaves half or three quarters empty; as many as keep the
 // state in the Infinity Cache, at most COLS_MAX.  64 sites of a 48^3 spin lattice, FP32,
 // M = 1024: 42.4 ms as 64 solves of one vector, 21.6 ms as one of 64 columns (38.4 us per
-// step, two vector blocks of 113 MB: 8.8 TB/s from the caches).
+// step for 173 MB of streams, and each column's sums through the LDS).
 constexpr int32_t COLS_MAX = 64, COLS_SLOTS = 16;
 struct ColsLayout {
     Plan p;
