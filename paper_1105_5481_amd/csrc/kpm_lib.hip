@@ -695,7 +695,7 @@ bool small_plan(const kpm_ham *h, Plan &p, int32_t M)
 }
 
 constexpr uint32_t CSR_FINE = 1u << 14;
-constexpr uint32_t RUN_PLANES = 4;   // planes a run of short segments covers
+constexpr uint32_t RUN_PLANES = 3;   // planes a run of short segments covers
 
 bool make_plan(const kpm_ham *h, int32_t M, int32_t R, int32_t vec, Plan &p, bool allow_tb = true)
 {
@@ -1591,9 +1591,11 @@ namespace {
 // Runs of the march instances of one launch: short segments (fewer than RUN_PLANES
 // planes) are walked in runs of about that many planes once the launch has more than
 // RUN_BLOCKS blocks without them (4 per CU); below that the blocks are what is missing.
-// us per step of all waves of 256 cubes (L = 16 .. 48, R = 16, FP32) / 128 cubes (16 .. 24)
-// with runs of 1, 4, 6, 8, 12, 16 planes: 711 / 713 / 729 / 740 / 797 / 818 and 93.2 / 90.1 /
-// 93.9 / 93.6 / 98.5 / 103 (segments of 8 planes and whole instances per XCD: 752, 88).
+// us per step of all waves, runs of 1 / 2 / 3 / 4 planes (before: segments of 8 planes or more,
+// whole instances per XCD): 256 cubes L = 16 .. 48, FP32 R = 16 703 / 693 / 690 / 696 (736),
+// R = 8 408 / 394 / 389 / 398 (393), R = 4 215 / 207 / 209 / 221 (232); 254 cubes 20 .. 37,
+// R = 4 150 / 145 / 148 / 152 (152); 100 cubes 16 .. 40, FP64 R = 8 206 / 196 / 191 / 193
+// (211); 128 cubes 16 .. 24, R = 16 95 / 91 / 90 / 93 (85).  Runs of 6 planes and more lose.
 constexpr uint64_t RUN_BLOCKS = 1024;
 void set_runs(std::vector<Inst> &ins)
 {
