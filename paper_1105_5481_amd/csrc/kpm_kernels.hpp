@@ -35,7 +35,7 @@
 // in a fixed order.  Results therefore do not depend on the launch grid or on
 // which other instances share the launch.  The blocks of one instance walk
 // its items per XCD (block b runs on XCD b mod 8 under round-robin dispatch):
-// XCD x owns the x-th eighth of the column tiles (march) or tiles (flat).
+// XCD x owns an eighth of them, as ItemRange says.
 #pragma once
 
 #include <type_traits>
@@ -48,7 +48,7 @@ namespace kpm {
 
 enum OpKind { OP_REAL2 = 0, OP_REAL3 = 1, OP_SPIN2 = 2, OP_SPIN3 = 3, OP_CSR_R = 4, OP_CSR_C = 5, OP_COUNT = 6 };
 enum { VEC_RADEMACHER = 0, VEC_PHASE = 1, VEC_UNIT = 2 };
-enum { MODE_FLAT = 0, MODE_MARCH = 1, MODE_SMALL = 2 };
+enum { MODE_FLAT = 0, MODE_MARCH = 1, MODE_SMALL = 2, MODE_TB = 3, MODE_TB3 = 4 };   // how a solve runs
 constexpr int BLOCK = 256;
 constexpr uint32_t XCD_MIN_ITEMS = 64;   // below this an instance's items are not split per XCD
 constexpr uint32_t NO_INSTANCE = 0xffffffffu;   // block-map entry of an idle block
@@ -477,10 +477,11 @@ __device__ __forceinline__ void reduce_run(const double (&red)[RUN_MAX][BLOCK / 
 // ---------------------------------------------------------------------------
 // mapping of an instance's blocks to its work items
 // ---------------------------------------------------------------------------
-// Work items of this instance handled by the block.  An item is (unit, seg)
-// with unit a column tile (march) or tile (flat).  Local item index it ->
-// seg = sb + it / nu, unit = ub + it % nu, for it = first, first + stride, ...
-// below count.  XCD split (block b runs on XCD b mod 8):
+// Work items of an instance handled by block `block` of the launch.  An item is (unit, seg)
+// with unit a column tile (march), tile (flat) or tile of a blocked pass.  Local item it, for
+// it = first, first + stride, ... below count, is the one that at() names; the kernels and the
+// host check take it from there, so that every split covers every item once.  XCD split (block b
+// runs on XCD b mod 8):
 //   xcd == 2: XCD x owns segments [x*segs/8, (x+1)*segs/8) of every unit, so a
 //             whole plane stays in one L2;
 //   xcd == 1: XCD x owns units [x*units/8, (x+1)*units/8) of every segment;
@@ -488,55 +489,60 @@ __device__ __forceinline__ void reduce_run(const double (&red)[RUN_MAX][BLOCK / 
 //             (equal to one item, whatever the units and segments);
 //   xcd == 4: this table entry covers items [q0, q1) of its instance, in that order;
 //   xcd == 0: no split.
-struct ItemRange {
-    uint32_t first, stride, count, ub, nu, sb, base;
+class ItemRange {
+    uint32_t ub, nu, sb, base;   // first unit, units, first segment; offset in their items
+
+public:
+    uint32_t first, stride, count;
+    __host__ __device__ __forceinline__ ItemRange(const Inst &I, uint32_t block, uint32_t units, uint32_t segs)
+        : ub(0), nu(units), sb(0), base(0)
+    {
+        const uint32_t bl = (block - I.block0) / I.bstride;
+        uint32_t ns = segs;
+        first = bl;
+        stride = I.nb;
+        if (I.xcd == 4) {
+            base = I.q0;
+            count = I.q1 - I.q0;
+            return;
+        }
+        if (I.xcd) {
+            const uint32_t x8 = bl & 7u;
+            first = bl >> 3;
+            stride = I.nb >> 3;
+            if (I.xcd == 3) {
+                const uint64_t all = (uint64_t)units * segs;
+                base = (uint32_t)((all * x8) >> 3);
+                count = (uint32_t)((all * (x8 + 1)) >> 3) - base;
+                return;
+            }
+            if (I.xcd == 2) {
+                sb = (uint32_t)(((uint64_t)segs * x8) >> 3);
+                ns = (uint32_t)(((uint64_t)segs * (x8 + 1)) >> 3) - sb;
+            } else {
+                ub = (uint32_t)(((uint64_t)units * x8) >> 3);
+                nu = (uint32_t)(((uint64_t)units * (x8 + 1)) >> 3) - ub;
+            }
+        }
+        count = nu * ns;
+    }
     // unit and segment of local item `it`
-    __device__ __forceinline__ void at(uint32_t it, uint32_t &unit, uint32_t &sg) const
+    __host__ __device__ __forceinline__ void at(uint32_t it, uint32_t &unit, uint32_t &sg) const
     {
         const uint32_t q = base + it, sl = q / nu;
         sg = sb + sl;
         unit = ub + (q - sl * nu);
     }
 };
-__device__ __forceinline__ ItemRange item_range(const Inst &I, uint32_t units, uint32_t segs)
+// The block's items of an instance of the given mode.  A march item is a run of I.run segments.
+__host__ __device__ __forceinline__ ItemRange item_range(const Inst &I, int mode, uint32_t block)
 {
-    const uint32_t bl = (blockIdx.x - I.block0) / I.bstride;
-    ItemRange r;
-    r.ub = 0;
-    r.nu = units;
-    r.sb = 0;
-    r.base = 0;
-    uint32_t ns = segs;
-    if (I.xcd == 4) {
-        r.first = bl;
-        r.stride = I.nb;
-        r.base = I.q0;
-        r.count = I.q1 - I.q0;
-        return r;
+    switch (mode) {
+    case MODE_MARCH: return ItemRange(I, block, I.nct, (I.nseg + I.run - 1) / I.run);
+    case MODE_TB: return ItemRange(I, block, I.nct * I.tbg, I.nseg);
+    case MODE_TB3: return ItemRange(I, block, I.nct * I.C, I.nseg);
+    default: return ItemRange(I, block, I.tiles, 1);
     }
-    if (I.xcd) {
-        const uint32_t x8 = bl & 7u;
-        r.first = bl >> 3;
-        r.stride = I.nb >> 3;
-        if (I.xcd == 3) {
-            const uint64_t all = (uint64_t)units * segs;
-            r.base = (uint32_t)((all * x8) >> 3);
-            r.count = (uint32_t)((all * (x8 + 1)) >> 3) - r.base;
-            return r;
-        }
-        if (I.xcd == 2) {
-            r.sb = (uint32_t)(((uint64_t)segs * x8) >> 3);
-            ns = (uint32_t)(((uint64_t)segs * (x8 + 1)) >> 3) - r.sb;
-        } else {
-            r.ub = (uint32_t)(((uint64_t)units * x8) >> 3);
-            r.nu = (uint32_t)(((uint64_t)units * (x8 + 1)) >> 3) - r.ub;
-        }
-    } else {
-        r.first = bl;
-        r.stride = I.nb;
-    }
-    r.count = r.nu * ns;
-    return r;
 }
 
 // ---------------------------------------------------------------------------
@@ -663,7 +669,7 @@ __global__ __launch_bounds__(BLOCK) void k_init(const Inst *__restrict__ tab, co
     if (I.step0 != 0) return;
     double *part = I.partial;   // slot 0
     if (I.mode == MODE_MARCH) {
-        const ItemRange ir = item_range(I, I.nct, (I.nseg + I.run - 1) / I.run);
+        const ItemRange ir = item_range(I, MODE_MARCH, blockIdx.x);
         const uint32_t PC = I.P * I.C;
         for (uint32_t it = ir.first; it < ir.count; it += ir.stride) {
             uint32_t ct, rn;
@@ -685,9 +691,10 @@ __global__ __launch_bounds__(BLOCK) void k_init(const Inst *__restrict__ tab, co
             }
         }
     } else {
-        const ItemRange ir = item_range(I, I.tiles, 1);
+        const ItemRange ir = item_range(I, MODE_FLAT, blockIdx.x);
         for (uint32_t it = ir.first; it < ir.count; it += ir.stride) {
-            const uint32_t t = ir.ub + it;
+            uint32_t t, sg;
+            ir.at(it, t, sg);
             Dots<S> acc;
             for (int u = 0; u < I.tpt; ++u) {
                 const uint32_t e = t * (uint32_t)(BLOCK * I.tpt) + (uint32_t)(u * BLOCK) + threadIdx.x;
@@ -809,7 +816,7 @@ __global__ __launch_bounds__(BLOCK) void k_step_march(const Inst *__restrict__ t
     // a thread's sums of the even segment of a pair, reduced with the odd one's (in the LDS:
     // four more VGPRs would cost the FP32 3D spin kernel one of its 7 waves per SIMD)
     __shared__ double held[COLS ? ColDots<S, SPIN>::NV * ColDots<S, SPIN>::V1 : Dots<S>::NV][BLOCK];
-    const ItemRange ir = item_range(I, I.nct, (I.nseg + I.run - 1) / I.run);
+    const ItemRange ir = item_range(I, MODE_MARCH, blockIdx.x);
     for (uint32_t it = ir.first; it < ir.count; it += ir.stride) {
         uint32_t ct, rn;
         ir.at(it, ct, rn);
@@ -1046,9 +1053,10 @@ __global__ __launch_bounds__(BLOCK) void k_step_flat(const Inst *__restrict__ ta
     S hop = 0;
     if (OPK == OP_REAL2 || OPK == OP_REAL3) hop = Mem<S, WIDE>::lds(I.hop, 0);
     double *part = I.partial + (size_t)((n + 1) % I.pslots) * I.tiles * 4;
-    const ItemRange ir = item_range(I, I.tiles, 1);
+    const ItemRange ir = item_range(I, MODE_FLAT, blockIdx.x);
     for (uint32_t it = ir.first; it < ir.count; it += ir.stride) {
-        const uint32_t t = ir.ub + it;
+        uint32_t t, sg;
+        ir.at(it, t, sg);
         Dots<S> acc;
         for (int u = 0; u < I.tpt; ++u) {
             const uint32_t e = t * (uint32_t)(BLOCK * I.tpt) + (uint32_t)(u * BLOCK) + threadIdx.x;

@@ -1583,39 +1583,16 @@ namespace {
 // the per-block map (instance index within the group, NO_INSTANCE for idle
 // blocks); returns the grid size.
 //
-// wave = true: with at least 8 instances, one-step march instances are balanced
-// whole over the XCDs even where their own plan would split them, with 25% slack
-// over the even share before one is split.  The march instances of a static
-// batch, for which this was, are placed by place_even below, so only its flat
-// instances come here with it (their work is split as above, with that slack).
-// Runs of the march instances of one launch: short segments (fewer than RUN_PLANES
-// planes) are walked in runs of about that many planes once the launch has more than
-// RUN_BLOCKS blocks without them (4 per CU); below that the blocks are what is missing.
-// us per step of all waves, runs of 1 / 2 / 3 / 4 planes (before: segments of 8 planes or more,
-// whole instances per XCD): 256 cubes L = 16 .. 48, FP32 R = 16 703 / 693 / 690 / 696 (736),
-// R = 8 408 / 394 / 389 / 398 (393), R = 4 215 / 207 / 209 / 221 (232); 254 cubes 20 .. 37,
-// R = 4 150 / 145 / 148 / 152 (152); 100 cubes 16 .. 40, FP64 R = 8 206 / 196 / 191 / 193
-// (211); 128 cubes 16 .. 24, R = 16 95 / 91 / 90 / 93 (85).  Runs of 6 planes and more lose.
-constexpr uint64_t RUN_BLOCKS = 1024;
-void set_runs(std::vector<Inst> &ins)
-{
-    uint64_t blocks = 0;
-    for (const Inst &I : ins) blocks += I.nb;
-    for (Inst &I : ins) {
-        I.run = 1;
-        if (I.mode != MODE_MARCH || I.S >= RUN_PLANES || blocks <= RUN_BLOCKS) continue;
-        I.run = (uint32_t)std::min<uint64_t>({RUN_PLANES / I.S, RUN_MAX, (blocks + RUN_BLOCKS - 1) / RUN_BLOCKS});
-        const uint32_t items = I.nct * ((I.nseg + I.run - 1) / I.run);
-        I.nb = std::min<uint32_t>(I.nb, (items + 7) / 8 * 8);
-    }
-}
-
+// slack: by how much an XCD may exceed the even share before an instance is split: 25%
+// for the flat instances of a static batch (its march instances are placed by place_even),
+// 10% for a dynamic batch, whose few members differ widely in size.
+constexpr double SLACK_STATIC = 1.25, SLACK_DYNAMIC = 1.10;
 constexpr uint32_t SPLIT_MIN_UNITS = 48;   // below this a split leaves too few units per XCD (halo re-fetch)
-uint32_t place_blocks(std::vector<Inst> &ins, std::vector<uint32_t> &map, bool wave = false)
+uint32_t place_blocks(std::vector<Inst> &ins, std::vector<uint32_t> &map, double slack)
 {
     std::vector<uint32_t> big, small;
     for (uint32_t r = 0; r < ins.size(); ++r)
-        ((wave && ins.size() >= 8 && ins[r].mode == MODE_MARCH) || !ins[r].xcd ? small : big).push_back(r);
+        (!ins[r].xcd ? small : big).push_back(r);
     if (small.size() < 8) {
         big.insert(big.end(), small.begin(), small.end());
         std::sort(big.begin(), big.end());
@@ -1631,7 +1608,7 @@ uint32_t place_blocks(std::vector<Inst> &ins, std::vector<uint32_t> &map, bool w
     std::stable_sort(small.begin(), small.end(), [&](uint32_t a, uint32_t b) { return cost(a) > cost(b); });
     uint64_t total = 0;
     for (uint32_t r : small) total += cost(r);
-    const double share = (double)total / 8.0 * (wave ? 1.25 : 1.10);
+    const double share = (double)total / 8.0 * slack;
     uint64_t load[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     uint32_t used[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     std::vector<uint32_t> whole, xcd_of;
@@ -1672,6 +1649,28 @@ uint32_t place_blocks(std::vector<Inst> &ins, std::vector<uint32_t> &map, bool w
         off[x] += I.nb;
     }
     return blocks + 8 * span;
+}
+
+// Runs of the march instances of one launch: short segments (fewer than RUN_PLANES
+// planes) are walked in runs of about that many planes once the launch has more than
+// RUN_BLOCKS blocks without them (4 per CU); below that the blocks are what is missing.
+// us per step of all waves, runs of 1 / 2 / 3 / 4 planes (before: segments of 8 planes or more,
+// whole instances per XCD): 256 cubes L = 16 .. 48, FP32 R = 16 703 / 693 / 690 / 696 (736),
+// R = 8 408 / 394 / 389 / 398 (393), R = 4 215 / 207 / 209 / 221 (232); 254 cubes 20 .. 37,
+// R = 4 150 / 145 / 148 / 152 (152); 100 cubes 16 .. 40, FP64 R = 8 206 / 196 / 191 / 193
+// (211); 128 cubes 16 .. 24, R = 16 95 / 91 / 90 / 93 (85).  Runs of 6 planes and more lose.
+constexpr uint64_t RUN_BLOCKS = 1024;
+void set_runs(std::vector<Inst> &ins)
+{
+    uint64_t blocks = 0;
+    for (const Inst &I : ins) blocks += I.nb;
+    for (Inst &I : ins) {
+        I.run = 1;
+        if (I.mode != MODE_MARCH || I.S >= RUN_PLANES || blocks <= RUN_BLOCKS) continue;
+        I.run = (uint32_t)std::min<uint64_t>({RUN_PLANES / I.S, RUN_MAX, (blocks + RUN_BLOCKS - 1) / RUN_BLOCKS});
+        const uint32_t items = I.nct * ((I.nseg + I.run - 1) / I.run);
+        I.nb = std::min<uint32_t>(I.nb, (items + 7) / 8 * 8);
+    }
 }
 
 // Even placement of the march instances of one wave of a static batch: the items of
@@ -1717,18 +1716,23 @@ uint32_t place_even(const std::vector<Inst> &ins, std::vector<Inst> &pieces, Eve
     for (uint32_t y = 0; y < 8; ++y) em.span = std::max(em.span, em.used[y]);
     return 8 * em.span;
 }
-// The block map of place_even's pieces, written on the device: block p < count fills
-// entry p's blocks, the last one marks the idle blocks.
+// Thread t of nt of share `p` of the block map of place_even's pieces: p < count fills entry p's
+// blocks, p = count marks the idle ones.
+__host__ __device__ inline void fill_map(const Inst *pieces, uint32_t count, const EvenMap &em, uint32_t *map, uint32_t p,
+                                         uint32_t t, uint32_t nt)
+{
+    if (p < count) {
+        const uint32_t nb = pieces[p].nb, b0 = pieces[p].block0;
+        for (uint32_t j = t; j < nb; j += nt) map[b0 + 8 * j] = p;
+    } else {
+        for (uint32_t y = 0; y < 8; ++y)
+            for (uint32_t j = em.used[y] + t; j < em.span; j += nt) map[y + 8 * j] = NO_INSTANCE;
+    }
+}
 __global__ __launch_bounds__(256) void k_fill_map(const Inst *__restrict__ pieces, uint32_t count, EvenMap em,
                                                   uint32_t *__restrict__ map)
 {
-    if (blockIdx.x < count) {
-        const uint32_t nb = pieces[blockIdx.x].nb, b0 = pieces[blockIdx.x].block0;
-        for (uint32_t j = threadIdx.x; j < nb; j += 256) map[b0 + 8 * j] = blockIdx.x;
-    } else {
-        for (uint32_t y = 0; y < 8; ++y)
-            for (uint32_t j = em.used[y] + threadIdx.x; j < em.span; j += 256) map[y + 8 * j] = NO_INSTANCE;
-    }
+    fill_map(pieces, count, em, map, blockIdx.x, threadIdx.x, 256);
 }
 }  // namespace
 namespace {
@@ -1814,7 +1818,7 @@ void add_groups(kpm_ham *const *h, const std::vector<int> &ids, BatchLayout &L, 
                 L.map_words += g.blocks;
             } else {
                 std::vector<uint32_t> m;
-                g.blocks = place_blocks(ins, m, true);
+                g.blocks = place_blocks(ins, m, SLACK_STATIC);
                 L.map_words += m.size();
             }
         }
@@ -1929,7 +1933,7 @@ kpm_status kpm_moments_batched(kpm_ham *const *h, int32_t count, const int32_t *
             if (pieces.size() != g->pfirst || place_even(ins, pieces, maps[q]) != g->blocks) return KPM_ERR_INVALID_ARG;
         } else {
             std::vector<uint32_t> map;
-            if (place_blocks(ins, map, true) != g->blocks) return KPM_ERR_INVALID_ARG;
+            if (place_blocks(ins, map, SLACK_STATIC) != g->blocks) return KPM_ERR_INVALID_ARG;
             std::copy(ins.begin(), ins.end(), tab.begin() + g->first);
             e = upload(map_dev + g->map_off, map.data(), map.size() * 4, st);
         }
@@ -2249,7 +2253,7 @@ kpm_status kpm_batch_advance(kpm_batch *b, int32_t steps, void *stream)
         }
         g.count = (uint32_t)ins.size();
         set_runs(ins);
-        if (g.mode != MODE_SMALL) g.blocks = place_blocks(ins, map);
+        if (g.mode != MODE_SMALL) g.blocks = place_blocks(ins, map, SLACK_DYNAMIC);
         tab.insert(tab.end(), ins.begin(), ins.end());
         groups.push_back(g);
     }
@@ -2700,12 +2704,12 @@ int32_t kpm_selftest_fastdiv(uint32_t d, const uint32_t *n, int32_t count)
 }
 
 // Host check of the block placement of one launch group: nb[i] blocks, the
-// XCD split flag xcd[i] (updated: 1 for instances the placement split, 0 for
+// XCD split flag xcd[i] (updated: 3 for instances the placement split, 0 for
 // those it placed whole) and, optionally, units[i] work units of instance i
-// (NULL: none).  wave = 0: flat instances of a dynamic batch; 1: march
-// instances of a static batch wave.  Writes block0/bstride per instance and the
-// per-block map (up to map_cap entries); returns the grid size, or -1 if the
-// map does not fit.
+// (NULL: none).  wave = 0: the slack of a dynamic batch; 1: that of a static one,
+// and with eight instances or more none comes with a split of its own.  Writes
+// block0/bstride per instance and the per-block map (up to map_cap entries);
+// returns the grid size, or -1 if the map does not fit.
 int64_t kpm_selftest_placement(const uint32_t *nb, int32_t *xcd, const uint32_t *units, int32_t count, int32_t wave,
                                uint32_t *block0, uint32_t *bstride, uint32_t *map_out, int64_t map_cap)
 {
@@ -2714,13 +2718,12 @@ int64_t kpm_selftest_placement(const uint32_t *nb, int32_t *xcd, const uint32_t 
     for (int32_t i = 0; i < count; ++i) {
         std::memset(&ins[i], 0, sizeof(Inst));
         ins[i].nb = nb[i];
-        ins[i].xcd = xcd[i];
-        ins[i].mode = wave ? MODE_MARCH : MODE_FLAT;
+        ins[i].xcd = wave && count >= 8 ? 0 : xcd[i];
+        ins[i].mode = MODE_FLAT;
         ins[i].tiles = units ? units[i] : 0;
-        ins[i].nct = units ? units[i] : 0;
     }
     std::vector<uint32_t> map;
-    const uint32_t blocks = place_blocks(ins, map, wave != 0);
+    const uint32_t blocks = place_blocks(ins, map, wave ? SLACK_STATIC : SLACK_DYNAMIC);
     if ((int64_t)map.size() > map_cap || map.size() != blocks) return -1;
     for (int32_t i = 0; i < count; ++i) {
         block0[i] = ins[i].block0;
@@ -2729,6 +2732,74 @@ int64_t kpm_selftest_placement(const uint32_t *nb, int32_t *xcd, const uint32_t 
     }
     std::copy(map.begin(), map.end(), map_out);
     return blocks;
+}
+
+// Host check of the work items of one launch group of `count` instances of one mode (0 flat, 1 march,
+// 3 and 4 blocked passes), as the kernels take them: units[i] x segs[i] items (segs 1 for flat),
+// planes[i] planes per march segment, nb[i] blocks, split flag xcd[i].  static_wave: placed as a
+// static batch places them, else as a dynamic one (xcd[i] is then updated to the placement's).  Returns the number of
+// items (march: segments) not run exactly once by the blocks of the grid, or -1.
+int64_t kpm_selftest_items(int32_t mode, int32_t static_wave, int32_t count, const uint32_t *units, const uint32_t *segs,
+                           const uint32_t *planes, const uint32_t *nb, int32_t *xcd)
+{
+    if (count < 1 || !units || !segs || !planes || !nb || !xcd) return -1;
+    std::vector<Inst> ins(count);
+    std::vector<std::vector<uint32_t>> runs(count);
+    for (int32_t i = 0; i < count; ++i) {
+        Inst &I = ins[i];
+        std::memset(&I, 0, sizeof(Inst));
+        I.mode = mode;
+        I.nb = nb[i];
+        I.xcd = xcd[i];
+        I.nct = units[i];
+        I.nseg = segs[i];
+        I.tiles = units[i] * segs[i];
+        I.S = planes[i];
+        I.run = I.C = I.tbg = 1;
+        I.nel = I.tiles * planes[i] * (uint32_t)BLOCK;
+        runs[i].assign(I.tiles, 0);
+    }
+    set_runs(ins);
+    std::vector<Inst> table;
+    std::vector<uint32_t> map;
+    std::vector<int32_t> of;   // instance of a table entry
+    if (static_wave && mode == MODE_MARCH) {
+        EvenMap em;
+        map.assign(place_even(ins, table, em), NO_INSTANCE - 1);   // unwritten entries stand out
+        for (uint32_t p = 0; p <= table.size(); ++p) fill_map(table.data(), (uint32_t)table.size(), em, map.data(), p, 0, 1);
+        // pieces come in table order, an instance's ranges one after the other
+        int32_t i = -1;
+        for (const Inst &P : table) {
+            if (P.q0 == 0) ++i;
+            of.push_back(i);
+        }
+    } else {
+        place_blocks(ins, map, static_wave ? SLACK_STATIC : SLACK_DYNAMIC);
+        table = ins;
+        for (int32_t i = 0; i < count; ++i) {
+            of.push_back(i);
+            xcd[i] = ins[i].xcd;
+        }
+    }
+    int64_t bad = 0;
+    for (uint32_t b = 0; b < map.size(); ++b) {
+        if (map[b] == NO_INSTANCE) continue;
+        if (map[b] >= table.size() || of[map[b]] < 0 || of[map[b]] >= count) return -1;
+        const Inst &I = table[map[b]];
+        std::vector<uint32_t> &run = runs[of[map[b]]];
+        const ItemRange ir = item_range(I, mode, b);
+        for (uint32_t it = ir.first; it < ir.count; it += ir.stride) {
+            uint32_t unit, r;
+            ir.at(it, unit, r);
+            for (uint32_t sg = r * I.run; sg < std::min((r + 1) * I.run, I.nseg); ++sg) {
+                if (unit >= I.nct || (size_t)sg * I.nct + unit >= run.size()) ++bad;
+                else ++run[(size_t)sg * I.nct + unit];
+            }
+        }
+    }
+    for (const auto &v : runs)
+        for (uint32_t n : v) bad += n != 1;
+    return bad;
 }
 
 }  // extern "C"

@@ -22,7 +22,6 @@ namespace kpm {
 
 constexpr uint32_t TB_BLOCK = 256;
 constexpr int TB_DMAX = 6;   // deepest pass
-constexpr int MODE_TB = 3;   // plan mode of solves run by these kernels
 // Blocks per CU (= waves per SIMD) a pass is held to: the VGPR budget is 512 over this
 // (FP32 four steps 118 of 128, six 152 of 168; FP64 five 165 real, 176 spin, six 194),
 // and its D levels of 8 KiB LDS fit as often.  Blocks of 256 threads: of 512, two per
@@ -101,7 +100,7 @@ __global__ __launch_bounds__(TB_BLOCK) void k_init_tb(const Inst *__restrict__ t
     const uint32_t C = I.C, Gs = I.tbg, Cg = I.tbw, Lx = I.P, Ly = I.Lm;
     const uint32_t h = (uint32_t)I.tbh, Wn = TB_BLOCK / Cg, Tn = Wn - 2 * h;
     const uint32_t tid = threadIdx.x, s = tid / Cg, ct = tid - s * Cg;
-    const ItemRange ir = item_range(I, I.nct * Gs, I.nseg);
+    const ItemRange ir = item_range(I, MODE_TB, blockIdx.x);
     for (uint32_t it = ir.first; it < ir.count; it += ir.stride) {
         uint32_t unit, sg;
         ir.at(it, unit, sg);
@@ -163,7 +162,7 @@ __global__ __launch_bounds__(TB_BLOCK) __attribute__((amdgpu_waves_per_eu(TB_WAV
     const bool first = (n == 0);
     const T zero = (T)(S)0;
     const T two = (T)(S)2;
-    const ItemRange ir = item_range(I, I.nct * Gs, I.nseg);
+    const ItemRange ir = item_range(I, MODE_TB, blockIdx.x);
     for (uint32_t it = ir.first; it < ir.count; it += ir.stride) {
         uint32_t unit, sg;
         ir.at(it, unit, sg);

@@ -34,7 +34,6 @@ namespace kpm {
 constexpr int TB3_BLOCK = 512;
 constexpr int TB3_EPT = 2;                                  // tile elements per thread
 constexpr uint32_t TB3_TILE = (uint32_t)TB3_BLOCK * TB3_EPT;  // elements (sites x one chunk) per tile
-constexpr int MODE_TB3 = 4;                                 // plan mode of solves run by these kernels
 
 // Geometry of one work item of a 3D blocked solve (Inst: P = owned rows per
 // tile T, nct = row tiles per plane, Lm = L_z, S = planes per segment).
@@ -101,7 +100,7 @@ __global__ __launch_bounds__(TB3_BLOCK) void k_init_tb3(const Inst *__restrict__
     typedef Mem<S, WIDE> G;
     const Inst I = tab[0];
     const uint32_t N = I.N, P = I.Lx * I.Ly;
-    const ItemRange ir = item_range(I, I.C * I.nct, I.nseg);
+    const ItemRange ir = item_range(I, MODE_TB3, blockIdx.x);
     for (uint32_t it = ir.first; it < ir.count; it += ir.stride) {
         uint32_t unit, sg;
         ir.at(it, unit, sg);
@@ -148,7 +147,7 @@ __global__ __launch_bounds__(TB3_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) 
     const bool hd = I.has_diag;
     const S hop = SPIN ? (S)0 : G::lds(I.hop, 0);
     const T zero = (T)(S)0;
-    const ItemRange ir = item_range(I, I.C * I.nct, I.nseg);
+    const ItemRange ir = item_range(I, MODE_TB3, blockIdx.x);
     for (uint32_t it = ir.first; it < ir.count; it += ir.stride) {
         uint32_t unit, sg;
         ir.at(it, unit, sg);
