@@ -53,7 +53,7 @@ __global__ __launch_bounds__(256) void k_dense_init(uint32_t D, uint32_t Dp, uin
 {
     const uint32_t tiles_r = Rp / tn;
     const uint32_t i0 = (blockIdx.x / tiles_r) * DN_TILE, r0 = (blockIdx.x % tiles_r) * tn;
-    double s = DOT_BIAS, c = 0.0;
+    double s = 0.0, c = 0.0;
     for (uint32_t q = threadIdx.x; q < DN_TILE * tn; q += 256) {
         const uint32_t i = i0 + q / tn, r = r0 + q % tn;
         double re = 0.0, im = 0.0;
@@ -63,9 +63,9 @@ __global__ __launch_bounds__(256) void k_dense_init(uint32_t D, uint32_t Dp, uin
             start_value(vec, w[r & 3], instance, D, i, r, re, im);
         }
         V[(uint64_t)i * Rp + r] = re;
-        dot2_acc_biased(s, c, re, re);
+        dot2_acc(s, c, re, re);
     }
-    block_reduce_store<true>(s - DOT_BIAS, c, 0.0, 0.0, part + (size_t)blockIdx.x * 4);
+    block_reduce_store<true>(s, c, 0.0, 0.0, part + (size_t)blockIdx.x * 4);
 }
 
 // One recursion step: next = H~ cur (FIRST) or 2 H~ cur - next, and the
@@ -150,7 +150,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
         }
         __syncthreads();
     }
-    double s0 = DOT_BIAS, c0 = 0.0, s1 = DOT_BIAS, c1 = 0.0;
+    double s0 = 0.0, c0 = 0.0, s1 = 0.0, c1 = 0.0;
 #pragma unroll
     for (int p = 0; p < NP; ++p)
 #pragma unroll
@@ -163,10 +163,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
                 double out = acc[p][q][v];
                 if (!FIRST) out = 2.0 * out - next[o];
                 next[o] = out;
-                dot2_acc_biased(s0, c0, out, out);
-                dot2_acc_biased(s1, c1, out, cur[o]);
+                dot2_acc(s0, c0, out, out);
+                dot2_acc(s1, c1, out, cur[o]);
             }
-    block_reduce_store<true>(s0 - DOT_BIAS, c0, s1 - DOT_BIAS, c1, part + (size_t)blockIdx.x * 4);
+    block_reduce_store<true>(s0, c0, s1, c1, part + (size_t)blockIdx.x * 4);
 }
 
 // ---------------------------------------------------------------------------
@@ -201,7 +201,7 @@ __global__ __launch_bounds__(64 * NW) void k_dense_resident(const double *__rest
 #pragma unroll
     for (uint32_t s = 0; s < Dp / 4; ++s) ha[s] = Ht[(4 * s + lk) * Dp + 16 * w + lr];
     double cur[4], prev[4] = {0.0, 0.0, 0.0, 0.0};
-    double s0 = DOT_BIAS, e0 = 0.0;
+    double s0 = 0.0, e0 = 0.0;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         const uint32_t i = 16 * w + 4 * v + lk;
@@ -213,10 +213,10 @@ __global__ __launch_bounds__(64 * NW) void k_dense_resident(const double *__rest
         }
         cur[v] = re;
         Vs[i * 16 + lr] = re;
-        dot2_acc_biased(s0, e0, re, re);
+        dot2_acc(s0, e0, re, re);
     }
     const size_t wslot = (size_t)blockIdx.x * NW + w;   // this wave's partial within a slot
-    wave_reduce_store<true, true>(s0 - DOT_BIAS, e0, 0.0, 0.0, part + wslot * 4);
+    wave_reduce_store<true>(s0, e0, 0.0, 0.0, part + wslot * 4);
     __syncthreads();
     for (int32_t n = 0; n < K; ++n) {
         dn_d4 acc[4];
@@ -231,18 +231,23 @@ __global__ __launch_bounds__(64 * NW) void k_dense_resident(const double *__rest
             }
         }
         __syncthreads();   // every wave has read the slab of r_n
-        double x0 = DOT_BIAS, y0 = 0.0, x1 = DOT_BIAS, y1 = 0.0;
+        double x0 = 0.0, y0 = 0.0, x1 = 0.0, y1 = 0.0;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             double out = (acc[0][v] + acc[1][v]) + (acc[2][v] + acc[3][v]);
             if (n > 0) out = 2.0 * out - prev[v];
-            dot2_acc_biased(x0, y0, out, out);
-            dot2_acc_biased(x1, y1, out, cur[v]);
+            if (v == 0) {
+                dot2_first(x0, y0, out, out);
+                dot2_first(x1, y1, out, cur[v]);
+            } else {
+                dot2_acc(x0, y0, out, out);
+                dot2_acc(x1, y1, out, cur[v]);
+            }
             prev[v] = cur[v];
             cur[v] = out;
             Vs[(16 * w + 4 * v + lk) * 16 + lr] = out;
         }
-        wave_reduce_store<true, true>(x0 - DOT_BIAS, y0, x1 - DOT_BIAS, y1, part + ((size_t)(n + 1) * nblk * NW + wslot) * 4);
+        wave_reduce_store<true>(x0, y0, x1, y1, part + ((size_t)(n + 1) * nblk * NW + wslot) * 4);
         __syncthreads();   // the slab of r_{n+1} is complete
     }
 }

@@ -121,37 +121,30 @@ __device__ __forceinline__ dd dd_add(dd x, dd y)
     s.lo += t.lo;
     return dd_fast_two_sum(s.hi, s.lo);
 }
-// x + y for sums of many terms: the rounded sum and, unnormalised, all errors so far
-// (summed in FP64, so the result is off by 2^-106 of the largest term).  8 operations;
-// dd_add takes 20.
+// x + y inside sums of many terms, in 11 operations (dd_add takes 20): off by about 2^-106 of
+// the larger term rather than of the sum, which is what the terms themselves are off by.
+// Over trees and runs of partials its error is that of dd_add (random products of any size and
+// sign, 2^-106 of their absolute sum for both); left unnormalised it is up to 2.8 times as much.
 __device__ __forceinline__ dd dd_sum(dd x, dd y)
 {
     const dd s = dd_two_sum(x.hi, y.hi);
-    return dd{s.hi, s.lo + (x.lo + y.lo)};
+    return dd_fast_two_sum(s.hi, s.lo + (x.lo + y.lo));
 }
-// (s, c) += x*y exactly up to the error term c, which is summed in FP64.
+// (s, c) += x*y exactly up to the error term c, which is summed in FP64.  The two-sum of s and
+// the rounded product p gives s + p = t + (s - (t - v)) + (p - v); the product's own error is
+// taken in with the last term, (p - v) + (x*y - p) = x*y - v in one fma.
 __device__ __forceinline__ void dot2_acc(double &s, double &c, double x, double y)
 {
-    double p = x * y;
-    double pe = fma(x, y, -p);
-    double t = s + p;
-    double v = t - s;
-    double e = (s - (t - v)) + (p - v);
+    const double t = s + x * y;
+    const double v = t - s;
+    c += (s - (t - v)) + fma(x, y, -v);
     s = t;
-    c += e + pe;
 }
-// The same in four operations, for sums that start at s = DOT_BIAS and products
-// smaller than s: then t - s, of t = s + x*y rounded once, is exact and x*y - (t - s)
-// is the whole rounding error.  The factors summed here are components of T_n(H~) xi
-// with |T_n| <= 1 and |xi_i| <= 1, so products stay near 1 and a thread's sum far
-// above -DOT_BIAS; the bias costs 2^-106 DOT_BIAS (1e-27) per product.  Larger
-// products (a scale that does not enclose the spectrum) are summed to FP64 accuracy.
-constexpr double DOT_BIAS = 98304.0;   // 1.5 * 2^16
-__device__ __forceinline__ void dot2_acc_biased(double &s, double &c, double x, double y)
+// The first product of a sum.
+__device__ __forceinline__ void dot2_first(double &s, double &c, double x, double y)
 {
-    const double t = fma(x, y, s);
-    c += fma(x, y, s - t);
-    s = t;
+    s = x * y;
+    c = fma(x, y, -s);
 }
 __device__ __forceinline__ dd dd_div_d(dd x, double b)
 {

@@ -193,13 +193,12 @@ template <typename T> __device__ __forceinline__ T two_minus(T v, T w)
     return __builtin_elementwise_fma((T)(2), v, -w);
 }
 
-// Dot-product accumulators: (sum, error) pairs in FP64 for FP64 vectors, started at
-// DOT_BIAS (four operations per product instead of ten); for FP32 vectors the
-// products are exact in FP64 and a plain FP64 sum suffices.  (x0 + x1, x2 + x3) are
-// the two sums.
+// Dot-product accumulators: (sum, error) pairs in FP64 for FP64 vectors; for
+// FP32 vectors the products are exact in FP64 and a plain FP64 sum suffices.
+// (x0 + x1, x2 + x3) are the two sums.
 template <typename S> struct Dots;
 template <> struct Dots<double> {
-    double s0 = DOT_BIAS, c0 = 0.0, s1 = DOT_BIAS, c1 = 0.0;
+    double s0 = 0.0, c0 = 0.0, s1 = 0.0, c1 = 0.0;
     static constexpr int NV = 4;   // values save() keeps
     __device__ __forceinline__ Dots() {}
     __device__ __forceinline__ explicit Dots(const double (&h)[NV][BLOCK])
@@ -215,18 +214,30 @@ template <> struct Dots<double> {
     {
 #pragma unroll
         for (int l = 0; l < 2; ++l) {
-            dot2_acc_biased(s0, c0, o[l], o[l]);
-            dot2_acc_biased(s1, c1, o[l], v[l]);
+            dot2_acc(s0, c0, o[l], o[l]);
+            dot2_acc(s1, c1, o[l], v[l]);
         }
+    }
+    __device__ __forceinline__ void first(V16<double>::T o, V16<double>::T v)   // add() to empty sums
+    {
+        dot2_first(s0, c0, o[0], o[0]);
+        dot2_first(s1, c1, o[0], v[0]);
+        dot2_acc(s0, c0, o[1], o[1]);
+        dot2_acc(s1, c1, o[1], v[1]);
     }
     __device__ __forceinline__ void norm_only(V16<double>::T o)
     {
 #pragma unroll
-        for (int l = 0; l < 2; ++l) dot2_acc_biased(s0, c0, o[l], o[l]);
+        for (int l = 0; l < 2; ++l) dot2_acc(s0, c0, o[l], o[l]);
     }
-    __device__ __forceinline__ double x0() const { return s0 - DOT_BIAS; }
+    __device__ __forceinline__ void cross_only(V16<double>::T o, V16<double>::T v)
+    {
+#pragma unroll
+        for (int l = 0; l < 2; ++l) dot2_acc(s1, c1, o[l], v[l]);
+    }
+    __device__ __forceinline__ double x0() const { return s0; }
     __device__ __forceinline__ double x1() const { return c0; }
-    __device__ __forceinline__ double x2() const { return s1 - DOT_BIAS; }
+    __device__ __forceinline__ double x2() const { return s1; }
     __device__ __forceinline__ double x3() const { return c1; }
     static constexpr bool DD = true;
 };
@@ -249,6 +260,7 @@ template <> struct Dots<float> {
             s1 = fma(a, (double)v[l], s1);
         }
     }
+    __device__ __forceinline__ void first(V16<float>::T o, V16<float>::T v) { add(o, v); }
     __device__ __forceinline__ void norm_only(V16<float>::T o)
     {
 #pragma unroll
@@ -289,8 +301,8 @@ template <bool CPLX> struct ColDots<double, CPLX> {
 #pragma unroll
         for (int l = 0; l < 2; ++l) {
             Dots<double> &a = d[CPLX ? 0 : l];
-            dot2_acc_biased(a.s0, a.c0, o[l], o[l]);
-            dot2_acc_biased(a.s1, a.c1, o[l], v[l]);
+            dot2_acc(a.s0, a.c0, o[l], o[l]);
+            dot2_acc(a.s1, a.c1, o[l], v[l]);
         }
     }
     __device__ __forceinline__ double value(int k) const
@@ -300,57 +312,28 @@ template <bool CPLX> struct ColDots<double, CPLX> {
     }
 };
 
-// FP64 sums of any magnitude (vectors that are not near 1): ten operations per product.
-struct DotsWide {
-    double s0 = 0.0, c0 = 0.0, s1 = 0.0, c1 = 0.0;
-    __device__ __forceinline__ void dot(V16<double>::T o, V16<double>::T v)
-    {
-#pragma unroll
-        for (int l = 0; l < 2; ++l) dot2_acc(s1, c1, o[l], v[l]);
-    }
-    __device__ __forceinline__ void norm_only(V16<double>::T o)
-    {
-#pragma unroll
-        for (int l = 0; l < 2; ++l) dot2_acc(s0, c0, o[l], o[l]);
-    }
-    __device__ __forceinline__ double x0() const { return s0; }
-    __device__ __forceinline__ double x1() const { return c0; }
-    __device__ __forceinline__ double x2() const { return s1; }
-    __device__ __forceinline__ double x3() const { return c1; }
-    static constexpr bool DD = true;
-};
-
-// Sum of two double-doubles inside a reduction.  FEW: both high parts are multiples of
-// 2^-36 (the last bit of DOT_BIAS) below 2^17, as sums of up to some ten thousand biased
-// products are, so their plain sum is exact.
-template <bool FEW> __device__ __forceinline__ dd dd_part(dd x, dd y)
-{
-    if (FEW) return dd{x.hi + y.hi, x.lo + y.lo};
-    return dd_sum(x, y);
-}
-
 // Sums of x0 + x1 and x2 + x3 over the wavefront, in (a, b): the lower 32 lanes
 // receive the first, the upper 32 the second (as a double-double when DD, else in a
 // alone).  The first exchange gives each half of the wave one of the two sums, so a
-// reduction is six additions of 8 operations, and no exchange goes through the LDS: with
+// reduction is six additions of 11 operations, and no exchange goes through the LDS: with
 // ds_bpermute shuffles of both sums it was twelve of 20 and 48 shuffles of 24 cycles, most
 // of a step of the single-workgroup solves.
-template <bool DD, bool FEW = false>
+template <bool DD>
 __device__ __forceinline__ void wave_reduce(double x0, double x1, double x2, double x3, double &a, double &b)
 {
     if (DD) {
         dd p{x0, x1}, q{x2, x3};
         swap_halves(p.hi, q.hi);
         swap_halves(p.lo, q.lo);
-        p = dd_part<FEW>(p, q);
+        p = dd_sum(p, q);
         q = p;
         swap_rows(p.hi, q.hi);
         swap_rows(p.lo, q.lo);
-        p = dd_part<FEW>(p, q);
-        p = dd_part<FEW>(p, dd{row_ror<8>(p.hi), row_ror<8>(p.lo)});
-        p = dd_part<FEW>(p, dd{row_ror<4>(p.hi), row_ror<4>(p.lo)});
-        p = dd_part<FEW>(p, dd{row_ror<2>(p.hi), row_ror<2>(p.lo)});
-        p = dd_part<FEW>(p, dd{row_ror<1>(p.hi), row_ror<1>(p.lo)});
+        p = dd_sum(p, q);
+        p = dd_sum(p, dd{row_ror<8>(p.hi), row_ror<8>(p.lo)});
+        p = dd_sum(p, dd{row_ror<4>(p.hi), row_ror<4>(p.lo)});
+        p = dd_sum(p, dd{row_ror<2>(p.hi), row_ror<2>(p.lo)});
+        p = dd_sum(p, dd{row_ror<1>(p.hi), row_ror<1>(p.lo)});
         a = p.hi;
         b = p.lo;
     } else {
@@ -368,26 +351,26 @@ __device__ __forceinline__ void wave_reduce(double x0, double x1, double x2, dou
 }
 
 // The wavefront's sums of (x0 + x1, x2 + x3), stored as four doubles (hi, lo, hi, lo) at dst.
-template <bool DD, bool FEW = false>
+template <bool DD>
 __device__ __forceinline__ void wave_reduce_store(double x0, double x1, double x2, double x3, double *dst)
 {
     double a, b;
-    wave_reduce<DD, FEW>(x0, x1, x2, x3, a, b);
+    wave_reduce<DD>(x0, x1, x2, x3, a, b);
     const int lane = threadIdx.x & 63;
     if ((lane & 31) == 0) {
         dst[lane >> 4] = a;
         dst[(lane >> 4) + 1] = b;
     }
 }
-template <bool FEW = false, typename A> __device__ __forceinline__ void wave_reduce_store(const A &d, double *dst)
+template <typename A> __device__ __forceinline__ void wave_reduce_store(const A &d, double *dst)
 {
-    wave_reduce_store<A::DD, FEW>(d.x0(), d.x1(), d.x2(), d.x3(), dst);
+    wave_reduce_store<A::DD>(d.x0(), d.x1(), d.x2(), d.x3(), dst);
 }
 
 // The wavefront's sums of two accumulators at once, each in the order of
 // wave_reduce_store: after the first exchange the even rows of 16 lanes go on with the
 // first, the odd rows with the second (7 additions instead of 12).
-template <bool FEW = false, typename A>
+template <typename A>
 __device__ __forceinline__ void wave_reduce_store(const A &d, const A &f, double *dst, double *fdst)
 {
     double a = d.x0(), b = d.x2(), u = f.x0(), v = f.x2();
@@ -397,15 +380,15 @@ __device__ __forceinline__ void wave_reduce_store(const A &d, const A &f, double
         swap_halves(p.lo, q.lo);
         swap_halves(r.hi, s.hi);
         swap_halves(r.lo, s.lo);
-        p = dd_part<FEW>(p, q);
-        r = dd_part<FEW>(r, s);
+        p = dd_sum(p, q);
+        r = dd_sum(r, s);
         swap_rows(p.hi, r.hi);
         swap_rows(p.lo, r.lo);
-        p = dd_part<FEW>(p, r);
-        p = dd_part<FEW>(p, dd{row_ror<8>(p.hi), row_ror<8>(p.lo)});
-        p = dd_part<FEW>(p, dd{row_ror<4>(p.hi), row_ror<4>(p.lo)});
-        p = dd_part<FEW>(p, dd{row_ror<2>(p.hi), row_ror<2>(p.lo)});
-        p = dd_part<FEW>(p, dd{row_ror<1>(p.hi), row_ror<1>(p.lo)});
+        p = dd_sum(p, r);
+        p = dd_sum(p, dd{row_ror<8>(p.hi), row_ror<8>(p.lo)});
+        p = dd_sum(p, dd{row_ror<4>(p.hi), row_ror<4>(p.lo)});
+        p = dd_sum(p, dd{row_ror<2>(p.hi), row_ror<2>(p.lo)});
+        p = dd_sum(p, dd{row_ror<1>(p.hi), row_ror<1>(p.lo)});
         a = p.hi;
         b = p.lo;
     } else {
@@ -1215,11 +1198,11 @@ __global__ __launch_bounds__(SMALL_BLOCK) void k_solve_small(const Inst *__restr
     const size_t pitch = (size_t)I.tiles * 4;
     double *const part = I.partial + (size_t)g * 4;
     if (n0 < 0) {   // <r_0|r_0>
-        if (alive) wave_reduce_store<true>(acc, red[0][0][w]);
+        if (alive) wave_reduce_store(acc, red[0][0][w]);
         __syncthreads();
         if (tid < 2) {
             dd a{0.0, 0.0};
-            for (uint32_t k = 0; k < nw; ++k) a = dd_part<true>(a, dd{red[0][0][k][2 * tid], red[0][0][k][2 * tid + 1]});
+            for (uint32_t k = 0; k < nw; ++k) a = dd_sum(a, dd{red[0][0][k][2 * tid], red[0][0][k][2 * tid + 1]});
             part[2 * tid] = a.hi;
             part[2 * tid + 1] = a.lo;
         }
@@ -1232,10 +1215,10 @@ __global__ __launch_bounds__(SMALL_BLOCK) void k_solve_small(const Inst *__restr
             const uint32_t lane = tid & 63, q = 2 * h + (lane >> 5), o = ((lane >> 4) & 1u) * 2, k = lane & 15;
             dd a{0.0, 0.0};
             if ((int32_t)q < m && k < nw) a = dd{red[half][q][k][o], red[half][q][k][o + 1]};
-            a = dd_part<true>(a, dd{row_ror<8>(a.hi), row_ror<8>(a.lo)});
-            a = dd_part<true>(a, dd{row_ror<4>(a.hi), row_ror<4>(a.lo)});
-            a = dd_part<true>(a, dd{row_ror<2>(a.hi), row_ror<2>(a.lo)});
-            a = dd_part<true>(a, dd{row_ror<1>(a.hi), row_ror<1>(a.lo)});
+            a = dd_sum(a, dd{row_ror<8>(a.hi), row_ror<8>(a.lo)});
+            a = dd_sum(a, dd{row_ror<4>(a.hi), row_ror<4>(a.lo)});
+            a = dd_sum(a, dd{row_ror<2>(a.hi), row_ror<2>(a.lo)});
+            a = dd_sum(a, dd{row_ror<1>(a.hi), row_ror<1>(a.lo)});
             if ((int32_t)q < m && k == 0) {
                 double *dst = part + (size_t)((nq + (int32_t)q + 1) % I.pslots) * pitch;
                 dst[o] = a.hi;
@@ -1301,7 +1284,8 @@ __global__ __launch_bounds__(SMALL_BLOCK) void k_solve_small(const Inst *__restr
             }
             if (n > 0) out = two_minus(out, y);
             nxt[e] = out;
-            a2.add(out, x);
+            if (EPT && u == 0) a2.first(out, x);
+            else a2.add(out, x);
             return out;
         };
         if (alive) {
@@ -1320,9 +1304,9 @@ __global__ __launch_bounds__(SMALL_BLOCK) void k_solve_small(const Inst *__restr
                     v[u] = out;
                 }
             }
-            if (q & 1) wave_reduce_store<true>(held, a2, red[half][q - 1][w], red[half][q][w]);
+            if (q & 1) wave_reduce_store(held, a2, red[half][q - 1][w], red[half][q][w]);
             else if (n + 1 < nz) held = a2;
-            else wave_reduce_store<true>(a2, red[half][q][w]);
+            else wave_reduce_store(a2, red[half][q][w]);
         }
         // step n's LDS writes before step n + 1 reads them, and its reads before they are overwritten
         __syncthreads();

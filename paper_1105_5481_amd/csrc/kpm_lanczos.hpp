@@ -69,8 +69,7 @@ __device__ __forceinline__ V16<double>::T lz_unit(V16<double>::T y, double nrm)
     return y;
 }
 
-// The first sum at dots index idx, rounded: <xi|xi> comes as a pair whose high part alone is
-// a multiple of 2^-36 (biased sums), 16 ulps at 4096 sites; later ones are rounded already.
+// The first sum at dots index idx, a pair, rounded to a double.
 __device__ __forceinline__ double lz_norm2(const Inst &I, int32_t idx)
 {
     return I.dots[(size_t)idx * 4] + I.dots[(size_t)idx * 4 + 1];
@@ -96,13 +95,13 @@ __global__ __launch_bounds__(BLOCK) void k_lz_matvec(const Inst *__restrict__ ta
     const double nrm = sqrt(n2);
     double hop = 0.0;
     if (OPK == OP_REAL2 || OPK == OP_REAL3) hop = G::lds(I.hop, 0);
-    DotsWide acc;
+    Dots<double> acc;
     const LzRange r = lz_range(I.nel);
     for (uint32_t e = r.first; e < r.end; e += r.stride) {
         T v;
         const T out = flat_apply<double, OPK, WIDE>(I, e, hop, [&](uint32_t q) { return lz_unit(G::ld(w, q), nrm); }, v);
         G::st(u, e, out);
-        acc.dot(out, v);
+        acc.cross_only(out, v);
     }
     __shared__ double sum[4];
     block_reduce_store(acc, sum);
@@ -127,7 +126,7 @@ __global__ __launch_bounds__(BLOCK) void k_lz_update(const Inst *__restrict__ ta
     }
     const double nrm = sqrt(lz_norm2(I, 2 * j));                      // of w_j: beta_{j-1} for j > 0
     const double nrp = j > 0 ? sqrt(lz_norm2(I, 2 * j - 2)) : 0.0;    // of w_{j-1}
-    DotsWide acc;
+    Dots<double> acc;
     const LzRange r = lz_range(I.nel);
     for (uint32_t e = r.first; e < r.end; e += r.stride) {
         const T uu = G::ld(u, e), vv = lz_unit(G::ld(w, e), nrm);
