@@ -665,7 +665,18 @@ bool tb_plan(const kpm_ham *h, Plan &p, uint64_t max_tiles = ~0ull)
 // steps with the state in the workspace between.  At 2048 sites a step takes about 1 us
 // against 3.5 to 5 us of a launch per step; with more sites per workgroup the launches
 // win (16^3 spin FP32 3.6 us per step).
-constexpr int64_t SMALL_SITES = 2048;
+//
+// A CSR row is walked one entry at a time there, its columns and values read by every group
+// of chunks from the caches, so a step takes about 1 us and 0.3 us per entry of a row (64
+// sites; 0.85 at 1000, 1.7 at 2000, whose entries outgrow the L1), whatever R.  The flat
+// kernel takes 4 to 5 us and 0.13 per entry.  us per step here and there, real FP32 R = 32:
+// 300 rows of 5 entries 1.8 / 4.4, of 25 7.8 / 7.8, of 501 142 / 65; 1000 rows of 5 2.5 / 4.4,
+// of 9 4.4 / 5.7, of 13 6.6 / 5.8, of 51 43 / 11; 2000 rows of 5 4.1 / 4.5, of 7 5.8 / 4.7, of
+// 501 1857 / 66; complex FP64 2000 rows of 5, R = 4 5.3 / 4.9, R = 64 5.7 / 6.9.  So CSR solves
+// are run here up to SMALL_NNZ entries, at most SMALL_ROW of them per row on average.  (Eight
+// entries at a time, as the flat kernel walks them, gained below 500 rows and lost up to half
+// of a step beyond.)
+constexpr int64_t SMALL_SITES = 2048, SMALL_NNZ = 10240, SMALL_ROW = 32;
 constexpr size_t SMALL_WS = 16u << 20;   // most workspace of the second kind
 int32_t small_slots(const Plan &p)
 {
@@ -680,6 +691,7 @@ bool small_plan(const kpm_ham *h, Plan &p, int32_t M)
     const uint64_t N = (uint64_t)h->N;
     p.whole = 2ull * p.nel * 16 <= lim;
     if (!p.whole && h->N > SMALL_SITES) return false;
+    if (!h->dim && h->nnz > std::min(SMALL_NNZ, SMALL_ROW * h->N)) return false;
     uint32_t w = p.whole ? (p.C + 15) / 16 : 1;                          // chunks per group
     w = std::min<uint32_t>(p.C, std::max<uint32_t>(w, (uint32_t)((64 + N - 1) / N)));   // a wave's worth at least
     if (2ull * N * w * 16 > lim) return false;
