@@ -218,6 +218,7 @@ __global__ __launch_bounds__(64 * NW) void k_dense_resident(const double *__rest
     const size_t wslot = (size_t)blockIdx.x * NW + w;   // this wave's partial within a slot
     wave_reduce_store<true>(s0, e0, 0.0, 0.0, part + wslot * 4);
     __syncthreads();
+    WaveSums<true> ws;   // of the last steps, four together
     for (int32_t n = 0; n < K; ++n) {
         dn_d4 acc[4];
 #pragma unroll
@@ -247,7 +248,10 @@ __global__ __launch_bounds__(64 * NW) void k_dense_resident(const double *__rest
             cur[v] = out;
             Vs[(16 * w + 4 * v + lk) * 16 + lr] = out;
         }
-        wave_reduce_store<true>(x0, y0, x1, y1, part + ((size_t)(n + 1) * nblk * NW + wslot) * 4);
+        const int q = n & 3;
+        ws.add(q, x0, y0, x1, y1);
+        if (q == 3 || n + 1 == K)
+            ws.finish(q + 1, part + ((size_t)(n + 1 - q) * nblk * NW + wslot) * 4, (size_t)nblk * NW * 4);
         __syncthreads();   // the slab of r_{n+1} is complete
     }
 }

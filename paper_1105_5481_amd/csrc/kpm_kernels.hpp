@@ -312,104 +312,81 @@ template <bool CPLX> struct ColDots<double, CPLX> {
     }
 };
 
-// Sums of x0 + x1 and x2 + x3 over the wavefront, in (a, b): the lower 32 lanes
-// receive the first, the upper 32 the second (as a double-double when DD, else in a
-// alone).  The first exchange gives each half of the wave one of the two sums, so a
-// reduction is six additions of 11 operations, and no exchange goes through the LDS: with
-// ds_bpermute shuffles of both sums it was twelve of 20 and 48 shuffles of 24 cycles, most
-// of a step of the single-workgroup solves.
-template <bool DD>
-__device__ __forceinline__ void wave_reduce(double x0, double x1, double x2, double x3, double &a, double &b)
+// ---------------------------------------------------------------------------
+// sums over a wavefront
+// ---------------------------------------------------------------------------
+// Two sums (x0 + x1, x2 + x3; double-doubles when DD, else x0 and x2 alone) of up to four
+// accumulators.  A level of the tree adds each lane's value and that of the lane 32, 16, 8, 4,
+// 2 or 1 away.  At the first three the two lanes hand each other half of what they have: the
+// lower 32 lanes go on with the first sum, the upper 32 with the second; the even rows of 16
+// lanes with one accumulator of a pair, the odd ones with the other; the lower and upper 8 lanes
+// of a row with the first and second pair.  Four accumulators so take ten additions of 11
+// operations, and no exchange goes through the LDS.  (With ds_bpermute shuffles it was 48 of 20
+// and 192 shuffles of 24 cycles, most of a step of the few-site solves.)  An accumulator's
+// tree, and so its bits, are the same whatever others share the exchanges.
+template <bool DD> __device__ __forceinline__ dd wave_add(dd x, dd y)
 {
-    if (DD) {
-        dd p{x0, x1}, q{x2, x3};
-        swap_halves(p.hi, q.hi);
-        swap_halves(p.lo, q.lo);
-        p = dd_sum(p, q);
-        q = p;
-        swap_rows(p.hi, q.hi);
-        swap_rows(p.lo, q.lo);
-        p = dd_sum(p, q);
-        p = dd_sum(p, dd{row_ror<8>(p.hi), row_ror<8>(p.lo)});
-        p = dd_sum(p, dd{row_ror<4>(p.hi), row_ror<4>(p.lo)});
-        p = dd_sum(p, dd{row_ror<2>(p.hi), row_ror<2>(p.lo)});
-        p = dd_sum(p, dd{row_ror<1>(p.hi), row_ror<1>(p.lo)});
-        a = p.hi;
-        b = p.lo;
-    } else {
-        swap_halves(x0, x2);
-        a = x0 + x2;
-        b = a;
-        swap_rows(a, b);
-        a += b;
-        a += row_ror<8>(a);
-        a += row_ror<4>(a);
-        a += row_ror<2>(a);
-        a += row_ror<1>(a);
-        b = 0.0;
-    }
+    if (DD) return dd_sum(x, y);
+    return dd{x.hi + y.hi, 0.0};
 }
-
-// The wavefront's sums of (x0 + x1, x2 + x3), stored as four doubles (hi, lo, hi, lo) at dst.
+template <bool DD, int N> __device__ __forceinline__ dd wave_ror(dd p)
+{
+    return dd{row_ror<N>(p.hi), DD ? row_ror<N>(p.lo) : 0.0};
+}
+template <bool DD> __device__ __forceinline__ dd wave_halves(dd p, dd q)
+{
+    swap_halves(p.hi, q.hi);
+    if (DD) swap_halves(p.lo, q.lo);
+    return wave_add<DD>(p, q);
+}
+template <bool DD> __device__ __forceinline__ dd wave_rows(dd p, dd q)
+{
+    swap_rows(p.hi, q.hi);
+    if (DD) swap_rows(p.lo, q.lo);
+    return wave_add<DD>(p, q);
+}
+template <bool DD> struct WaveSums {
+    dd r{0.0, 0.0}, t{0.0, 0.0};   // the last accumulator or pair; the first pair
+    // accumulator k = 0 .. 3, in order (k the same in every lane)
+    __device__ __forceinline__ void add(int k, double x0, double x1, double x2, double x3)
+    {
+        const dd h = wave_halves<DD>(dd{x0, x1}, dd{x2, x3});
+        if ((k & 1) == 0) r = h;
+        else if (k == 1) t = wave_rows<DD>(r, h);
+        else r = wave_rows<DD>(r, h);
+    }
+    template <typename A> __device__ __forceinline__ void add(int k, const A &d) { add(k, d.x0(), d.x1(), d.x2(), d.x3()); }
+    // the sums of the n accumulators added: accumulator k as four doubles (hi, lo, hi, lo) at dst + k * pitch
+    __device__ __forceinline__ void finish(int n, double *dst, size_t pitch)
+    {
+        dd u = n == 2 ? t : r;
+        if (n & 1) u = wave_rows<DD>(u, u);
+        const dd v = n == 1 ? u : t;
+        const int lane = threadIdx.x & 63;
+        const bool up = (lane & 8) != 0;
+        const dd keep{up ? u.hi : v.hi, up ? u.lo : v.lo}, give{up ? v.hi : u.hi, up ? v.lo : u.lo};
+        dd p = wave_add<DD>(keep, wave_ror<DD, 8>(give));
+        p = wave_add<DD>(p, wave_ror<DD, 4>(p));   // valid in lanes 4 .. 7 of each 8,
+        p = wave_add<DD>(p, wave_ror<DD, 2>(p));   // ... 6 and 7,
+        p = wave_add<DD>(p, wave_ror<DD, 1>(p));   // ... 7
+        const int k = ((lane >> 4) & 1) + ((lane >> 3) & 1) * 2;
+        if ((lane & 7) == 7 && k < n) {
+            double *o = dst + (size_t)k * pitch + ((lane & 32) >> 4);
+            o[0] = p.hi;
+            o[1] = p.lo;
+        }
+    }
+};
 template <bool DD>
 __device__ __forceinline__ void wave_reduce_store(double x0, double x1, double x2, double x3, double *dst)
 {
-    double a, b;
-    wave_reduce<DD>(x0, x1, x2, x3, a, b);
-    const int lane = threadIdx.x & 63;
-    if ((lane & 31) == 0) {
-        dst[lane >> 4] = a;
-        dst[(lane >> 4) + 1] = b;
-    }
+    WaveSums<DD> s;
+    s.add(0, x0, x1, x2, x3);
+    s.finish(1, dst, 0);
 }
 template <typename A> __device__ __forceinline__ void wave_reduce_store(const A &d, double *dst)
 {
     wave_reduce_store<A::DD>(d.x0(), d.x1(), d.x2(), d.x3(), dst);
-}
-
-// The wavefront's sums of two accumulators at once, each in the order of
-// wave_reduce_store: after the first exchange the even rows of 16 lanes go on with the
-// first, the odd rows with the second (7 additions instead of 12).
-template <typename A>
-__device__ __forceinline__ void wave_reduce_store(const A &d, const A &f, double *dst, double *fdst)
-{
-    double a = d.x0(), b = d.x2(), u = f.x0(), v = f.x2();
-    if (A::DD) {
-        dd p{a, d.x1()}, q{b, d.x3()}, r{u, f.x1()}, s{v, f.x3()};
-        swap_halves(p.hi, q.hi);
-        swap_halves(p.lo, q.lo);
-        swap_halves(r.hi, s.hi);
-        swap_halves(r.lo, s.lo);
-        p = dd_sum(p, q);
-        r = dd_sum(r, s);
-        swap_rows(p.hi, r.hi);
-        swap_rows(p.lo, r.lo);
-        p = dd_sum(p, r);
-        p = dd_sum(p, dd{row_ror<8>(p.hi), row_ror<8>(p.lo)});
-        p = dd_sum(p, dd{row_ror<4>(p.hi), row_ror<4>(p.lo)});
-        p = dd_sum(p, dd{row_ror<2>(p.hi), row_ror<2>(p.lo)});
-        p = dd_sum(p, dd{row_ror<1>(p.hi), row_ror<1>(p.lo)});
-        a = p.hi;
-        b = p.lo;
-    } else {
-        swap_halves(a, b);
-        swap_halves(u, v);
-        a += b;
-        u += v;
-        swap_rows(a, u);
-        a += u;
-        a += row_ror<8>(a);
-        a += row_ror<4>(a);
-        a += row_ror<2>(a);
-        a += row_ror<1>(a);
-        b = 0.0;
-    }
-    const int lane = threadIdx.x & 63;
-    if ((lane & 15) == 0) {
-        double *o = (lane & 16) ? fdst : dst;
-        o[(lane & 32) >> 4] = a;
-        o[((lane & 32) >> 4) + 1] = b;
-    }
 }
 
 // Sum (x0 + x1, x2 + x3) over the block in a fixed order, stored as four doubles
@@ -797,7 +774,8 @@ __global__ __launch_bounds__(BLOCK) void k_step_march(const Inst *__restrict__ t
     typedef std::conditional_t<COLS, ColDots<S, SPIN>, Dots<S>> Acc;
     __shared__ double red[COLS ? 1 : RUN_MAX][BLOCK / 64][4];   // wave sums of the run's segments
     // a thread's sums of the even segment of a pair, reduced with the odd one's (in the LDS:
-    // four more VGPRs would cost the FP32 3D spin kernel one of its 7 waves per SIMD)
+    // four more VGPRs would cost the FP32 3D spin kernel one of its 7 waves per SIMD; all four
+    // segments of a run reduced at its end measured 1-4% slower)
     __shared__ double held[COLS ? ColDots<S, SPIN>::NV * ColDots<S, SPIN>::V1 : Dots<S>::NV][BLOCK];
     const ItemRange ir = item_range(I, MODE_MARCH, blockIdx.x);
     for (uint32_t it = ir.first; it < ir.count; it += ir.stride) {
@@ -890,9 +868,19 @@ __global__ __launch_bounds__(BLOCK) void k_step_march(const Inst *__restrict__ t
                 column_sums(I, acc, held, ct, part + (size_t)(sg * I.nct + ct) * I.R * 4);
             } else {
                 const uint32_t k = sg - s0, w = threadIdx.x >> 6;
-                if (k & 1u) wave_reduce_store(Dots<S>(held), acc, red[k - 1][w], red[k][w]);
-                else if (sg + 1 < s1) acc.save(held);
-                else wave_reduce_store(acc, red[k][w]);
+                if (!(k & 1u) && sg + 1 < s1) {
+                    acc.save(held);
+                } else {
+                    WaveSums<Dots<S>::DD> ws;
+                    if (k & 1u) {
+                        ws.add(0, Dots<S>(held));
+                        ws.add(1, acc);
+                        ws.finish(2, red[k - 1][w], BLOCK / 64 * 4);
+                    } else {
+                        ws.add(0, acc);
+                        ws.finish(1, red[k][w], 0);
+                    }
+                }
             }
         }
         if constexpr (!COLS) {
@@ -1065,7 +1053,7 @@ __global__ __launch_bounds__(BLOCK) void k_step_flat(const Inst *__restrict__ ta
 // diagonal, neighbour indices (16 bits each) and bonds stay in registers, so a step
 // reads the neighbours from the LDS and writes one chunk.  (EPT = 0: more chunks per
 // thread, taken from the LDS and placed anew each step.)
-// Dots are summed per wave for two steps at once and over the waves every fourth step,
+// Dots are summed per wave for four steps at once and then over the waves,
 // by waves 0 and 1 while the others go on; each step leaves one partial per group.
 //
 // What bounds it: the chain of one step (LDS reads, the stencil, the sums, the barrier).
@@ -1226,7 +1214,7 @@ __global__ __launch_bounds__(SMALL_BLOCK) void k_solve_small(const Inst *__restr
             }
         }
     };
-    Dots<S> held;
+    WaveSums<Dots<S>::DD> ws;   // of the last steps, four together
     for (int32_t n = na; n < nz; ++n) {
         const int32_t j = n - na;          // steps of this launch so far
         const int q = j & 3, half = (j >> 2) & 1;
@@ -1304,9 +1292,8 @@ __global__ __launch_bounds__(SMALL_BLOCK) void k_solve_small(const Inst *__restr
                     v[u] = out;
                 }
             }
-            if (q & 1) wave_reduce_store(held, a2, red[half][q - 1][w], red[half][q][w]);
-            else if (n + 1 < nz) held = a2;
-            else wave_reduce_store(a2, red[half][q][w]);
+            ws.add(q, a2);
+            if (q == 3 || n + 1 == nz) ws.finish(q + 1, red[half][0][w], SMALL_WAVES * 4);
         }
         // step n's LDS writes before step n + 1 reads them, and its reads before they are overwritten
         __syncthreads();
