@@ -382,7 +382,7 @@ kpm_status kpm_start_vectors(int32_t vec, int32_t complex_layout, uint64_t seed,
  *                                KPM_LAUNCH_MAX_BLOCKS blocks
  *   KPM_LAUNCH_XCD_SPLIT         how an instance's work items are split over the 8 XCDs:
  *                                0 automatic (march: evenly, in plane order), 1 by column tiles, 2 by march segments, 3 none
- *   KPM_LAUNCH_ALTERNATE         1: odd march segments of 4 planes or more walk downwards
+ *   KPM_LAUNCH_ALTERNATE         1: odd march segments of 3 planes or more walk downwards
  *   KPM_LAUNCH_SMALL             1: a solve of few sites (its two vector blocks fit in the LDS of
  *                                one compute unit, or it has at most 2048 sites; CSR: up to 10240
  *                                entries, 32 per row on average) keeps its

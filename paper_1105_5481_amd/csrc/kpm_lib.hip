@@ -707,7 +707,10 @@ bool small_plan(const kpm_ham *h, Plan &p, int32_t M)
 }
 
 constexpr uint32_t CSR_FINE = 1u << 14;
-constexpr uint32_t RUN_PLANES = 3;   // planes a run of short segments covers
+constexpr uint32_t SEG_ITEMS = 64;   // least items for which segments are kept to two planes
+// Planes that a run of segments of one or two planes covers (set_runs).
+constexpr uint32_t RUN_SEG = 2;   // longest such segment
+uint32_t run_planes(int prec, int opk) { return prec == KPM_F64 && (opk == OP_REAL3 || opk == OP_SPIN3) ? 4 : 3; }
 
 bool make_plan(const kpm_ham *h, int32_t M, int32_t R, int32_t vec, Plan &p, bool allow_tb = true)
 {
@@ -776,8 +779,8 @@ bool make_plan(const kpm_ham *h, int32_t M, int32_t R, int32_t vec, Plan &p, boo
         const bool spin_stream = h->opk == OP_SPIN3 && h->prec == KPM_F32 &&
                                  stream_choice(2ull * h->N * p.Rs * p.esz + (uint64_t)h->N * 7 * p.esz) == 1;
         p.grid_cap = spin_stream ? std::max<uint32_t>(8, (uint32_t)g_max_blocks / 32 * 8) : (uint32_t)g_max_blocks;
-        // Segments: as many as give the target work items (two blocks per CU), down to one
-        // plane each.  A launch of a small lattice lasts as long as one block's planes, each
+        // Segments: as many as give the target work items (two blocks per CU), down to two
+        // planes each, in small lattices one.  A launch of a small lattice lasts as long as one block's planes, each
         // a load's latency; held to 8 planes or more, 16^3 to 48^3 lattices filled a fraction
         // of the chip.  us per step, 8 planes -> now (R): spin FP32 16^3 (8) 8.8 -> 3.6, 32^3
         // (16) 11.7 -> 5.6, 40^3 (16) 11.1 -> 7.8, 70 x 50 x 33 (9) 15.4 -> 9; FP64 32^3 (16)
@@ -789,6 +792,16 @@ bool make_plan(const kpm_ham *h, int32_t M, int32_t R, int32_t vec, Plan &p, boo
         } else {
             nseg = (uint32_t)(((uint64_t)g_march_items + p.nct / 2) / p.nct);
             nseg = std::max<uint32_t>(1, std::min<uint32_t>(nseg, p.Lm));
+            // One plane only where a 3D lattice is so small that two leave fewer than SEG_ITEMS
+            // items: every segment's sums are reduced by themselves, and in shared launches, where
+            // blocks abound, one-plane segments cost more than they save.  us per step, one ->
+            // two planes (8 planes and whole members per XCD): 128 cubes 16 .. 24 spin R = 16 FP32
+            // 88.7 -> 82.2 (84.9), R = 8 FP64 99.0 -> 90.0 (90.5); 60 squares of 64^2 real R = 16
+            // FP32 20.1 -> 19.4 (19.3), 30 of 200^2 spin R = 4 FP32 26.0 -> 24.9 (27.6).  Alone: 16^3
+            // spin FP32 R = 8 4.1 -> 4.9 (kept at one), 24^3 R = 16 4.8 -> 5.2, 64^2 real FP64
+            // R = 8 4.0 -> 4.6.
+            if (h->dim == 2 || (uint64_t)p.nct * ((p.Lm + 1) / 2) >= SEG_ITEMS)
+                nseg = std::min<uint32_t>(nseg, (p.Lm + 1) / 2);
         }
         p.S = (p.Lm + nseg - 1) / nseg;
         p.nseg = (p.Lm + p.S - 1) / p.S;
@@ -801,7 +814,7 @@ bool make_plan(const kpm_ham *h, int32_t M, int32_t R, int32_t vec, Plan &p, boo
         if (g_xcd_split == 1) p.xcd = p.nct >= XCD_MIN_ITEMS ? 1 : 0;
         if (g_xcd_split == 2) p.xcd = p.nseg >= 8 ? 2 : 0;
         if (g_xcd_split == 3) p.xcd = 0;
-        p.alt = p.S >= RUN_PLANES ? g_alternate : 0;   // shorter segments may be walked in runs
+        p.alt = p.S > RUN_SEG ? g_alternate : 0;   // shorter segments may be walked in runs
     } else {
         p.mode = MODE_FLAT;
         // CSR tiles of one chunk per thread up to CSR_FINE tiles: the gathers want every
@@ -1663,23 +1676,24 @@ uint32_t place_blocks(std::vector<Inst> &ins, std::vector<uint32_t> &map, double
     return blocks + 8 * span;
 }
 
-// Runs of the march instances of one launch: short segments (fewer than RUN_PLANES
-// planes) are walked in runs of about that many planes once the launch has more than
-// RUN_BLOCKS blocks without them (4 per CU); below that the blocks are what is missing.
-// us per step of all waves, runs of 1 / 2 / 3 / 4 planes (before: segments of 8 planes or more,
-// whole instances per XCD): 256 cubes L = 16 .. 48, FP32 R = 16 703 / 693 / 690 / 696 (736),
-// R = 8 408 / 394 / 389 / 398 (393), R = 4 215 / 207 / 209 / 221 (232); 254 cubes 20 .. 37,
-// R = 4 150 / 145 / 148 / 152 (152); 100 cubes 16 .. 40, FP64 R = 8 206 / 196 / 191 / 193
-// (211); 128 cubes 16 .. 24, R = 16 95 / 91 / 90 / 93 (85).  Runs of 6 planes and more lose.
+// Runs of the march instances of one launch: segments of one or two planes are walked in runs
+// of up to `planes` planes (run_planes) once the launch has more than RUN_BLOCKS blocks without
+// them (4 per CU); below that the blocks are what is missing.  A run reads its two halo planes
+// once, but takes its planes one after the other.  us per step of all waves, planes 2 / 3 / 4
+// (segments of 8 planes or more, whole members per XCD): FP32 256 cubes 16 .. 48 R = 16 723 /
+// 721 / 731 (761), 128 of 16 .. 24 82.2 / 82.2 / 84.8 (84.9), 100 of 12 .. 32 R = 8 52.2 / 50.8 /
+// 55.9 (56.0), 20 of 300 x 200 sites 37.7 / 37.5 / 41.5 (42.9); FP64 128 cubes 16 .. 24 R = 16
+// 172 / 170 / 160 (161), 100 of 16 .. 40 R = 8 216 / 208 / 207 (221), 60 of 64^2 sites 34.4 /
+// 34.4 / 36.8 (35.5).  Six planes and more lose everywhere.
 constexpr uint64_t RUN_BLOCKS = 1024;
-void set_runs(std::vector<Inst> &ins)
+void set_runs(std::vector<Inst> &ins, uint32_t planes)
 {
     uint64_t blocks = 0;
     for (const Inst &I : ins) blocks += I.nb;
     for (Inst &I : ins) {
         I.run = 1;
-        if (I.mode != MODE_MARCH || I.S >= RUN_PLANES || blocks <= RUN_BLOCKS) continue;
-        I.run = (uint32_t)std::min<uint64_t>({RUN_PLANES / I.S, RUN_MAX, (blocks + RUN_BLOCKS - 1) / RUN_BLOCKS});
+        if (I.mode != MODE_MARCH || I.S > RUN_SEG || blocks <= RUN_BLOCKS) continue;
+        I.run = (uint32_t)std::min<uint64_t>({planes / I.S, RUN_MAX, (blocks + RUN_BLOCKS - 1) / RUN_BLOCKS});
         const uint32_t items = I.nct * ((I.nseg + I.run - 1) / I.run);
         I.nb = std::min<uint32_t>(I.nb, (items + 7) / 8 * 8);
     }
@@ -1820,7 +1834,7 @@ void add_groups(kpm_ham *const *h, const std::vector<int> &ids, BatchLayout &L, 
         }
         g.count = (uint32_t)ins.size();
         if (g.mode != MODE_SMALL) {
-            set_runs(ins);
+            set_runs(ins, run_planes(L.prec, g.opk));
             if (g.mode == MODE_MARCH) {
                 std::vector<Inst> pieces;
                 EvenMap em;
@@ -1940,7 +1954,7 @@ kpm_status kpm_moments_batched(kpm_ham *const *h, int32_t count, const int32_t *
     for (size_t q = 0; q < all.size() && e == KPM_OK; ++q) {
         const BatchGroup *g = all[q];
         std::vector<Inst> ins(tab.begin() + g->first, tab.begin() + g->first + g->count);
-        set_runs(ins);
+        set_runs(ins, run_planes(L.prec, g->opk));
         if (g->mode == MODE_MARCH) {
             if (pieces.size() != g->pfirst || place_even(ins, pieces, maps[q]) != g->blocks) return KPM_ERR_INVALID_ARG;
         } else {
@@ -2264,7 +2278,7 @@ kpm_status kpm_batch_advance(kpm_batch *b, int32_t steps, void *stream)
             ins.push_back(I);
         }
         g.count = (uint32_t)ins.size();
-        set_runs(ins);
+        set_runs(ins, run_planes(act[0]->h->prec, g.opk));
         if (g.mode != MODE_SMALL) g.blocks = place_blocks(ins, map, SLACK_DYNAMIC);
         tab.insert(tab.end(), ins.begin(), ins.end());
         groups.push_back(g);
@@ -2748,10 +2762,10 @@ int64_t kpm_selftest_placement(const uint32_t *nb, int32_t *xcd, const uint32_t 
 
 // Host check of the work items of one launch group of `count` instances of one mode (0 flat, 1 march,
 // 3 and 4 blocked passes), as the kernels take them: units[i] x segs[i] items (segs 1 for flat),
-// planes[i] planes per march segment, nb[i] blocks, split flag xcd[i].  static_wave: placed as a
+// planes[i] planes per march segment, runs of up to `run` planes, nb[i] blocks, split flag xcd[i].  static_wave: placed as a
 // static batch places them, else as a dynamic one (xcd[i] is then updated to the placement's).  Returns the number of
 // items (march: segments) not run exactly once by the blocks of the grid, or -1.
-int64_t kpm_selftest_items(int32_t mode, int32_t static_wave, int32_t count, const uint32_t *units, const uint32_t *segs,
+int64_t kpm_selftest_items(int32_t mode, int32_t run, int32_t static_wave, int32_t count, const uint32_t *units, const uint32_t *segs,
                            const uint32_t *planes, const uint32_t *nb, int32_t *xcd)
 {
     if (count < 1 || !units || !segs || !planes || !nb || !xcd) return -1;
@@ -2771,7 +2785,7 @@ int64_t kpm_selftest_items(int32_t mode, int32_t static_wave, int32_t count, con
         I.nel = I.tiles * planes[i] * (uint32_t)BLOCK;
         runs[i].assign(I.tiles, 0);
     }
-    set_runs(ins);
+    set_runs(ins, run);
     std::vector<Inst> table;
     std::vector<uint32_t> map;
     std::vector<int32_t> of;   // instance of a table entry

@@ -15,12 +15,12 @@ def L():
     return kpm.lib()
 
 
-def _missed(L, mode, static, units, segs, planes, xcd, cap=2048):
+def _missed(L, mode, static, units, segs, planes, xcd, cap=2048, run=3):
     u, s, p = (np.array(v, dtype=np.uint32) for v in (units, segs, planes))
     x = np.array(xcd, dtype=np.int32)
     nb = np.minimum((u * s + 7) // 8 * 8, cap).astype(np.uint32)
     P = lambda a: a.ctypes.data_as(ctypes.c_void_p)
-    return L.kpm_selftest_items(mode, static, len(u), P(u), P(s), P(p), P(nb), P(x)), x
+    return L.kpm_selftest_items(mode, run, static, len(u), P(u), P(s), P(p), P(nb), P(x)), x
 
 
 @pytest.mark.parametrize("static", [0, 1])
@@ -50,4 +50,5 @@ def test_every_item_once(L, case, mode, static):
     xcd = [int(g.choice([0, 3] + ([1] if u >= 8 else []) + ([2] if s >= 8 else []))) if u * s >= 64 else 0
            for u, s in zip(units, segs)]
     for cap in (8, 64, 2048):
-        assert _missed(L, mode, static, units, segs, planes, xcd, cap)[0] == 0, cap
+        for run in (3, 4):    # planes of a run
+            assert _missed(L, mode, static, units, segs, planes, xcd, cap, run)[0] == 0, (cap, run)
