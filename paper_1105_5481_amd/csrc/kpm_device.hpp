@@ -130,6 +130,11 @@ __device__ __forceinline__ dd dd_sum(dd x, dd y)
     const dd s = dd_two_sum(x.hi, y.hi);
     return dd_fast_two_sum(s.hi, s.lo + (x.lo + y.lo));
 }
+__device__ __forceinline__ dd dd_sum(dd x, double y)
+{
+    const dd s = dd_two_sum(x.hi, y);
+    return dd_fast_two_sum(s.hi, s.lo + x.lo);
+}
 // (s, c) += x*y exactly up to the error term c, which is summed in FP64.  The two-sum of s and
 // the rounded product p gives s + p = t + (s - (t - v)) + (p - v); the product's own error is
 // taken in with the last term, (p - v) + (x*y - p) = x*y - v in one fma.
