@@ -918,6 +918,11 @@ __global__ __launch_bounds__(BLOCK) void k_step_march(const Inst *__restrict__ t
 //   the same in FP64                            60.6 -> 61.2 -> 55.5   (60.1)
 //   200000 rows of 17, complex FP32, R = 8     100.2 -> 74.4 -> 70.3   (70.3)
 //   30000 rows of 13, complex FP32, R = 16      14.1 ->  9.9 -> 10.2   (38.0)
+// The last four or fewer of a row take half as many loads: eight at a time alone, then four
+// at the end (before):
+//   500000 rows of 3, FP64, R = 8               34.6 -> 32.4   (31.6)
+//   500000 rows of 9, FP32, R = 8               29.1 -> 24.6   (28.4)
+//   100000 rows of 21, FP32, R = 16             35.8 -> 32.9   (62.4)
 constexpr int CSR_AHEAD = 8;
 // H~ r on chunk e, r read through ld(chunk index); v receives the chunk itself.
 template <typename S, int OPK, bool WIDE, typename LD>
@@ -982,24 +987,26 @@ __device__ __forceinline__ typename V16<S>::T flat_apply(const Inst &I, uint32_t
         T a;
 #pragma unroll
         for (int l = 0; l < W; ++l) a[l] = d * v[l];
-        for (int64_t kk = kb; kk < ke; kk += CSR_AHEAD) {
-            uint32_t jj[CSR_AHEAD];
-            S2 h[CSR_AHEAD];
-            T vj[CSR_AHEAD];
+        // entries kk .. kk + n - 1 (n a constant), as many of them as the row has
+        auto entries = [&](int64_t kk, auto n) {
+            constexpr int AHEAD = decltype(n)::value;
+            uint32_t jj[AHEAD];
+            S2 h[AHEAD];
+            T vj[AHEAD];
 #pragma unroll
-            for (int z = 0; z < CSR_AHEAD; ++z) {
+            for (int z = 0; z < AHEAD; ++z) {
                 const int64_t o = min(kk + z, ke - 1);
                 jj[z] = kk + z < ke ? (uint32_t)I.col[o] : i;   // i: an entry not added
                 if constexpr (OPK == OP_CSR_R) h[z] = S2{((const S *)I.val)[o], (S)0};
                 else h[z] = ((const S2 *)I.val)[o];
             }
 #pragma unroll
-            for (int z = 0; z < CSR_AHEAD; ++z) {
+            for (int z = 0; z < AHEAD; ++z) {
                 vj[z] = (T)(S)0;
                 if (jj[z] != i) vj[z] = ld(jj[z] * C + c);
             }
 #pragma unroll
-            for (int z = 0; z < CSR_AHEAD; ++z) {
+            for (int z = 0; z < AHEAD; ++z) {
                 if (jj[z] == i) continue;
                 if constexpr (OPK == OP_CSR_R) {
                     a = A::mac(a, h[z][0], vj[z]);
@@ -1013,7 +1020,10 @@ __device__ __forceinline__ typename V16<S>::T flat_apply(const Inst &I, uint32_t
                     }
                 }
             }
-        }
+        };
+        int64_t kk = kb;
+        for (; ke - kk > CSR_AHEAD / 2; kk += CSR_AHEAD) entries(kk, std::integral_constant<int, CSR_AHEAD>());
+        if (kk < ke) entries(kk, std::integral_constant<int, CSR_AHEAD / 2>());
         out = a;
     }
     return out;
