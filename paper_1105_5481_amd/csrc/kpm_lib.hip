@@ -793,13 +793,15 @@ bool make_plan(const kpm_ham *h, int32_t M, int32_t R, int32_t vec, Plan &p, boo
             nseg = (uint32_t)(((uint64_t)g_march_items + p.nct / 2) / p.nct);
             nseg = std::max<uint32_t>(1, std::min<uint32_t>(nseg, p.Lm));
             // One plane only where a 3D lattice is so small that two leave fewer than SEG_ITEMS
-            // items: every segment's sums are reduced by themselves, and in shared launches, where
-            // blocks abound, one-plane segments cost more than they save.  us per step, one ->
-            // two planes (8 planes and whole members per XCD): 128 cubes 16 .. 24 spin R = 16 FP32
-            // 88.7 -> 82.2 (84.9), R = 8 FP64 99.0 -> 90.0 (90.5); 60 squares of 64^2 real R = 16
-            // FP32 20.1 -> 19.4 (19.3), 30 of 200^2 spin R = 4 FP32 26.0 -> 24.9 (27.6).  Alone: 16^3
-            // spin FP32 R = 8 4.1 -> 4.9 (kept at one), 24^3 R = 16 4.8 -> 5.2, 64^2 real FP64
-            // R = 8 4.0 -> 4.6.
+            // items: every segment's sums are reduced by themselves, which in FP64 takes half as
+            // long as a plane, and in shared launches, where blocks abound, one-plane segments
+            // cost more than they save.  us per step (segments of 8 planes, whole members per XCD):
+            // FP64, one -> two planes: 128 cubes 16 .. 24 spin R = 8 99.0 -> 90.0 (90.5), alone
+            // 16^3 4.3 -> 5.0 (11.0).  FP32, two planes from 64 / 200 items / never: 128 cubes
+            // 16 .. 24 R = 16 76.9 / 78.3 / 81.1 (79.6), 128 of 20 .. 30 141.0 / 147.6 / 145.0
+            // (149.2), 256 of 16 .. 48 681 / 678 / 672 (705), alone 24^3 R = 16 5.2 / 5.2 / 4.8
+            // (10.1).  2D: 60 squares of 64^2 R = 16 FP32 20.1 -> 19.4 (19.3), 30 of 200^2 spin
+            // R = 4 26.0 -> 24.9 (27.6), alone 64^2 FP64 R = 8 4.0 -> 4.6 (8.1).
             if (h->dim == 2 || (uint64_t)p.nct * ((p.Lm + 1) / 2) >= SEG_ITEMS)
                 nseg = std::min<uint32_t>(nseg, (p.Lm + 1) / 2);
         }
