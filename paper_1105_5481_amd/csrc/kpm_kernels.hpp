@@ -1079,8 +1079,8 @@ __global__ __launch_bounds__(BLOCK) void k_step_flat(const Inst *__restrict__ ta
 // What bounds it: the chain of one step (LDS reads, the stencil, the sums, the barrier).
 // us per step of whole solves of 128 steps, launches included; before: one 1024-thread
 // workgroup for all chunks and a whole wave sum per wave and step where they fitted, else a
-// launch per step: 32 x 32 sites FP64 R = 8 5.65 -> 1.13, R = 32 7.9 -> 1.16; 10^3 spin FP32
-// R = 16 10.5 -> 1.2; 12^3 spin FP64 R = 16 13.7 -> 2.9; 64 x 64 FP32 R = 4 3.5 -> 2.9.
+// launch per step: 32 x 32 sites FP64 R = 8 5.7 -> 1.3, R = 32 7.9 -> 1.3; 10^3 spin FP32
+// R = 16 10.5 -> 1.2; 12^3 spin FP64 R = 16 13.8 -> 3.1; 64 x 64 FP32 R = 4 3.5 -> 2.9.
 constexpr uint32_t SMALL_BLOCK = 1024;
 constexpr uint32_t SMALL_WAVES = SMALL_BLOCK / 64;
 constexpr uint32_t SMALL_EPT = 2;     // most chunks per thread kept in registers

@@ -597,11 +597,13 @@ bool tb3_plan(const kpm_ham *h, Plan &p)
 //   max(lat + b w D, b 0.75 us if the vectors stream from HBM),
 // b blocks per CU at once.  lat and w (us) fit measured passes of ten lattices
 // (144^2 .. 2048^2, R = 2 .. 64, both precisions and hoppings; 700 tilings) within 5-20%,
-// and the tiling picked is within 8% of the best one measured (FP64 spin: 13%).
+// and the tiling picked is within 8% of the best one measured (FP64 spin: 13%).  FP64 passes
+// take 8-12% longer than the fit since their dots are full pairs; the depth it picks is still
+// within 1.5% of the best of 3 .. 6 on nine lattices.
 // Per step against 512-thread blocks with whole sites or groups of >= 8 chunks, XCDs
-// split by tiles and 3 or 4 steps per pass: 2048^2 R = 64 FP32 235 -> 166 us, FP64
-// 636 -> 405; 1024^2 spin R = 32 FP32 112 -> 79; 339^2 spin R = 34 18.1 -> 11.5;
-// 1001 x 750 R = 21 FP64 65 -> 30; 512^2 R = 16 7.6 -> 5.4.
+// split by tiles and 3 or 4 steps per pass: 2048^2 R = 64 FP32 230 -> 164 us, FP64
+// 628 -> 414; 1024^2 spin R = 32 FP32 113 -> 80; 339^2 spin R = 34 18.9 -> 12.3;
+// 1001 x 750 R = 21 FP64 62 -> 32; 512^2 R = 16 8.1 -> 6.1.
 // Tilings of more than max_tiles items are passed over; false if none is left.
 bool tb_plan(const kpm_ham *h, Plan &p, uint64_t max_tiles = ~0ull)
 {
@@ -664,7 +666,7 @@ bool tb_plan(const kpm_ham *h, Plan &p, uint64_t max_tiles = ~0ull)
 // are kept), and beyond them those of at most SMALL_SITES sites, in launches of up to P_slots
 // steps with the state in the workspace between.  At 2048 sites a step takes about 1 us
 // against 3.5 to 5 us of a launch per step; with more sites per workgroup the launches
-// win (16^3 spin FP32 3.6 us per step).
+// win (16^3 spin FP32, R = 8: 4.1 us per step).
 //
 // A CSR row is walked one entry at a time there, its columns and values read by every group
 // of chunks from the caches, so a step takes about 1 us and 0.3 us per entry of a row (64
@@ -753,8 +755,8 @@ bool make_plan(const kpm_ham *h, int32_t M, int32_t R, int32_t vec, Plan &p, boo
                h->L[1] >= 2 * tb_halo(h->prec, h->opk, p.C / tb_groups(p.C, (uint32_t)h->L[0]),
                                       tb_groups(p.C, (uint32_t)h->L[0]) > 1)) {
         // several steps per pass: the site's chunks in tbg groups, windows of
-        // floor(TB_BLOCK/Cg) sites of one group (Cg = C/tbg; threads beyond window * Cg
-        // idle), x-tiles of the window less 2 tbh halo sites, segments of rows
+        // floor(TB_BLOCK/Cg) sites of one group (Cg = tbw chunks, the last group perhaps fewer;
+        // threads beyond window * Cg idle), x-tiles of the window less 2 tbh halo sites, segments of rows
         p.mode = MODE_TB;
         p.nbuf = 4;
         tb_plan(h, p);
@@ -780,11 +782,12 @@ bool make_plan(const kpm_ham *h, int32_t M, int32_t R, int32_t vec, Plan &p, boo
                                  stream_choice(2ull * h->N * p.Rs * p.esz + (uint64_t)h->N * 7 * p.esz) == 1;
         p.grid_cap = spin_stream ? std::max<uint32_t>(8, (uint32_t)g_max_blocks / 32 * 8) : (uint32_t)g_max_blocks;
         // Segments: as many as give the target work items (two blocks per CU), down to two
-        // planes each, in small lattices one.  A launch of a small lattice lasts as long as one block's planes, each
-        // a load's latency; held to 8 planes or more, 16^3 to 48^3 lattices filled a fraction
-        // of the chip.  us per step, 8 planes -> now (R): spin FP32 16^3 (8) 8.8 -> 3.6, 32^3
-        // (16) 11.7 -> 5.6, 40^3 (16) 11.1 -> 7.8, 70 x 50 x 33 (9) 15.4 -> 9; FP64 32^3 (16)
-        // 11.6 -> 9.0, real FP64 16^3 (8) 9.3 -> 4.0.  From 48^3 (R = 16) up both rules agree.
+        // planes each, in small lattices one.  A launch of a small lattice lasts as long as one
+        // block's planes, each a load's latency; held to 8 planes or more, 16^3 to 48^3 lattices
+        // filled a fraction of the chip.  us per step, 8 planes -> now (R): spin FP32 16^3 (8)
+        // 9.1 -> 4.1, 32^3 (16) 12.0 -> 6.3, 40^3 (16) 11.2 -> 8.3, 70 x 50 x 33 (9) 15.9 -> 8.9;
+        // FP64 32^3 (16) 12.2 -> 9.2, real FP64 16^3 (8) 10.2 -> 4.2.  From 48^3 (R = 16) up both
+        // rules agree.
         uint32_t nseg;
         if (spin_stream) {
             nseg = (uint32_t)((4ull * (uint64_t)g_march_items + p.nct - 1) / p.nct);
@@ -809,8 +812,9 @@ bool make_plan(const kpm_ham *h, int32_t M, int32_t R, int32_t vec, Plan &p, boo
         p.nseg = (p.Lm + p.S - 1) / p.S;
         p.tiles = p.nct * p.nseg;
         // each XCD an eighth of the items, in plane order.  Split by column tiles instead, the
-        // XCDs differ by up to a tile's whole column: 100^3 lattices 43.8 -> 28.4 us per step
-        // (spin FP32, R = 5), 53.4 -> 36.3 (real FP64, R = 8).  The streamed FP32 spin solves,
+        // XCDs differ by up to a tile's whole column: 100^3 lattices 47.6 -> 30.1 us per step
+        // (spin FP32, R = 5), 54.4 -> 34.4 (real FP64, R = 8); where the tiles divide evenly the two
+        // are within 4% of each other, but for 64 x 64 x 20 and 45^3 (R = 24, 33: 9-10% slower).  The streamed FP32 spin solves,
         // a quarter of the blocks, keep the tiles together (even shares 3-6% slower)
         p.xcd = spin_stream ? (p.nct >= XCD_MIN_ITEMS ? 1 : 0) : (p.tiles >= XCD_MIN_ITEMS ? 3 : 0);
         if (g_xcd_split == 1) p.xcd = p.nct >= XCD_MIN_ITEMS ? 1 : 0;

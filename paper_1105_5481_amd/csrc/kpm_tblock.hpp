@@ -13,8 +13,8 @@
 // once) and the outputs (written once) use non-temporal accesses when the
 // instance streams.
 //
-// What bounds a pass: at 2048^2 sites, R = 64, FP32, six steps in 995 us move 4.5
-// vector streams (4.8 TB/s, a plain copy reaches 5.0) and issue 55 vector
+// What bounds a pass: at 2048^2 sites, R = 64, FP32, six steps in 977 us move 4.4
+// vector streams (4.9 TB/s, a plain copy reaches 5.0) and issue 55 vector
 // instructions per chunk and step (70% of the vector ALU's rate).
 #pragma once
 
@@ -23,9 +23,9 @@ namespace kpm {
 constexpr uint32_t TB_BLOCK = 256;
 constexpr int TB_DMAX = 6;   // deepest pass
 // Blocks per CU (= waves per SIMD) a pass is held to: the VGPR budget is 512 over this
-// (FP32 four steps 118 of 128, six 152 of 168; FP64 five 165 real, 176 spin, six 194),
+// (FP32 four steps 118 of 128, six 152 of 168; FP64 five 165 real, 176 spin, six 187 and 194),
 // and its D levels of 8 KiB LDS fit as often.  Blocks of 256 threads: of 512, two per
-// CU, with the same tiles measured 1.2-1.5x slower (235 -> 166 us per step on the 2048^2
+// CU, with the same tiles measured 1.2-1.5x slower (230 -> 164 us per step on the 2048^2
 // lattice at R = 64), their barriers tie twice the waves together.
 constexpr int TB_WAVES_PER_EU(bool f64, bool spin, int D)
 {
