@@ -2025,7 +2025,7 @@ namespace {
 // Columns per solve: the vectors of one solve share each site's bonds, and fill the chunks
 // that a solve of one vector leaves half or three quarters empty; as many as keep the
 // state in the Infinity Cache, at most COLS_MAX (their partials, 512 bytes per item and
-// column, stay below 70 MB).  us per step of all solves, at most 64 / 128 / 256 columns each:
+// column, stay below 100 MB).  us per step of all solves, at most 64 / 128 / 256 columns each:
 // 256 sites of 100^2 real FP32 28.5 / 18.5 / 10.4, of 20^3 real FP64 36.8 / 21.2 / 16.8, of 32^3
 // spin FP32 56.4 / 44.0 / 38.7, 126 of 48^3 spin FP32 80.4 / 78.7 / 78.4 (the cache's limit).
 // Against one solve per site, all in one batch: 64 sites of 48^3 spin FP32 80.6 -> 40.7, 9 sites
